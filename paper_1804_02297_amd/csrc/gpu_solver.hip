@@ -1383,6 +1383,303 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) =
   }
 }
 
+// Five to kThinRhs right-hand sides: the products of fwd_sb_kernel (KIND 0),
+// bwd_sb_kernel (KIND 1) and bwd_u12_kernel (KIND 2) with 16 rows and CT tiles
+// of 16 rhs per wave, four row tiles per workgroup.
+// What bounds it: with a few rhs the factor streams through once (memory) at
+// the wide levels, and at the top of the tree each launch is a chain of
+// latencies.  The 64 x 64 LDS tiles of the kernels above multiplied mostly
+// zero columns at 16 rhs (four times the FP64 MFMAs), kept a 6912-row front to
+// 108 workgroups, and staged every factor value through LDS between two
+// barriers.  Here the right-hand sides go to LDS once (KST of them at a time:
+// 48 KB in FP64, three workgroups per CU) and each lane loads its factor
+// operands itself, D chunks of 16 columns ahead; the rows a wave updates are
+// read before its products.  A lane loads four consecutive columns of its row
+// and to_mfma turns them into one column of each of four MFMA steps: loaded
+// straight in the MFMA layout (neighbouring lanes in different rows, one value
+// each) the address unit took 64 cycles per instruction for a quarter of the
+// data, 10 of the 17 us of a top-of-tree launch.
+// Blocks of M right of a row's own 48-row tile and entries of H left of the
+// diagonal are exact zeros and are skipped.  SPLIT (FP64 launches of about a
+// wave per SIMD): two waves per row tile, one the real, one the imaginary
+// part, because four dependent FP64 MFMAs per four columns are what such a
+// launch waits for.  Every output keeps the order of products of the LDS
+// kernels (K ascending in steps of four into the same accumulators), so blocks
+// of any size above kGemvRhs agree bit for bit.
+// Measured, 16 rhs: complex128 preconditioner apply at n = 48 25.4 -> 8.4 ms;
+// complex64 block FGMRES at n = 32 30.9 -> 17.0 ms; a launch at the top of the
+// tree 23.5 (FP64) and 17 us (FP32) -> 14.7 and 8 us.
+constexpr int kThinRhs = 32;
+constexpr int kThinPad = 256;   // factor values past the end that thin_kernel may read
+// Four consecutive values from p (aligned to one value only), 16 bytes a load.
+__device__ __forceinline__ void load4(const float* p, float (&v)[4]) {
+  typedef float f4 __attribute__((ext_vector_type(4), aligned(4)));
+  const f4 t = *reinterpret_cast<const f4*>(p);
+  v[0] = t.x;
+  v[1] = t.y;
+  v[2] = t.z;
+  v[3] = t.w;
+}
+__device__ __forceinline__ void load4(const double* p, double (&v)[4]) {
+  typedef double d2 __attribute__((ext_vector_type(2), aligned(8)));
+  const d2 a = reinterpret_cast<const d2*>(p)[0], b = reinterpret_cast<const d2*>(p)[1];
+  v[0] = a.x;
+  v[1] = a.y;
+  v[2] = b.x;
+  v[3] = b.y;
+}
+// v[j] of lane group g (lanes 16 g ..) and v[g] of lane group j change places:
+// from four consecutive columns per lane to one column of each MFMA step.
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+template <typename F>
+__device__ __forceinline__ void swap_halves(double& a, double& b, F f) {
+  float al = __int_as_float(__double2loint(a)), ah = __int_as_float(__double2hiint(a));
+  float bl = __int_as_float(__double2loint(b)), bh = __int_as_float(__double2hiint(b));
+  f(al, bl);
+  f(ah, bh);
+  a = __hiloint2double(__float_as_int(ah), __float_as_int(al));
+  b = __hiloint2double(__float_as_int(bh), __float_as_int(bl));
+}
+__device__ __forceinline__ void swap32(double& a, double& b) {
+  swap_halves(a, b, [](float& x, float& y) { swap32(x, y); });
+}
+__device__ __forceinline__ void swap16(double& a, double& b) {
+  swap_halves(a, b, [](float& x, float& y) { swap16(x, y); });
+}
+template <typename R>
+__device__ __forceinline__ void to_mfma(R (&v)[4]) {
+  swap32(v[0], v[2]);
+  swap32(v[1], v[3]);
+  swap16(v[0], v[1]);
+  swap16(v[2], v[3]);
+}
+
+template <typename R, int KIND, int CT, bool SPLIT>
+__global__ __launch_bounds__(SPLIT ? 128 : 256) __attribute__((amdgpu_waves_per_eu(SPLIT ? 1 : 2))) void thin_kernel(
+    const FrontDev* __restrict__ fr, const int* __restrict__ lvl, int nlvl, int kb0, int nks_max, long np_max,
+    const R* __restrict__ fac, const int* __restrict__ ib, int nrhs, R* __restrict__ Xr, R* __restrict__ Xi,
+    R* __restrict__ Zr, R* __restrict__ Zi, R* __restrict__ Ur, R* __restrict__ Ui, R* __restrict__ Pr,
+    R* __restrict__ Pi) {
+  typedef typename Mma<R>::v4 v4;
+  constexpr bool G3 = sizeof(R) == 4;    // three real products per complex one, as CAcc
+  static_assert(!(G3 && SPLIT), "the three-product form needs all its sums in one wave");
+  constexpr int NZ = kSB / 16;           // row tiles of the block itself (KIND 0, 1)
+  constexpr int NT = SPLIT ? 128 : 256;
+  constexpr int TPW = SPLIT ? 1 : 4;     // row tiles per workgroup
+  constexpr int D = SPLIT && CT == 1 ? 6 : !G3 && CT == 2 ? 2 : 4;   // chunks of 16 columns in flight
+  constexpr int KST = kSB / CT, W = 16 * CT;
+  static_assert(NZ % TPW == 0, "a workgroup's tiles are all of the block or all outside it");
+  __shared__ R Bsr[KST * W], Bsi[KST * W];
+  const int tid = threadIdx.x, lane = tid & 63, lr = lane & 15, g = lane >> 4;
+  const int part = SPLIT ? (tid >> 6) & 1 : 0;
+  const int tile0 = blockIdx.x * TPW, tile = tile0 + (SPLIT ? 0 : tid >> 6);
+  const int ks = blockIdx.z;
+  bool first = true;
+  for (int q = blockIdx.y; q < nlvl; q += gridDim.y) {
+    const FrontDev d = fr[lvl[q]];
+    // the whole descriptor in one go: read where they are used, its fields
+    // would be a chain of dependent scalar loads
+    asm volatile("" ::"s"(d.np), "s"(d.nb), "s"(d.nf), "s"(d.e0), "s"(d.p), "s"(d.l), "s"(d.u), "s"(d.m), "s"(d.h),
+                 "s"(d.bm));
+    const long nf = d.nf, np = d.np, nb = d.nb;
+    const bool own = KIND != 2 && tile0 < NZ;   // rows of the block: z = M x or x = H y
+    long rb, re;                                // rows of this launch part: [rb, re)
+    int K, nks = 1;
+    if (KIND == 2) {
+      nks = (int)((nb + kKS - 1) / kKS);
+      if (ks >= nks) continue;
+      K = (int)min((long)kKS, nb - (long)ks * kKS);
+      rb = 0;
+      re = np;
+    } else {
+      if (kb0 >= np) continue;
+      K = (int)min((long)kSB, np - kb0);
+      rb = own || KIND == 1 ? 0 : kb0 + K;
+      re = own ? K : (KIND == 0 ? nf : kb0);
+    }
+    const int toff = KIND == 2 || own ? 0 : NZ;
+    if (rb + 16L * (tile0 - toff) >= re) continue;
+    const long i0 = rb + 16L * (tile - toff);
+    const bool active = i0 < re;
+    const int cnt = active ? (int)min(16L, re - i0) : 1;
+    int k0 = 0, k1 = K;
+    if (own && KIND == 0) k1 = min(K, ((int)i0 / kT + 1) * kT);
+    if (own && KIND == 1) k0 = (int)i0;
+    // this lane's factor row (rows past cnt repeat the last, unused)
+    const long gi = active ? i0 + min(lr, cnt - 1) : rb;
+    const R* ar;
+    long im;                                    // distance to the imaginary plane
+    if (KIND == 2) {
+      ar = fac + d.p + gi * nf + np + (long)ks * kKS;
+      im = np * nf;
+    } else if (own) {
+      ar = fac + (KIND == 0 ? d.m : d.h) + (long)(kb0 / kSB) * 2 * kSB * kSB + gi * kSB;
+      im = (long)kSB * kSB;
+    } else if (KIND == 1 || gi < np) {
+      ar = fac + d.p + gi * nf + kb0;
+      im = np * nf;
+    } else {
+      ar = fac + d.l + (gi - np) * np + kb0;
+      im = nb * np;
+    }
+    // Chunks of 16 columns from kc on, up to D past the row's end (never used;
+    // the factor's allocation is kThinPad longer for the last row): no bounds,
+    // so the loads in flight are counted exactly.
+    ar += 4 * g;
+    const R* ai = ar + im;
+    R fr_[D][4], fi_[D][4];
+    auto fetch = [&](int u, int kc) {
+      load4(ar + kc, fr_[u]);
+      load4(ai + kc, fi_[u]);
+    };
+    const long eb = d.e0 + kb0;
+    // destinations; the rows updated in place are read ahead of the products
+    long dst[4];
+    const bool upd = KIND == 2 ? nks == 1 : !own;
+    R* const Tr = KIND == 2 ? (nks > 1 ? Pr : Zr) : (KIND == 0) == own ? Zr : Xr;
+    R* const Ti = KIND == 2 ? (nks > 1 ? Pi : Zi) : (KIND == 0) == own ? Zi : Xi;
+    bool bnd[4];
+    R or_[CT][4], oi_[CT][4];
+    int col[CT];
+#pragma unroll
+    for (int c = 0; c < CT; ++c) col[c] = min(16 * c + lr, nrhs - 1);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const long row = active ? i0 + min(Mma<R>::row(lane, r), cnt - 1) : rb;
+      bnd[r] = KIND == 0 && !own && row >= np;
+      if (KIND == 2 && nks > 1)
+        dst[r] = (((long)q * nks_max + ks) * np_max + row) * nrhs;
+      else if (own)
+        dst[r] = (eb + row) * nrhs;
+      else
+        dst[r] = (bnd[r] ? d.u + row - np : d.e0 + row) * nrhs;
+      if (upd)
+#pragma unroll
+        for (int c = 0; c < CT; ++c) {
+          or_[c][r] = (bnd[r] ? Ur : Tr)[dst[r] + col[c]];
+          oi_[c][r] = (bnd[r] ? Ui : Ti)[dst[r] + col[c]];
+        }
+    }
+    v4 p[3][CT];
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+#pragma unroll
+      for (int c = 0; c < CT; ++c) p[m][c] = v4{R(0), R(0), R(0), R(0)};
+    for (int st = 0; st < K; st += KST) {
+      const int se = min(K, st + KST);
+      const int a0 = max(k0, st), a1 = min(k1, se);
+      if (active && a0 < a1)
+#pragma unroll
+        for (int u = 0; u < D; ++u) fetch(u, a0 + 16 * u);
+      __builtin_amdgcn_sched_barrier(0);
+      // this stage's right-hand sides, zeros past its last column
+      constexpr int NU = KST * W / NT;
+      R vr[NU], vi[NU];
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const int kk = min(st + (tid + NT * u) / W, K - 1), c = (tid + NT * u) % W;
+        const long e = KIND == 2 ? (long)ib[d.bm + (long)ks * kKS + kk] : eb + kk;
+        const long o = e * nrhs + min(c, nrhs - 1);
+        vr[u] = (KIND == 1 ? Zr : Xr)[o];
+        vi[u] = (KIND == 1 ? Zi : Xi)[o];
+      }
+      __builtin_amdgcn_sched_barrier(0);
+      if (!first) __syncthreads();              // the previous stage's reads are done
+      first = false;
+#pragma unroll
+      for (int u = 0; u < NU; ++u) {
+        const bool in = st + (tid + NT * u) / W < se;
+        Bsr[tid + NT * u] = in ? vr[u] : R(0);
+        Bsi[tid + NT * u] = in ? vi[u] : R(0);
+      }
+      __syncthreads();
+      if (!active) continue;
+      R br_[2][CT][4], bi_[2][CT][4];           // LDS operands, one chunk ahead
+      auto rhs = [&](int b, int kc) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {
+            const int o = min(kc - st + 4 * s + g, KST - 1) * W + lr + 16 * c;
+            br_[b][c][s] = Bsr[o];
+            bi_[b][c][s] = Bsi[o];
+          }
+      };
+      auto mul = [&](int u, int b) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s)
+#pragma unroll
+          for (int c = 0; c < CT; ++c) {
+            const R br = br_[b][c][s], bi = bi_[b][c][s];
+            if constexpr (G3) {
+              p[0][c] = Mma<R>::op(fr_[u][s], br, p[0][c]);
+              p[1][c] = Mma<R>::op(fi_[u][s], bi, p[1][c]);
+              p[2][c] = Mma<R>::op(fr_[u][s] + fi_[u][s], br + bi, p[2][c]);
+            } else if constexpr (SPLIT) {       // re: ar br - ai bi; im: ar bi + ai br
+              p[0][c] = Mma<R>::op(fr_[u][s], part ? bi : br, p[0][c]);
+              p[0][c] = Mma<R>::op(part ? fi_[u][s] : -fi_[u][s], part ? br : bi, p[0][c]);
+            } else {
+              p[0][c] = Mma<R>::op(fr_[u][s], br, p[0][c]);
+              p[0][c] = Mma<R>::op(-fi_[u][s], bi, p[0][c]);
+              p[1][c] = Mma<R>::op(fr_[u][s], bi, p[1][c]);
+              p[1][c] = Mma<R>::op(fi_[u][s], br, p[1][c]);
+            }
+          }
+      };
+      static_assert(D % 2 == 0, "the LDS operands alternate between two sets");
+      int kc = a0;
+      rhs(0, kc);
+      for (; kc + 16 * D < a1; kc += 16 * D)
+#pragma unroll
+        for (int u = 0; u < D; ++u) {
+          rhs((u + 1) & 1, kc + 16 * (u + 1));
+          to_mfma(fr_[u]);
+          to_mfma(fi_[u]);
+          __builtin_amdgcn_sched_barrier(0);
+          mul(u, u & 1);
+          fetch(u, kc + 16 * (u + D));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+      for (int u = 0; u < D; ++u)
+        if (kc + 16 * u < a1) {
+          to_mfma(fr_[u]);
+          to_mfma(fi_[u]);
+#pragma unroll
+          for (int s = 0; s < 4; ++s)           // columns past the end of the last chunk
+            if (kc + 16 * u + 4 * s + g >= a1) fr_[u][s] = fi_[u][s] = R(0);
+          if (u + 1 < D) rhs((u + 1) & 1, kc + 16 * (u + 1));
+          __builtin_amdgcn_sched_barrier(0);
+          mul(u, u & 1);
+        }
+    }
+    if (!active) continue;
+#pragma unroll
+    for (int c = 0; c < CT; ++c) {
+      v4 cr = p[0][c], ci = SPLIT ? p[0][c] : p[1][c];
+      if constexpr (G3) {
+        cr = p[0][c] - p[1][c];
+        ci = p[2][c] - p[0][c] - p[1][c];
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        if (Mma<R>::row(lane, r) < cnt && 16 * c + lr < nrhs) {
+          if (!SPLIT || part == 0) (bnd[r] ? Ur : Tr)[dst[r] + col[c]] = upd ? or_[c][r] - cr[r] : cr[r];
+          if (!SPLIT || part == 1) (bnd[r] ? Ui : Ti)[dst[r] + col[c]] = upd ? oi_[c][r] - ci[r] : ci[r];
+        }
+    }
+  }
+}
+
 // Few right-hand sides (at most kGemvRhs): the products of fwd_sb_kernel
 // (FWD) and bwd_sb_kernel as matrix-vector products, kGemvLanes lanes per
 // row with the block's vector in LDS (the 64-rhs MFMA tiles would compute mostly zero
@@ -1694,10 +1991,41 @@ ls_status factor_numeric(GpuSolver& g, const C<double>* rows, hipStream_t s) {
 // workgroups; the factor blocks are then read once per 32 rhs.
 constexpr long kSplitWg = 512;
 
+// FP64 launches of fewer row tiles than this (about a wave per SIMD) take
+// thin_kernel's SPLIT form.
+constexpr long kSplitTiles = 1024;
+
+// tiles: 16-row tiles of the launch, those of the super-block itself included.
+template <typename R, int KIND>
+void launch_thin(long tiles, unsigned gy, unsigned gz, hipStream_t s, const FrontDev* fr, const int* lvl, int nl,
+                 int kb0, int nks, long np_max, const R* fac, const int* ib, int nrhs, R* Xr, R* Xi, R* Zr, R* Zi,
+                 R* Ur, R* Ui, R* Pr, R* Pi) {
+  if constexpr (sizeof(R) == 8) {
+    if (tiles * gy * gz < kSplitTiles) {
+      const auto kern = nrhs <= 16 ? thin_kernel<R, KIND, 1, true> : thin_kernel<R, KIND, 2, true>;
+      hipLaunchKernelGGL(kern, dim3((unsigned)std::max(1L, tiles), gy, gz), dim3(128), 0, s, fr, lvl, nl, kb0, nks,
+                         np_max, fac, ib, nrhs, Xr, Xi, Zr, Zi, Ur, Ui, Pr, Pi);
+      return;
+    }
+  }
+  const auto kern = nrhs <= 16 ? thin_kernel<R, KIND, 1, false> : thin_kernel<R, KIND, 2, false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)std::max(1L, (tiles + 3) / 4), gy, gz), dim3(256), 0, s, fr, lvl, nl, kb0,
+                     nks, np_max, fac, ib, nrhs, Xr, Xi, Zr, Zi, Ur, Ui, Pr, Pi);
+}
+
 template <typename R>
 void launch_sb(bool fwd, unsigned gx, unsigned gy, int nrhs, hipStream_t s, const FrontDev* fr, const int* lvl,
                int nl, int kb0, const R* fac, R* Xr, R* Xi, R* Zr, R* Zi, R* Ur, R* Ui) {
   const unsigned gz = (unsigned)((nrhs + kSR - 1) / kSR);
+  if (nrhs <= kThinRhs) {
+    if (fwd)
+      launch_thin<R, 0>(gx * (kRB / 16L), gy, 1, s, fr, lvl, nl, kb0, 1, 0, fac, nullptr, nrhs, Xr, Xi, Zr, Zi, Ur,
+                        Ui, nullptr, nullptr);
+    else
+      launch_thin<R, 1>(gx * (kRB / 16L), gy, 1, s, fr, lvl, nl, kb0, 1, 0, fac, nullptr, nrhs, Xr, Xi, Zr, Zi, Ur,
+                        Ui, nullptr, nullptr);
+    return;
+  }
   if constexpr (sizeof(R) == 4) {
     if ((long)gx * gy * gz < kSplitWg) {
       const unsigned gz2 = (unsigned)((nrhs + 31) / 32);
@@ -1801,6 +2129,9 @@ ls_status solve_numeric(GpuSolver& g, const C<double>* b, C<double>* xo, int nrh
                                                   nks[dep]),
                          dim3(256), 0, s, fr, lvl, nl, nks[dep], mnp, fac, ib, nrhs, (const R*)Xr, (const R*)Xi, Zr,
                          Zi, Pr, Pi);
+    else if (nrhs <= kThinRhs)
+      launch_thin<R, 2>((mnp + 15) / 16, gy, (unsigned)nks[dep], s, fr, lvl, nl, 0, nks[dep], mnp, fac, ib, nrhs, Xr,
+                        Xi, Zr, Zi, Ur, Ui, Pr, Pi);
     else
       hipLaunchKernelGGL(bwd_u12_kernel<R>, dim3(gu, gy, gz * nks[dep]), dim3(256), 0, s, fr, lvl, nl, nks[dep],
                          mnp, fac, ib, nrhs, (const R*)Xr, (const R*)Xi, Zr, Zi, Pr, Pi);
@@ -1860,7 +2191,7 @@ ls_status gpu_factor_grid(const int dims[3], int nc, const C<double>* rows_dev, 
   const long fac_elems = sym.fac_elems;
   const IntMap& ibh = sym.ibh;
   const size_t rs = fp32 ? sizeof(float) : sizeof(double);
-  LS_TRY(g->fac.alloc((size_t)fac_elems * rs));
+  LS_TRY(g->fac.alloc((size_t)(fac_elems + kThinPad) * rs));
   LS_TRY(g->ib.alloc(ibh.size() * sizeof(int)));
   LS_TRY(g->ipm.alloc((size_t)std::max(1L, g->N) * sizeof(int)));
   LS_TRY(g->fd.alloc(g->fh.size() * sizeof(FrontDev)));

@@ -196,3 +196,21 @@ def test_gpu_factor_state_errors(lib):
     with pytest.raises(LSError) as e:
         SparseGpu(2, np.zeros((8, 3, 27, 3), np.complex128))   # below the smallest grid
     assert e.value.code == -1
+
+
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+def test_thin_block_solves_equal_wide_ones(lib, prec):
+    """5 to 32 right-hand sides (16-row tiles, one or two tiles of 16 rhs) on
+    fronts of several super-blocks with ragged last tiles, odd row strides and
+    split boundary products: bit for bit the columns of a 33-rhs solve, which
+    takes the 64-rhs tiles."""
+    from paper_1804_02297_amd.binding import SparseGpu
+    n = 15
+    _, rows = _oracle_system(n, 9)
+    sp = SparseGpu(n, rows, prec=prec)
+    b = I.random_field(33, n, 81)
+    full = sp.solve(_dev(b)).cpu().numpy()
+    for nr in (5, 15, 16, 17, 31, 32):
+        print(f"{prec} {nr} rhs", flush=True)
+        assert np.array_equal(sp.solve(_dev(b[:nr])).cpu().numpy(), full[:nr]), nr
+    sp.close()
