@@ -10,8 +10,8 @@
 //   zero the fronts; assemble S's entries; extend-add the children's update
 //   blocks (child 0, then child 1: their targets overlap); then for each
 //   48-column step kb of the pivot block:
-//     diag_kernel   LU of the 48 x 48 diagonal tile in LDS, pivots searched
-//                   among the tile's rows; the tile's L^-1 and U^-1
+//     diag_kernel   LU of the 48 x 48 diagonal tile, pivots searched among
+//                   the tile's rows
 //     panel_kernel  L below the tile (l U = f) and U right of it (L u = P f),
 //                   by substitution
 //     schur_kernel  F -= L U on the trailing block, complex product on
@@ -161,179 +161,322 @@ __global__ __launch_bounds__(256) void extend_add_kernel(const FrontDev* __restr
   }
 }
 
+// Lane-swap instructions: swap32 exchanges lanes 32.. of a with lanes 0..31 of b,
+// swap16 the odd rows of 16 lanes of a with the even rows of b.
+__device__ __forceinline__ void swap32(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap16(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+template <typename F>
+__device__ __forceinline__ void swap_halves(double& a, double& b, F f) {
+  float al = __int_as_float(__double2loint(a)), ah = __int_as_float(__double2hiint(a));
+  float bl = __int_as_float(__double2loint(b)), bh = __int_as_float(__double2hiint(b));
+  f(al, bl);
+  f(ah, bh);
+  a = __hiloint2double(__float_as_int(ah), __float_as_int(al));
+  b = __hiloint2double(__float_as_int(bh), __float_as_int(bl));
+}
+__device__ __forceinline__ void swap32(double& a, double& b) {
+  swap_halves(a, b, [](float& x, float& y) { swap32(x, y); });
+}
+__device__ __forceinline__ void swap16(double& a, double& b) {
+  swap_halves(a, b, [](float& x, float& y) { swap16(x, y); });
+}
+
+// Largest of v over a wave, in every lane: rotations inside the rows of 16
+// lanes, then the two lane-swap instructions across rows.
+template <int ROT>
+__device__ __forceinline__ float row_ror(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0x120 + ROT, 0xF, 0xF, false));
+}
+template <int ROT>
+__device__ __forceinline__ double row_ror(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), 0x120 + ROT, 0xF, 0xF, false),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), 0x120 + ROT, 0xF, 0xF, false));
+}
+template <typename R>
+__device__ __forceinline__ R wave_max(R v) {
+  v = fmax(v, row_ror<8>(v));
+  v = fmax(v, row_ror<4>(v));
+  v = fmax(v, row_ror<2>(v));
+  v = fmax(v, row_ror<1>(v));
+  R w = v;
+  swap16(v, w);
+  v = fmax(v, w);
+  w = v;
+  swap32(v, w);
+  return fmax(v, w);
+}
+
+__device__ __forceinline__ float lane_value(float v, int l) {
+  return __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), l));
+}
+__device__ __forceinline__ double lane_value(double v, int l) {
+  return __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(v), l),
+                          __builtin_amdgcn_readlane(__double2loint(v), l));
+}
+
 // LU with partial pivoting of the diagonal tile [kb, kb + tw)^2 of every front
-// of a level (one workgroup per front), then the tile's L^-1 (unit lower) and
-// U^-1 (upper), stored for the panel kernel and the solves.
+// of a level, one workgroup per front.
+// What bounds it: 48 dependent elimination steps in one workgroup, launched
+// 126 times one after another in an n = 29 factor; a step's time is its
+// instruction count, one wave per SIMD.  So the tile is taken in three panels
+// of 16 columns, a lane per row and the panel's columns in registers: a step
+// needs no LDS and no barrier (the pivot row is read from its lane, rows are
+// exchanged by renaming, lpos, instead of moving them).  Every wave factors the panel for
+// itself and updates four columns of each later panel; the panels meet in
+// LDS, two barriers each.  The tile's inverses, which only the solves need,
+// are formed for a whole level at once (tile_inverse_kernel).  FP64, average
+// launch of the n = 29 factor: 36 us (204 us with the tile in LDS, six barriers
+// a step and the inverses in the same launch); FP32 30 us (219 us).
 template <typename R>
 __global__ __launch_bounds__(256) void diag_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl, int nlvl,
-                                                   int kb, R* __restrict__ buf, R* __restrict__ fac,
-                                                   int* __restrict__ ib) {
-  __shared__ R Dr[kT][kT + 1], Di[kT][kT + 1];
-  __shared__ R Xr[kT][kT + 1], Xi[kT][kT + 1];
-  __shared__ int perm[kT];
-  __shared__ int piv;
-  const int tid = threadIdx.x;
+                                                   int kb, R* __restrict__ buf, int* __restrict__ ib) {
+  static_assert(kT == 48, "three panels of 16 columns, 48 rows in the lanes of a wave");
+  __shared__ R Sr[kT][kT + 1], Si[kT][kT + 1];   // the tile, rows as loaded
+  __shared__ int rowof[kT];                      // position in pivot order -> row as loaded
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, row = min(lane, kT - 1);
   for (int q = blockIdx.x; q < nlvl; q += gridDim.x) {
     const FrontDev d = fr[lvl[q]];
     if (kb >= d.np) continue;
     const int tw = min(kT, d.np - kb);
     const long nf = d.nf;
-    R* Fr = buf + d.f;
+    R* Fr = buf + d.f + kb * nf + kb;
     R* Fi = Fr + nf * nf;
-    for (int o = tid; o < tw * tw; o += blockDim.x) {
-      const int i = o / tw, c = o % tw;
-      Dr[i][c] = Fr[(kb + i) * nf + kb + c];
-      Di[i][c] = Fi[(kb + i) * nf + kb + c];
-    }
-    if (tid < tw) perm[tid] = tid;
-    __syncthreads();
-    for (int j = 0; j < tw; ++j) {
-      if (tid < 64) {
-        R v = R(-1);
-        int idx = tid;
-        if (tid >= j && tid < tw) v = Dr[tid][j] * Dr[tid][j] + Di[tid][j] * Di[tid][j];
+    __syncthreads();                             // the previous front's LDS reads are done
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) {
-          const R ov = __shfl_xor(v, off);
-          const int oi = __shfl_xor(idx, off);
-          if (ov > v || (ov == v && oi < idx)) {
-            v = ov;
-            idx = oi;
+    for (int u = 0; u < kT * kT / 256; ++u) {
+      const int o = tid + 256 * u, i = o / kT, c = o % kT;
+      const bool in = i < tw && c < tw;
+      Sr[i][c] = in ? Fr[i * nf + c] : R(0);
+      Si[i][c] = in ? Fi[i * nf + c] : R(0);
+    }
+    __syncthreads();
+    R tr[2][4], ti[2][4];                        // this wave's columns of panels 1 and 2
+#pragma unroll
+    for (int g = 0; g < 2; ++g)
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        tr[g][c] = Sr[row][16 * (g + 1) + 4 * wave + c];
+        ti[g][c] = Si[row][16 * (g + 1) + 4 * wave + c];
+      }
+    int lpos = lane;                             // place of this lane's row in pivot order
+    for (int pb = 0; pb < 3; ++pb) {
+      R ar[16], ai[16];
+#pragma unroll
+      for (int c = 0; c < 16; ++c) {
+        ar[c] = Sr[row][16 * pb + c];
+        ai[c] = Si[row][16 * pb + c];
+      }
+      static_for<0, 16>([&](auto JJ) {              // a constant column index keeps the panel in registers
+        constexpr int jj = decltype(JJ)::value;
+        const int j = 16 * pb + jj;
+        if (j >= tw) return;
+        // the pivot: largest |x|^2 among the rows not yet used, the first of them in pivot order
+        const R xr = ar[jj], xi = ai[jj];
+        const bool cand = lpos >= j && lpos < tw;
+        const R v = cand ? xr * xr + xi * xi : R(-1);
+        const R best = wave_max(v);
+        unsigned long long eq = __ballot(cand && v == best);
+        if (eq == 0) eq = __ballot(lpos == j);   // NaN only
+        int prow = __ffsll(eq) - 1;
+        for (unsigned long long m = eq & (eq - 1); m; m &= m - 1) {
+          const int o = __ffsll(m) - 1;
+          if (__builtin_amdgcn_readlane(lpos, o) < __builtin_amdgcn_readlane(lpos, prow)) prow = o;
+        }
+        prow = __builtin_amdgcn_readfirstlane(prow);
+        const int pp = __builtin_amdgcn_readlane(lpos, prow);
+        lpos = lpos == j ? pp : lpos == pp ? j : lpos;
+        R pr = lane_value(xr, prow), pi = lane_value(xi, prow);
+        if (pr == R(0) && pi == R(0)) {          // exactly singular tile: perturb (FGMRES absorbs it)
+          pr = sqrt(std::numeric_limits<R>::min());
+          if (lane == prow) ar[jj] = pr;
+        }
+        const R den = pr * pr + pi * pi;
+        const R ir = pr / den, ii = -pi / den;
+        const bool below = lpos > j;
+        const R lr = below ? xr * ir - xi * ii : R(0), li = below ? xr * ii + xi * ir : R(0);
+        ar[jj] = below ? lr : ar[jj];
+        ai[jj] = below ? li : ai[jj];
+        auto update = [&](R& xr, R& xi) {        // x -= l u, u this column's value in the pivot row
+          const R ur = lane_value(xr, prow), ui = lane_value(xi, prow);
+          xr = fma(li, ui, fma(-lr, ur, xr));
+          xi = fma(-li, ur, fma(-lr, ui, xi));
+        };
+#pragma unroll
+        for (int c = jj + 1; c < 16; ++c) update(ar[c], ai[c]);
+        if (pb < 1)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) update(tr[0][c], ti[0][c]);
+        if (pb < 2)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) update(tr[1][c], ti[1][c]);
+      });
+      __syncthreads();                           // every wave has read this panel
+      if (lane < kT) {
+#pragma unroll
+        for (int c = 0; c < 16; ++c)
+          if (c >> 2 == wave) {                  // the finished panel, and the next one as updated
+            Sr[lane][16 * pb + c] = ar[c];
+            Si[lane][16 * pb + c] = ai[c];
           }
-        }
-        if (tid == 0) piv = idx;
-      }
-      __syncthreads();
-      const int p = piv;
-      if (p != j) {
-        for (int c = tid; c < tw; c += blockDim.x) {
-          R t = Dr[j][c];
-          Dr[j][c] = Dr[p][c];
-          Dr[p][c] = t;
-          t = Di[j][c];
-          Di[j][c] = Di[p][c];
-          Di[p][c] = t;
-        }
-        if (tid == 0) {
-          const int t = perm[j];
-          perm[j] = perm[p];
-          perm[p] = t;
-        }
-      }
-      __syncthreads();
-      if (tid == 0 && Dr[j][j] == R(0) && Di[j][j] == R(0))
-        Dr[j][j] = sqrt(std::numeric_limits<R>::min());   // exactly singular tile: perturb (FGMRES absorbs it)
-      __syncthreads();
-      const R pr = Dr[j][j], pi = Di[j][j];
-      const R den = pr * pr + pi * pi;
-      const R ir = pr / den, ii = -pi / den;
-      for (int i = j + 1 + tid; i < tw; i += blockDim.x) {
-        const R xr = Dr[i][j], xi = Di[i][j];
-        Dr[i][j] = xr * ir - xi * ii;
-        Di[i][j] = xr * ii + xi * ir;
-      }
-      __syncthreads();
-      const int m = tw - j - 1;
-      for (int o = tid; o < m * m; o += blockDim.x) {
-        const int i = j + 1 + o / m, c = j + 1 + o % m;
-        const R lr = Dr[i][j], li = Di[i][j], ur = Dr[j][c], ui = Di[j][c];
-        Dr[i][c] -= lr * ur - li * ui;
-        Di[i][c] -= lr * ui + li * ur;
-      }
-      __syncthreads();
-    }
-    for (int o = tid; o < tw * tw; o += blockDim.x) {
-      const int i = o / tw, c = o % tw;
-      Fr[(kb + i) * nf + kb + c] = Dr[i][c];
-      Fi[(kb + i) * nf + kb + c] = Di[i][c];
-    }
-    if (tid < tw) ib[d.pv + kb + tid] = perm[tid];
-    R* T = fac + d.t + (long)(kb / kT) * 4 * kTileElems;
-    // L^-1, one column per thread: X[r][c] = -sum_{c <= k < r} L[r][k] X[k][c]
-    for (int c = tid; c < tw; c += blockDim.x) {
-      for (int r = 0; r < tw; ++r) {
-        if (r < c) {
-          Xr[r][c] = R(0);
-          Xi[r][c] = R(0);
-        } else if (r == c) {
-          Xr[r][c] = R(1);
-          Xi[r][c] = R(0);
-        } else {
-          R sr = R(0), si = R(0);
-          for (int k = c; k < r; ++k) {
-            sr += Dr[r][k] * Xr[k][c] - Di[r][k] * Xi[k][c];
-            si += Dr[r][k] * Xi[k][c] + Di[r][k] * Xr[k][c];
+        if (pb < 2)
+#pragma unroll
+          for (int c = 0; c < 4; ++c) {
+            Sr[lane][16 * (pb + 1) + 4 * wave + c] = pb == 0 ? tr[0][c] : tr[1][c];
+            Si[lane][16 * (pb + 1) + 4 * wave + c] = pb == 0 ? ti[0][c] : ti[1][c];
           }
-          Xr[r][c] = -sr;
-          Xi[r][c] = -si;
-        }
+      }
+      __syncthreads();
+    }
+    if (wave == 0 && lane < kT) {
+      rowof[lpos] = lane;
+      if (lane < tw) ib[d.pv + kb + lpos] = lane;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kT * kT / 256; ++u) {
+      const int o = tid + 256 * u, i = o / kT, c = o % kT;
+      if (i < tw && c < tw) {
+        Fr[i * nf + c] = Sr[rowof[i]][c];
+        Fi[i * nf + c] = Si[rowof[i]][c];
       }
     }
-    __syncthreads();
-    for (int o = tid; o < tw * tw; o += blockDim.x) {
-      const int i = o / tw, c = o % tw;
-      T[i * kT + c] = Xr[i][c];
-      T[kTileElems + i * kT + c] = Xi[i][c];
-    }
-    __syncthreads();
-    // U^-1, one column per thread: X[c][c] = 1 / U[c][c],
-    // X[r][c] = -(sum_{r < k <= c} U[r][k] X[k][c]) / U[r][r]
-    for (int c = tid; c < tw; c += blockDim.x) {
-      for (int r = tw - 1; r > c; --r) {
-        Xr[r][c] = R(0);
-        Xi[r][c] = R(0);
-      }
-      for (int r = c; r >= 0; --r) {
-        R nr, ni;
-        if (r == c) {
-          nr = R(1);
-          ni = R(0);
-        } else {
-          R sr = R(0), si = R(0);
-          for (int k = r + 1; k <= c; ++k) {
-            sr += Dr[r][k] * Xr[k][c] - Di[r][k] * Xi[k][c];
-            si += Dr[r][k] * Xi[k][c] + Di[r][k] * Xr[k][c];
-          }
-          nr = -sr;
-          ni = -si;
-        }
-        const R ur = Dr[r][r], ui = Di[r][r];
-        const R dd = ur * ur + ui * ui;
-        const R vr = ur / dd, vi = -ui / dd;
-        Xr[r][c] = nr * vr - ni * vi;
-        Xi[r][c] = nr * vi + ni * vr;
-      }
-    }
-    __syncthreads();
-    for (int o = tid; o < tw * tw; o += blockDim.x) {
-      const int i = o / tw, c = o % tw;
-      T[2 * kTileElems + i * kT + c] = Xr[i][c];
-      T[3 * kTileElems + i * kT + c] = Xi[i][c];
-    }
-    __syncthreads();
   }
 }
 
-// Rows (columns) per workgroup of the panel kernel: one per thread, each held
-// in a row of LDS.
+// L^-1 (unit lower) and U^-1 (upper) of every factored 48 x 48 tile of a
+// level's fronts (grid.x fronts, grid.y tiles), for the solves' super-blocks.
+// Both advance together, one row of each per barrier, as rank-1 updates of
+// register tiles (thread (ti, tj) of 16 x 16 owns rows ti + 16 a, columns
+// tj + 16 b).  About 45 us a launch whatever its size, once per level.
 template <typename R>
-struct PanelCfg {
-  static constexpr int PR = sizeof(R) == 4 ? 256 : 128;
-};
+__global__ __launch_bounds__(256) void tile_inverse_kernel(const FrontDev* __restrict__ fr,
+                                                           const int* __restrict__ lvl, int nlvl,
+                                                           const R* __restrict__ buf, R* __restrict__ fac) {
+  __shared__ R Dr[kT][kT + 1], Di[kT][kT + 1];
+  __shared__ R xlr[2][kT], xli[2][kT], xur[2][kT], xui[2][kT];
+  const int tid = threadIdx.x, ti = tid >> 4, tj = tid & 15;
+  const int kb = blockIdx.y * kT;
+  for (int q = blockIdx.x; q < nlvl; q += gridDim.x) {
+    const FrontDev d = fr[lvl[q]];
+    if (kb >= d.np) continue;
+    const int tw = min(kT, d.np - kb);
+    const long nf = d.nf;
+    const R* Fr = buf + d.f + kb * nf + kb;
+    const R* Fi = Fr + nf * nf;
+    __syncthreads();                             // the previous front's LDS reads are done
+    for (int o = tid; o < kT * kT; o += 256) {
+      const int i = o / kT, c = o % kT;
+      const bool in = i < tw && c < tw;
+      Dr[i][c] = in ? Fr[i * nf + c] : R(0);
+      Di[i][c] = in ? Fi[i * nf + c] : R(0);
+    }
+    // L^-1 rows k ascending: X[k][c] = -sum_{c <= l < k} L[k][l] X[l][c]; U^-1 rows e descending:
+    // X[e][c] = (delta_ec - sum_{e < l <= c} U[e][l] X[l][c]) / U[e][e].  sl, su: the running sums.
+    R slr[3][3] = {}, sli[3][3] = {}, sur[3][3] = {}, sui[3][3] = {};
+    R* T = fac + d.t + (long)(kb / kT) * 4 * kTileElems;
+    __syncthreads();
+#pragma unroll
+    for (int ka = 0; ka < 3; ++ka) {
+      for (int kt = 0; kt < 16; ++kt) {
+        const int k = 16 * ka + kt, e = tw - 1 - k, p = k & 1;
+        if (k >= tw) break;
+        if (ti == kt) {
+#pragma unroll
+          for (int b = 0; b < 3; ++b) {
+            const int c = tj + 16 * b;
+            const R vr = c < k ? -slr[ka][b] : c == k ? R(1) : R(0);
+            const R vi = c < k ? -sli[ka][b] : R(0);
+            xlr[p][c] = vr;
+            xli[p][c] = vi;
+            if (c < tw) {
+              T[k * kT + c] = vr;
+              T[kTileElems + k * kT + c] = vi;
+            }
+          }
+        }
+        if (ti == (e & 15)) {
+          const R ur = Dr[e][e], ui = Di[e][e];
+          const R dd = ur * ur + ui * ui;
+          const R gr = ur / dd, gi = -ui / dd;
+#pragma unroll
+          for (int b = 0; b < 3; ++b) {
+            const int c = tj + 16 * b, ea = e >> 4;
+            const R sr = ea == 0 ? sur[0][b] : ea == 1 ? sur[1][b] : sur[2][b];
+            const R si = ea == 0 ? sui[0][b] : ea == 1 ? sui[1][b] : sui[2][b];
+            const R nr = c == e ? R(1) : -sr, ni = c == e ? R(0) : -si;
+            const R vr = c < e ? R(0) : nr * gr - ni * gi;
+            const R vi = c < e ? R(0) : nr * gi + ni * gr;
+            xur[p][c] = c < tw ? vr : R(0);
+            xui[p][c] = c < tw ? vi : R(0);
+            if (c < tw) {
+              T[2 * kTileElems + e * kT + c] = vr;
+              T[3 * kTileElems + e * kT + c] = vi;
+            }
+          }
+        }
+        __syncthreads();
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+          const int r = ti + 16 * a;
+          const bool lo = r > k && r < tw, up = r < e;
+          const R dlr = lo ? Dr[r][k] : R(0), dli = lo ? Di[r][k] : R(0);
+          const R dur = up ? Dr[r][e] : R(0), dui = up ? Di[r][e] : R(0);
+#pragma unroll
+          for (int b = 0; b < 3; ++b) {
+            const int c = tj + 16 * b;
+            slr[a][b] += dlr * xlr[p][c] - dli * xli[p][c];
+            sli[a][b] += dlr * xli[p][c] + dli * xlr[p][c];
+            sur[a][b] += dur * xur[p][c] - dui * xui[p][c];
+            sui[a][b] += dur * xui[p][c] + dui * xur[p][c];
+          }
+        }
+      }
+    }
+  }
+}
+
+// Rows (columns) per workgroup of the panel kernel.
+constexpr int kPR = 64;   // 256 threads load kPR x kT values in kT / 4 rounds
 
 // Workgroups [0, half): the L part below the tile by substitution, l U = f
-// for PR rows (U the tile's upper factor).  Workgroups [half, 2 half): the U
-// part right of it, L u = P f for PR columns (L the tile's unit lower factor,
+// for kPR rows (U the tile's upper factor).  Workgroups [half, 2 half): the U
+// part right of it, L u = P f for kPR columns (L the tile's unit lower factor,
 // P its row permutation).  Substitution rather than the tile's explicit
 // inverse keeps the panel backward stable.
+// What bounds it: the 48 dependent steps of a row.  Four neighbouring lanes
+// share a row (column) in registers, lane q the unknowns 4 m + q, so a step is
+// one lane's product, a broadcast inside the quad and at most twelve updates a
+// lane; the tile is read from LDS a quad's 4 values at a time, the reciprocals
+// of the diagonal are formed once, and every load is in flight before the first
+// wait.  FP64, average launch of the n = 29 factor: 37 us (152 us with one
+// thread per row and the row in LDS).
+template <int Q>
+__device__ __forceinline__ float quad_bcast(float v) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), Q * 0x55, 0xF, 0xF, false));
+}
+template <int Q>
+__device__ __forceinline__ double quad_bcast(double v) {
+  return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), Q * 0x55, 0xF, 0xF, false),
+                          __builtin_amdgcn_mov_dpp(__double2loint(v), Q * 0x55, 0xF, 0xF, false));
+}
 template <typename R>
-__global__ __launch_bounds__(256) void panel_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl,
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 3 : 2))) void panel_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl,
                                                     int nlvl, int kb, int half, R* __restrict__ buf,
                                                     const int* __restrict__ ib) {
-  constexpr int PR = PanelCfg<R>::PR;
-  __shared__ R Tr[kT][kT + 1], Ti[kT][kT + 1];   // the factored diagonal tile
-  __shared__ R Br[PR][kT + 1], Bi[PR][kT + 1];   // one row (or column) per thread
-  const int tid = threadIdx.x;
+  // T[j][c]: U[j][c] for the rows, L[c][j] for the columns, zero at and left of the diagonal
+  // and past the tile; gr, gi: 1 / U[j][j] (rows)
+  __shared__ R Tr[kT][kT], Ti[kT][kT];
+  __shared__ R gr[kT], gi[kT];
+  __shared__ R Bs[kPR][kT + 1];                  // one plane of the rows at a time (two workgroups per CU in FP64)
+  const int tid = threadIdx.x, row = tid >> 2, qd = tid & 3;
   const bool lrole = (int)blockIdx.x < half;
   const long blk = lrole ? blockIdx.x : blockIdx.x - half;
   for (int q = blockIdx.y; q < nlvl; q += gridDim.y) {
@@ -341,66 +484,95 @@ __global__ __launch_bounds__(256) void panel_kernel(const FrontDev* __restrict__
     if (kb >= d.np) continue;
     const int tw = min(kT, d.np - kb);
     const long ke = kb + tw, nf = d.nf;
-    const long x0 = ke + blk * PR;
+    const long x0 = ke + blk * kPR;
     if (x0 >= nf) continue;
-    const int cnt = (int)min((long)PR, nf - x0);
+    const int cnt = (int)min((long)kPR, nf - x0);
     R* Fr = buf + d.f;
     R* Fi = Fr + nf * nf;
-    for (int o = tid; o < tw * tw; o += blockDim.x) {
-      const int i = o / tw, c = o % tw;
-      Tr[i][c] = Fr[(kb + i) * nf + kb + c];
-      Ti[i][c] = Fi[(kb + i) * nf + kb + c];
+    // every load is issued before the first wait: the rows (columns) and the tile
+    R br[kT / 4], bi[kT / 4], vr[kT * kT / 256], vi[kT * kT / 256];
+    int pk[kT / 4];
+#pragma unroll
+    for (int m = 0; m < kT / 4; ++m) pk[m] = lrole ? 0 : ib[d.pv + kb + min((tid >> 6) + 4 * m, tw - 1)];
+#pragma unroll
+    for (int u = 0; u < kT * kT / 256; ++u) {
+      const int o = tid + 256 * u, i = o / kT, c = o % kT;
+      const long src = min(i, tw - 1) * nf + min(c, tw - 1);
+      vr[u] = Fr[kb * nf + kb + src];
+      vi[u] = Fi[kb * nf + kb + src];
     }
-    if (lrole) {
-      for (int o = tid; o < cnt * tw; o += blockDim.x) {
-        const int i = o / tw, k = o % tw;
-        Br[i][k] = Fr[(x0 + i) * nf + kb + k];
-        Bi[i][k] = Fi[(x0 + i) * nf + kb + k];
-      }
-    } else {
-      for (int o = tid; o < cnt * tw; o += blockDim.x) {
-        const int k = o / cnt, j = o % cnt;
-        const long src = (kb + ib[d.pv + kb + k]) * nf + x0 + j;
-        Br[j][k] = Fr[src];
-        Bi[j][k] = Fi[src];
+#pragma unroll
+    for (int m = 0; m < kT / 4; ++m) {
+      // rows: 48 values each, kPR * kT / 256 = 12 loads a thread; columns: row (tid >> 6) + 4 m, column tid & 63
+      const int o = tid + 256 * m, i = lrole ? o / kT : tid & 63, k = lrole ? o % kT : (tid >> 6) + 4 * m;
+      const long src = lrole ? (x0 + min(i, cnt - 1)) * nf + kb + min(k, tw - 1)
+                             : (kb + pk[m]) * nf + x0 + min(i, cnt - 1);
+      br[m] = Fr[src];
+      bi[m] = Fi[src];
+    }
+    __syncthreads();                              // the previous front's LDS reads are done
+#pragma unroll
+    for (int u = 0; u < kT * kT / 256; ++u) {
+      const int o = tid + 256 * u, i = o / kT, c = o % kT;   // F row i, column c
+      const int j = lrole ? i : c, k = lrole ? c : i;
+      const bool in = k > j && k < tw;
+      Tr[j][k] = in ? vr[u] : R(0);
+      Ti[j][k] = in ? vi[u] : R(0);
+      if (k == j) {
+        const R den = vr[u] * vr[u] + vi[u] * vi[u];
+        gr[k] = k >= tw ? R(0) : lrole ? vr[u] / den : R(1);
+        gi[k] = k >= tw || !lrole ? R(0) : -vi[u] / den;
       }
     }
-    __syncthreads();
-    if (tid < cnt) {
-      R* br = Br[tid];
-      R* bi = Bi[tid];
+#pragma unroll
+    for (int pl = 0; pl < 2; ++pl) {
+#pragma unroll
+      for (int m = 0; m < kT / 4; ++m) {
+        const int o = tid + 256 * m, i = lrole ? o / kT : tid & 63, k = lrole ? o % kT : (tid >> 6) + 4 * m;
+        Bs[i][k] = i < cnt && k < tw ? (pl ? bi : br)[m] : R(0);
+      }
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < kT / 4; ++m) (pl ? bi : br)[m] = Bs[row][4 * m + qd];
+      __syncthreads();
+    }
+    // step j = 4 M + Q: x_j = f_j / T_jj, then f_c -= x_j T[j][c] for c > j (T is zero elsewhere)
+    auto step = [&](auto M, auto Q) {
+      constexpr int m0 = decltype(M)::value, q0 = decltype(Q)::value, j = 4 * m0 + q0;
+      const R zr = quad_bcast<q0>(br[m0]), zi = quad_bcast<q0>(bi[m0]);
+      const R wr = gr[j], wi = gi[j];
+      const R xr = zr * wr - zi * wi, xi = zr * wi + zi * wr;
+      if (qd == q0) {
+        br[m0] = xr;
+        bi[m0] = xi;
+      }
+#pragma unroll
+      for (int m = m0; m < kT / 4; ++m) {
+        const R tr = Tr[j][4 * m + qd], t2 = Ti[j][4 * m + qd];
+        br[m] -= xr * tr - xi * t2;
+        bi[m] -= xr * t2 + xi * tr;
+      }
+    };
+    static_for<0, kT / 4>([&](auto M) { static_for<0, 4>([&](auto Q) { step(M, Q); }); });
+#pragma unroll
+    for (int pl = 0; pl < 2; ++pl) {
+      R* F = pl ? Fi : Fr;
+      if (pl) __syncthreads();
+#pragma unroll
+      for (int m = 0; m < kT / 4; ++m) Bs[row][4 * m + qd] = (pl ? bi : br)[m];
+      __syncthreads();
       if (lrole) {
-        for (int j = 0; j < tw; ++j) {   // l_j = f_j / U_jj; f_c -= l_j U_jc for c > j
-          const R ur = Tr[j][j], ui = Ti[j][j];
-          const R den = ur * ur + ui * ui;
-          const R xr = br[j], xi = bi[j];
-          const R lr = (xr * ur + xi * ui) / den, li = (xi * ur - xr * ui) / den;
-          br[j] = lr;
-          bi[j] = li;
-          for (int c = j + 1; c < tw; ++c) {
-            br[c] -= lr * Tr[j][c] - li * Ti[j][c];
-            bi[c] -= lr * Ti[j][c] + li * Tr[j][c];
-          }
-        }
-        for (int c = 0; c < tw; ++c) {
-          Fr[(x0 + tid) * nf + kb + c] = br[c];
-          Fi[(x0 + tid) * nf + kb + c] = bi[c];
+        for (int o = tid; o < cnt * kT; o += 256) {
+          const int i = o / kT, k = o % kT;
+          if (k < tw) F[(x0 + i) * nf + kb + k] = Bs[i][k];
         }
       } else {
-        for (int k = 0; k < tw; ++k) {   // u_r -= L_rk u_k for r > k (unit diagonal)
-          const R ukr = br[k], uki = bi[k];
-          for (int r = k + 1; r < tw; ++r) {
-            br[r] -= Tr[r][k] * ukr - Ti[r][k] * uki;
-            bi[r] -= Tr[r][k] * uki + Ti[r][k] * ukr;
-          }
-        }
-        for (int r = 0; r < tw; ++r) {
-          Fr[(kb + r) * nf + x0 + tid] = br[r];
-          Fi[(kb + r) * nf + x0 + tid] = bi[r];
+        for (int o = tid; o < kPR * tw; o += 256) {
+          const int k = o / kPR, j = o % kPR;
+          if (j < cnt) F[(kb + k) * nf + x0 + j] = Bs[j][k];
         }
       }
     }
-    __syncthreads();
   }
 }
 
@@ -1430,31 +1602,6 @@ __device__ __forceinline__ void load4(const double* p, double (&v)[4]) {
 }
 // v[j] of lane group g (lanes 16 g ..) and v[g] of lane group j change places:
 // from four consecutive columns per lane to one column of each MFMA step.
-__device__ __forceinline__ void swap32(float& a, float& b) {
-  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  a = __uint_as_float(r[0]);
-  b = __uint_as_float(r[1]);
-}
-__device__ __forceinline__ void swap16(float& a, float& b) {
-  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-  a = __uint_as_float(r[0]);
-  b = __uint_as_float(r[1]);
-}
-template <typename F>
-__device__ __forceinline__ void swap_halves(double& a, double& b, F f) {
-  float al = __int_as_float(__double2loint(a)), ah = __int_as_float(__double2hiint(a));
-  float bl = __int_as_float(__double2loint(b)), bh = __int_as_float(__double2hiint(b));
-  f(al, bl);
-  f(ah, bh);
-  a = __hiloint2double(__float_as_int(ah), __float_as_int(al));
-  b = __hiloint2double(__float_as_int(bh), __float_as_int(bl));
-}
-__device__ __forceinline__ void swap32(double& a, double& b) {
-  swap_halves(a, b, [](float& x, float& y) { swap32(x, y); });
-}
-__device__ __forceinline__ void swap16(double& a, double& b) {
-  swap_halves(a, b, [](float& x, float& y) { swap16(x, y); });
-}
 template <typename R>
 __device__ __forceinline__ void to_mfma(R (&v)[4]) {
   swap32(v[0], v[2]);
@@ -1945,9 +2092,9 @@ ls_status factor_numeric(GpuSolver& g, const C<double>* rows, hipStream_t s) {
     for (long kb0 = 0; kb0 < mnp; kb0 += kOB) {
       const long kbe = std::min(mnp, kb0 + kOB);
       for (long kb = kb0; kb < kbe; kb += kT) {
-        hipLaunchKernelGGL(diag_kernel<R>, dim3(gy), dim3(256), 0, s, fr, lvl, nl, (int)kb, buf, fac, ib);
+        hipLaunchKernelGGL(diag_kernel<R>, dim3(gy), dim3(256), 0, s, fr, lvl, nl, (int)kb, buf, ib);
         const long rest = mnf - kb - 1;           // rows right of / below the tile, at most
-        const int half = (int)std::max(1L, (rest + PanelCfg<R>::PR - 1) / PanelCfg<R>::PR);
+        const int half = (int)std::max(1L, (rest + kPR - 1) / kPR);
         hipLaunchKernelGGL(panel_kernel<R>, dim3(2 * half, gy), dim3(256), 0, s, fr, lvl, nl, (int)kb, half, buf,
                            (const int*)ib);
         const unsigned tall = (unsigned)std::max(1L, (rest + 63) / 64);
@@ -1966,6 +2113,8 @@ ls_status factor_numeric(GpuSolver& g, const C<double>* rows, hipStream_t s) {
     hipLaunchKernelGGL(copyout_kernel<R>, dim3(grid_for(mnf * mnf, 256, 8192), std::min(gy, 64u)), dim3(256), 0, s,
                        fr, lvl, nl, (const R*)buf, fac);
     // selective inversion of the super-blocks, then the folded L and U entries
+    hipLaunchKernelGGL(tile_inverse_kernel<R>, dim3(gy, (unsigned)((mnp + kT - 1) / kT)), dim3(256), 0, s, fr, lvl, nl,
+                       (const R*)buf, fac);
     const unsigned nsb = (unsigned)((mnp + kSB - 1) / kSB);
     const unsigned ncc = (unsigned)(kSB / SolveCfg<R>::RZ);
     hipLaunchKernelGGL((sb_inverse_kernel<R, true>), dim3(gy, nsb, ncc), dim3(256), 0, s, fr, lvl, nl,
