@@ -6,6 +6,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <string>
+#include <utility>
 #include <vector>
 
 #include "../../include/ls.h"
@@ -29,6 +30,11 @@ namespace ls {
 int choose_fft_size(int n);
 bool fft_size_supported(int P);
 
+// Device memory of at least `bytes` on the current device (nullptr: none left), and its
+// release; released blocks are kept for reuse within bounds (devmem.hip).
+void* device_take(size_t bytes, size_t* got, int* dev);
+void device_give(void* p, size_t got, int dev);
+
 // Device buffer with RAII release.
 struct DevBuf {
   void* p = nullptr;
@@ -40,20 +46,28 @@ struct DevBuf {
   ls_status alloc(size_t b) {
     release();
     if (b == 0) return LS_OK;
-    if (hipMalloc(&p, b) != hipSuccess) {
-      p = nullptr;
-      return LS_ENOMEM;
-    }
+    p = device_take(b, &got_, &dev_);
+    if (!p) return LS_ENOMEM;
     bytes = b;
     return LS_OK;
   }
   void release() {
-    if (p) (void)hipFree(p);
+    if (p) device_give(p, got_, dev_);
     p = nullptr;
     bytes = 0;
   }
+  void swap(DevBuf& o) {
+    std::swap(p, o.p);
+    std::swap(bytes, o.bytes);
+    std::swap(got_, o.got_);
+    std::swap(dev_, o.dev_);
+  }
   template <typename T>
   T* as() const { return reinterpret_cast<T*>(p); }
+
+ private:
+  size_t got_ = 0;   // size of the block behind p
+  int dev_ = 0;
 };
 
 // Operator data owned by a plan: contrast, Khat in both precisions, twiddles

@@ -253,10 +253,8 @@ ls_status mlp_add_samples(MlpState& st, StencilData& sd, int n, double k, const 
       LS_HIP(hipMemcpyAsync(nt.p, st.ts.p, (size_t)st.nsamples * MLP_O * 4, hipMemcpyDeviceToDevice, s));
     }
     LS_HIP(hipStreamSynchronize(s));
-    std::swap(st.xs.p, nx.p);
-    std::swap(st.xs.bytes, nx.bytes);
-    std::swap(st.ts.p, nt.p);
-    std::swap(st.ts.bytes, nt.bytes);
+    st.xs.swap(nx);
+    st.ts.swap(nt);
     st.cap = cap;
   }
   PointFitCtx ctx;
