@@ -93,7 +93,6 @@ struct ApplyPlan {
   DevBuf kh64, kh32;             // octant symbol / P^3: [H][H][6][H]
   DevBuf tw64, tw32;             // exp(-2 pi i t / P), t in [0, P)
   DevBuf work;                   // pass intermediates
-  size_t work_per_rhs64 = 0;     // bytes per rhs in FP64
   ApplyTune tune[3];             // per ls_prec
   // the paper's own 3x4 form (selected by form = 1), built on first use
   int form = 0;
@@ -110,10 +109,25 @@ ls_status apply_plan_init(ApplyPlan& ap, int n, double k, int max_rhs, const voi
 // rhs; the dyadic form only) and lifts the max_rhs limit.
 ls_status apply_run(ApplyPlan& ap, const void* x, void* y, int nrhs, ls_prec prec, hipStream_t s,
                     bool minus_conv = false, hipEvent_t* ev = nullptr, void* work = nullptr);
-// Bytes of pass workspace one rhs needs at prec: 3 (P n^2 + P^2 n) complex values.
-inline size_t apply_work_bytes(const ApplyPlan& ap, ls_prec prec) {
+// Row lengths of the pass workspace for rows of n and of n^2 values of es
+// bytes: whole 128-byte lines.  A pass writes runs of a row; where a row does
+// not start on a line, each run leaves two partial lines (dim-2 forward pass,
+// n = 150, two rhs, complex64: 929 us, 442 with rows of 160).  Up to n = 32 the workspace stays in
+// cache and the rows their length.
+inline int work_ld(int n, size_t es) {
+  const int q = (int)(128 / es);
+  return n > 32 ? (n + q - 1) / q * q : n;
+}
+inline long work_ld2(int n, size_t es) {
+  const long q = (long)(128 / es), n2 = (long)n * n;
+  return n > 32 ? (n2 + q - 1) / q * q : n2;
+}
+// Bytes of pass workspace one rhs needs at prec for `fields` transformed fields:
+// complex values [P][n] and [P][P] rows of work_ld (work_ld2(n) <= n work_ld(n)).
+// The complex128 size covers every precision.
+inline size_t apply_work_bytes(const ApplyPlan& ap, ls_prec prec, int fields = 3) {
   const size_t es = (prec == LS_C128) ? 16 : 8;
-  return (size_t)3 * ((size_t)ap.P * ap.n * ap.n + (size_t)ap.P * ap.P * ap.n) * es;
+  return (size_t)fields * ((size_t)ap.P * ap.n + (size_t)ap.P * ap.P) * work_ld(ap.n, es) * es;
 }
 // apply_run over any number of right-hand sides, ap.tune[prec].chunk (default
 // max_rhs) at a time.

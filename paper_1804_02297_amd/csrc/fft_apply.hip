@@ -258,8 +258,7 @@ ls_status apply_plan_init(ApplyPlan& ap, int n, double k, int max_rhs, const voi
   LS_TRY(ap.kh32.alloc(H3 * 6 * sizeof(C<float>)));
   LS_TRY(ap.tw64.alloc(P * sizeof(C<double>)));
   LS_TRY(ap.tw32.alloc(P * sizeof(C<float>)));
-  ap.work_per_rhs64 = (size_t)3 * ((size_t)P * n * n + (size_t)P * P * n) * sizeof(C<double>);
-  LS_TRY(ap.work.alloc(ap.work_per_rhs64 * (size_t)max_rhs));
+  LS_TRY(ap.work.alloc(apply_work_bytes(ap, LS_C128) * (size_t)max_rhs));
   // twiddles exp(-2 pi i t / P), evaluated in long double on the host
   std::vector<C<double>> t64(P);
   std::vector<C<float>> t32(P);
@@ -293,7 +292,7 @@ ls_status apply_plan_set_form(ApplyPlan& ap, int form, hipStream_t s) {
     LS_TRY(ap.p64.alloc(3 * n3 * sizeof(C<double>)));
     LS_TRY(ap.p32.alloc(3 * n3 * sizeof(C<float>)));
     // FP64 sizes: X1 and X2 of four fields and W of one, per rhs
-    const size_t per = ((size_t)4 * P * n * n + (size_t)4 * P * P * n + (size_t)n3) * sizeof(C<double>);
+    const size_t per = apply_work_bytes(ap, LS_C128, 4) + (size_t)n3 * sizeof(C<double>);
     LS_TRY(ap.work34.alloc(per * (size_t)ap.max_rhs));
     hipLaunchKernelGGL(gradient_p_kernel, dim3((unsigned)((n3 + 255) / 256)), dim3(256), 0, s,
                        ap.m64.as<C<double>>(), n, ap.h, ap.p64.as<C<double>>(), ap.p32.as<C<float>>());

@@ -66,7 +66,9 @@ constexpr int col_tile(int P, int mode) {
 
 // ---- strided-dimension four-step FFT ----------------------------------------
 // Lines are contiguous (index `line` in [0, L)); the transform runs along rows
-// with stride L.  Block = T lines x TPL threads; work item blk = batch * ntiles +
+// with strides in_rs and out_rs (the contrast and the identity term have
+// stride L).  The last pass reads lines laid out in rows of wrap_ld of which
+// wrap_n are used: line -> (line / wrap_n) wrap_ld + line % wrap_n.  Block = T lines x TPL threads; work item blk = batch * ntiles +
 // tile.  An ordinary launch has one workgroup per item (blk = blockIdx.x); a
 // PERSIST launch has the workgroups the device holds at once, which take
 // blk = blockIdx.x, blockIdx.x + gridDim.x, ... < nblk.  The two are
@@ -75,8 +77,8 @@ constexpr int col_tile(int P, int mode) {
 template <typename R, typename IO, int P, int N1, int N2, int T, int MODE, bool PAD, bool PERSIST = false>
 __global__ __launch_bounds__(T * cmax(N1, N2)) void col_fft_kernel(
     const void* __restrict__ in_, void* __restrict__ out_, const C<R>* __restrict__ mfac,
-    const C<R>* __restrict__ tw, int rows_in, int rows_out, long L, long in_bstride,
-    long out_bstride, int ntiles, long nblk, R scale) {
+    const C<R>* __restrict__ tw, int rows_in, int rows_out, long L, long in_rs, long out_rs, long in_bstride,
+    long out_bstride, int wrap_n, int wrap_ld, int ntiles, long nblk, R scale) {
   constexpr int DIR = (MODE == COL_P1 || MODE == COL_FWD) ? -1 : 1;
   // PAD: a forward pass reads at most P/2 rows, an inverse pass keeps at most P/2
   constexpr int KIN = (PAD && DIR < 0) ? (N2 + 1) / 2 : N2;
@@ -89,6 +91,8 @@ __global__ __launch_bounds__(T * cmax(N1, N2)) void col_fft_kernel(
     const int tile = (int)(blk % ntiles);
     const long line = (long)tile * T + t;
     const bool live = line < L;
+    long line_in = line;
+    if (MODE == COL_P5) line_in = (long)((int)line / wrap_n) * wrap_ld + (int)line % wrap_n;
 
     // the identity term of the last pass is loaded with the transform's input
     // rather than after the transform (its latency would otherwise end every
@@ -100,7 +104,7 @@ __global__ __launch_bounds__(T * cmax(N1, N2)) void col_fft_kernel(
       for (int q1 = 0; q1 < QOUT; ++q1) {
         const int row = j + N2 * q1;
         xid[q1] = (x && live && j < N2 && row < rows_out)
-                      ? ld_stream(x + batch * out_bstride + (long)row * L + line)
+                      ? ld_stream(x + batch * out_bstride + (long)row * out_rs + line)
                       : cmk<IO>(0, 0);
       }
     }
@@ -112,7 +116,7 @@ __global__ __launch_bounds__(T * cmax(N1, N2)) void col_fft_kernel(
         const int row = j + N1 * k;
         C<R> z = cmk<R>(0, 0);
         if (live && row < rows_in) {
-          const long off = batch * in_bstride + (long)row * L + line;
+          const long off = batch * in_bstride + (long)row * in_rs + line_in;
           if (MODE == COL_P1) {
             C<IO> xv = ld_stream(reinterpret_cast<const C<IO>*>(in_) + off);
             z = ccast<R>(xv) * mfac[(long)row * L + line];
@@ -141,7 +145,7 @@ __global__ __launch_bounds__(T * cmax(N1, N2)) void col_fft_kernel(
         for (int q1 = 0; q1 < QOUT; ++q1) {
           const int row = j + N2 * q1;
           if (row < rows_out) {
-            const long off = batch * out_bstride + (long)row * L + line;
+            const long off = batch * out_bstride + (long)row * out_rs + line;
             if (MODE == COL_P5) {
               C<IO>* y = reinterpret_cast<C<IO>*>(out_);
               const C<IO> xv = xid[q1];                                // identity term, or zero
@@ -170,7 +174,7 @@ __global__ __launch_bounds__(T * cmax(N1, N2)) void col_fft_kernel(
 }
 
 // ---- pass 3: contiguous-dimension FFT, 3x3 Khat multiply, inverse -----------
-// X: [B][3][P][P][n] (q1, q2, i3).  Kh: octant [H][H][6][H], components
+// X: [B][3][P][P][ld] (q1, q2, i3; ld >= n).  Kh: octant [H][H][6][H], components
 // (xx, yy, zz, xy, xz, yz), already divided by P^3.
 //
 // A team is 4 jobs x JL threads: the up-to-four lines (+-f1, +-f2) of one
@@ -195,7 +199,7 @@ template <typename R, int P, int N1, int N2, int W, bool PERSIST = false>
 __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C<R>* __restrict__ X,
                                                                                const C<R>* __restrict__ Kh,
                                                                                const C<R>* __restrict__ tw,
-                                                                               int n, int B) {
+                                                                               int n, int ld, int B) {
   constexpr int H = P / 2 + 1;
   constexpr int JL = job_lanes(cmax(N1, N2));
   constexpr int TEAM = 4 * JL;
@@ -235,8 +239,8 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
     const bool active = !((s1 && edge1) || (s2 && edge2));
     const int q1 = s1 ? P - f1 : f1;
     const int q2 = s2 ? P - f2 : f2;
-    const long plane = (long)P * P * n;         // one component of one rhs
-    const long lineoff = ((long)q1 * P + q2) * n;
+    const long plane = (long)P * P * ld;        // one component of one rhs
+    const long lineoff = ((long)q1 * P + q2) * ld;
 
     const C<R>* kg = Kh + ((long)f1 * H + f2) * 6 * H;
     for (int e = tid; e < 3 * H; e += W * TEAM) {
@@ -431,7 +435,7 @@ __device__ __forceinline__ double pair_swap(double x) {
 
 template <typename R, int W, bool PERSIST = false>
 __global__ __launch_bounds__(W * 128) void kmul2_kernel(C<R>* __restrict__ X, const C<R>* __restrict__ Kh,
-                                                         const C<R>* __restrict__ tw, int n, int B) {
+                                                         const C<R>* __restrict__ tw, int n, int ld, int B) {
   constexpr int P = 256, N = 16, H = P / 2 + 1;
   constexpr int EXS = N * (N + 1);            // padded exchange of one job
   __shared__ C<R> kl[6 * H];
@@ -452,8 +456,8 @@ __global__ __launch_bounds__(W * 128) void kmul2_kernel(C<R>* __restrict__ X, co
     const bool active = !((s1 && edge1) || (s2 && edge2));
     const int q1 = s1 ? P - f1 : f1;
     const int q2 = s2 ? P - f2 : f2;
-    const long plane = (long)P * P * n;
-    const long lineoff = ((long)q1 * P + q2) * n;
+    const long plane = (long)P * P * ld;
+    const long lineoff = ((long)q1 * P + q2) * ld;
 
     const C<R>* kg = Kh + ((long)f1 * H + f2) * 6 * H;
     for (int e = tid; e < 6 * H; e += W * 128) kl[e] = kg[e];
@@ -625,7 +629,7 @@ __global__ void pdot_kernel(const C<IO>* __restrict__ x, const C<R>* __restrict_
 template <typename R, int P, int N1, int N2>
 __global__ __launch_bounds__(4 * cmax(N1, N2)) void kmul34_kernel(C<R>* __restrict__ X,
                                                                   const C<R>* __restrict__ Kp,
-                                                                  const C<R>* __restrict__ tw, int n, int B) {
+                                                                  const C<R>* __restrict__ tw, int n, int ld, int B) {
   constexpr int H = P / 2 + 1;
   constexpr int TPL = cmax(N1, N2);
   constexpr int EXS = N1 * N2 + N2;
@@ -643,8 +647,8 @@ __global__ __launch_bounds__(4 * cmax(N1, N2)) void kmul34_kernel(C<R>* __restri
   const bool active = !((s1 && edge1) || (s2 && edge2));
   const int q1 = s1 ? P - f1 : f1;
   const int q2 = s2 ? P - f2 : f2;
-  const long plane = (long)P * P * n;
-  const long lineoff = ((long)q1 * P + q2) * n;
+  const long plane = (long)P * P * ld;
+  const long lineoff = ((long)q1 * P + q2) * ld;
   const C<R>* kg = Kp + ((long)f1 * H + f2) * 4 * H;
   for (int e = tid; e < 4 * H; e += blockDim.x) kl[e] = kg[e];
   for (int e = tid; e < P; e += blockDim.x) twl[e] = tw[e];
@@ -750,20 +754,27 @@ inline long resident_workgroups(const void* kern, int threads) {
   return r;
 }
 
+// Layout of a strided pass: lines, row strides and batch strides of its two
+// sides, and how the last pass's input lines are laid out (col_fft_kernel).
+struct ColShape {
+  long lines, in_rs, out_rs, in_bs, out_bs;
+  int wrap_n = 1, wrap_ld = 1;
+};
+
 // HALF: rows are read and written in runs of half the default length (T / 2
 // lines).  persist: a grid of the resident workgroups only (at least one work
 // item each), which then stride over the work items.
 template <typename R, typename IO, int P, int MODE, bool PAD = true, bool HALF = false>
 static ls_status launch_col(const void* in, void* out, const void* aux, const C<R>* tw, int rows_in,
-                            int rows_out, long L, long in_bs, long out_bs, long nbatch, R scale,
-                            hipStream_t s, bool persist = false) {
+                            int rows_out, const ColShape& c, long nbatch, R scale, hipStream_t s,
+                            bool persist = false) {
   constexpr Fac f = col_factors(P);
   constexpr int T0 = col_tile<R>(P, MODE);
   constexpr int T = (HALF && T0 >= 16) ? T0 / 2 : T0;
   constexpr int threads = T * cmax(f.n1, f.n2);
   const auto kern = persist ? col_fft_kernel<R, IO, P, f.n1, f.n2, T, MODE, PAD, true>
                             : col_fft_kernel<R, IO, P, f.n1, f.n2, T, MODE, PAD, false>;
-  const long ntiles = (L + T - 1) / T;
+  const long ntiles = (c.lines + T - 1) / T;
   const long blocks = nbatch * ntiles;
   if (blocks <= 0) return LS_OK;
   if (ntiles > 0x7fffffffL) return LS_EINVAL;
@@ -775,7 +786,8 @@ static ls_status launch_col(const void* in, void* out, const void* aux, const C<
   }
   if (grid > 0x7fffffffL) return LS_EINVAL;
   hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, s, in, out, reinterpret_cast<const C<R>*>(aux),
-                     tw, rows_in, rows_out, L, in_bs, out_bs, (int)ntiles, blocks, scale);
+                     tw, rows_in, rows_out, c.lines, c.in_rs, c.out_rs, c.in_bs, c.out_bs, c.wrap_n, c.wrap_ld,
+                     (int)ntiles, blocks, scale);
   return hipGetLastError() == hipSuccess ? LS_OK : LS_EHIP;
 }
 
@@ -783,19 +795,19 @@ static ls_status launch_col(const void* in, void* out, const void* aux, const C<
 // default run holds at least 16 lines and P >= 64; elsewhere the default)
 template <typename R, typename IO, int P, int MODE>
 static ls_status launch_col_rt(bool half, bool persist, const void* in, void* out, const void* aux, const C<R>* tw,
-                               int rows_in, int rows_out, long L, long in_bs, long out_bs, long nbatch, R scale,
+                               int rows_in, int rows_out, const ColShape& c, long nbatch, R scale,
                                hipStream_t s) {
   if constexpr (P >= 64 && col_tile<R>(P, MODE) >= 16) {
     if (half)
-      return launch_col<R, IO, P, MODE, true, true>(in, out, aux, tw, rows_in, rows_out, L, in_bs, out_bs, nbatch,
-                                                    scale, s, persist);
+      return launch_col<R, IO, P, MODE, true, true>(in, out, aux, tw, rows_in, rows_out, c, nbatch, scale, s,
+                                                    persist);
   }
-  return launch_col<R, IO, P, MODE, true, false>(in, out, aux, tw, rows_in, rows_out, L, in_bs, out_bs, nbatch,
-                                                 scale, s, persist);
+  return launch_col<R, IO, P, MODE, true, false>(in, out, aux, tw, rows_in, rows_out, c, nbatch, scale, s,
+                                                 persist);
 }
 
 template <typename R, int P, int W>
-static ls_status launch_kmul_w(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int B, bool persist, hipStream_t s) {
+static ls_status launch_kmul_w(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int ld, int B, bool persist, hipStream_t s) {
   constexpr Fac f = row_factors<R>(P);
   constexpr int H = P / 2 + 1;
   constexpr int threads = W * 4 * job_lanes(cmax(f.n1, f.n2));
@@ -806,7 +818,7 @@ static ls_status launch_kmul_w(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, i
     if (r <= 0) return LS_EHIP;
     grid = std::min(grid, r);
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, s, X, Kh, tw, n, B);
+  hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, s, X, Kh, tw, n, ld, B);
   return hipGetLastError() == hipSuccess ? LS_OK : LS_EHIP;
 }
 
@@ -816,7 +828,7 @@ static ls_status launch_kmul_w(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, i
 // different phases (loads, arithmetic, stores), which one large workgroup
 // cannot.  The autotuner may pick another count per plan.
 template <typename R, int P>
-static ls_status launch_kmul(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int B, int wt, bool persist,
+static ls_status launch_kmul(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int ld, int B, int wt, bool persist,
                             hipStream_t s) {
   constexpr Fac f = row_factors<R>(P);
   constexpr int TPL = cmax(f.n1, f.n2);
@@ -833,17 +845,17 @@ static ls_status launch_kmul(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int
       if (r <= 0) return LS_EHIP;
       grid = std::min(grid, r);
     }
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, s, X, Kh, tw, n, B);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(threads), 0, s, X, Kh, tw, n, ld, B);
     return hipGetLastError() == hipSuccess ? LS_OK : LS_EHIP;
   }
   if (wt <= 0) wt = 2;
   if constexpr (4 * TPL == 64) {
-    if (wt >= 4 && B >= 4) return launch_kmul_w<R, P, 4>(X, Kh, tw, n, B, persist, s);
-    if (wt >= 2 && B >= 2) return launch_kmul_w<R, P, 2>(X, Kh, tw, n, B, persist, s);
+    if (wt >= 4 && B >= 4) return launch_kmul_w<R, P, 4>(X, Kh, tw, n, ld, B, persist, s);
+    if (wt >= 2 && B >= 2) return launch_kmul_w<R, P, 2>(X, Kh, tw, n, ld, B, persist, s);
   } else if constexpr (job_lanes(TPL) == 32) {
-    if (wt >= 2 && B >= 2) return launch_kmul_w<R, P, 2>(X, Kh, tw, n, B, persist, s);
+    if (wt >= 2 && B >= 2) return launch_kmul_w<R, P, 2>(X, Kh, tw, n, ld, B, persist, s);
   }
-  return launch_kmul_w<R, P, 1>(X, Kh, tw, n, B, persist, s);
+  return launch_kmul_w<R, P, 1>(X, Kh, tw, n, ld, B, persist, s);
 }
 
 template <typename R, int P>
@@ -860,9 +872,11 @@ template <int P>
 static ls_status fft3d_f64(C<double>* E, C<double>* scratch, const C<double>* tw, hipStream_t s) {
   const long P2 = (long)P * P;
   // dim 1: lines = P^2 (dims 2,3), rows = dim 1
-  LS_TRY((launch_col<double, double, P, COL_FWD, false>(E, scratch, nullptr, tw, P, P, P2, 0, 0, 1, 1.0, s)));
+  LS_TRY((launch_col<double, double, P, COL_FWD, false>(E, scratch, nullptr, tw, P, P, ColShape{P2, P2, P2, 0, 0}, 1, 1.0,
+                                                           s)));
   // dim 2: batch over dim 1, lines = P (dim 3)
-  LS_TRY((launch_col<double, double, P, COL_FWD, false>(scratch, E, nullptr, tw, P, P, P, P2, P2, P, 1.0, s)));
+  LS_TRY((launch_col<double, double, P, COL_FWD, false>(scratch, E, nullptr, tw, P, P, ColShape{P, P, P, P2, P2}, P, 1.0,
+                                                           s)));
   // dim 3: contiguous
   LS_TRY((launch_rowfft<double, P>(E, tw, P2, s)));
   return LS_OK;
@@ -874,35 +888,33 @@ static ls_status run_passes(ApplyPlan& ap, const void* x, void* y, int nrhs, con
                             hipEvent_t* ev, void* work) {
   const int n = ap.n;
   const long n2 = (long)n * n, n3 = n2 * n;
-  C<R>* X1 = work ? static_cast<C<R>*>(work) : ap.work.as<C<R>>();   // [B][3][P][n^2]  (also Y1)
-  C<R>* X2 = X1 + (long)nrhs * 3 * P * n2;                 // [B][3][P][P][n]
+  const int ld = work_ld(n, sizeof(C<R>));
+  const long r1 = work_ld2(n, sizeof(C<R>)), w1 = (long)n * ld;
+  C<R>* X1 = work ? static_cast<C<R>*>(work) : ap.work.as<C<R>>();   // [B][3][P][r1]; as Y1 [B][3][P][n][ld]
+  C<R>* X2 = X1 + (long)nrhs * 3 * P * w1;                 // [B][3][P][P][ld]
   const long nb = (long)nrhs * 3;
 #define LS_MARK(i) \
   if (ev) LS_HIP(hipEventRecord(ev[i], s))
   LS_MARK(0);
   const bool pe = (tn.persist & 1) != 0, pe3 = (tn.persist & 2) != 0;
   // pass 1: along dim 1, lines = n^2
-  LS_TRY((launch_col_rt<R, IO, P, COL_P1>(tn.half_runs & 1, pe, x, X1, m, tw, n, P, n2, n3, (long)P * n2, nb, (R)1,
-                                          s)));
+  LS_TRY((launch_col_rt<R, IO, P, COL_P1>(tn.half_runs & 1, pe, x, X1, m, tw, n, P, ColShape{n2, n2, r1, n3, P * r1},
+                                          nb, (R)1, s)));
   LS_MARK(1);
   // pass 2: along dim 2, batch (b, c, q1), lines = n
-  LS_TRY((launch_col_rt<R, R, P, COL_FWD>(tn.half_runs & 2, pe, X1, X2, nullptr, tw, n, P, n, n2, (long)P * n,
-                                          nb * P, (R)1, s)));
+  LS_TRY((launch_col_rt<R, R, P, COL_FWD>(tn.half_runs & 2, pe, X1, X2, nullptr, tw, n, P,
+                                          ColShape{n, n, ld, r1, (long)P * ld}, nb * P, (R)1, s)));
   LS_MARK(2);
   // pass 3: along dim 3 with the 3x3 multiply
-  LS_TRY((launch_kmul<R, P>(X2, kh, tw, n, nrhs, tn.kmul_w, pe3, s)));
+  LS_TRY((launch_kmul<R, P>(X2, kh, tw, n, ld, nrhs, tn.kmul_w, pe3, s)));
   LS_MARK(3);
   // pass 4: inverse along dim 2
-  LS_TRY((launch_col_rt<R, R, P, COL_INV>(tn.half_runs & 4, pe, X2, X1, nullptr, tw, P, n, n, (long)P * n, n2,
-                                          nb * P, (R)1, s)));
+  LS_TRY((launch_col_rt<R, R, P, COL_INV>(tn.half_runs & 4, pe, X2, X1, nullptr, tw, P, n,
+                                          ColShape{n, ld, ld, (long)P * ld, w1}, nb * P, (R)1, s)));
   LS_MARK(4);
-  // pass 5: inverse along dim 1, y = x + v
-  if (minus_conv)   // y = -K*(m x)
-    LS_TRY((launch_col_rt<R, IO, P, COL_P5>(tn.half_runs & 8, pe, X1, y, nullptr, tw, P, n, n2, (long)P * n2, n3,
-                                            nb, (R)-1, s)));
-  else
-    LS_TRY((launch_col_rt<R, IO, P, COL_P5>(tn.half_runs & 8, pe, X1, y, x, tw, P, n, n2, (long)P * n2, n3, nb,
-                                            (R)1, s)));
+  // pass 5: inverse along dim 1, y = x + v, or y = -K*(m x) when minus_conv
+  LS_TRY((launch_col_rt<R, IO, P, COL_P5>(tn.half_runs & 8, pe, X1, y, minus_conv ? nullptr : x, tw, P, n,
+                                          ColShape{n2, w1, n2, P * w1, n3, n, ld}, nb, minus_conv ? (R)-1 : (R)1, s)));
   LS_MARK(5);
 #undef LS_MARK
   return LS_OK;
@@ -916,9 +928,11 @@ static ls_status run_passes34(ApplyPlan& ap, const void* x, void* y, int nrhs, c
                               const C<R>* kp, const C<R>* tw, bool minus_conv, hipStream_t s, hipEvent_t* ev) {
   const int n = ap.n;
   const long n2 = (long)n * n, n3 = n2 * n;
-  C<R>* X1 = ap.work34.as<C<R>>();
-  C<R>* X2 = X1 + (long)nrhs * 4 * P * n2;
-  C<R>* W = X2 + (long)nrhs * 4 * P * P * n;
+  const int ld = work_ld(n, sizeof(C<R>));
+  const long r1 = work_ld2(n, sizeof(C<R>)), w1 = (long)n * ld;
+  C<R>* X1 = ap.work34.as<C<R>>();                         // [4B][P][r1]; as Y1 [3B][P][n][ld]
+  C<R>* X2 = X1 + (long)nrhs * 4 * P * w1;                 // [4B][P][P][ld]
+  C<R>* W = X2 + (long)nrhs * 4 * P * P * ld;              // [B][n^3]
   const long nb = (long)nrhs * 3;
 #define LS_MARK(i) \
   if (ev) LS_HIP(hipEventRecord(ev[i], s))
@@ -926,26 +940,26 @@ static ls_status run_passes34(ApplyPlan& ap, const void* x, void* y, int nrhs, c
   hipLaunchKernelGGL((pdot_kernel<R, IO>), dim3((unsigned)((n3 * nrhs + 255) / 256)), dim3(256), 0, s,
                      static_cast<const C<IO>*>(x), p, W, n3, nrhs);
   LS_HIP(hipGetLastError());
-  LS_TRY((launch_col<R, IO, P, COL_P1>(x, X1, m, tw, n, P, n2, n3, (long)P * n2, nb, (R)1, s)));
-  LS_TRY((launch_col<R, R, P, COL_FWD>(W, X1 + nb * P * n2, nullptr, tw, n, P, n2, n3, (long)P * n2, nrhs, (R)1,
-                                       s)));
+  LS_TRY((launch_col<R, IO, P, COL_P1>(x, X1, m, tw, n, P, ColShape{n2, n2, r1, n3, P * r1}, nb, (R)1, s)));
+  LS_TRY((launch_col<R, R, P, COL_FWD>(W, X1 + nb * P * r1, nullptr, tw, n, P, ColShape{n2, n2, r1, n3, P * r1}, nrhs,
+                                       (R)1, s)));
   LS_MARK(1);
-  LS_TRY((launch_col<R, R, P, COL_FWD>(X1, X2, nullptr, tw, n, P, n, n2, (long)P * n, 4L * nrhs * P, (R)1, s)));
+  LS_TRY((launch_col<R, R, P, COL_FWD>(X1, X2, nullptr, tw, n, P, ColShape{n, n, ld, r1, (long)P * ld}, 4L * nrhs * P,
+                                       (R)1, s)));
   LS_MARK(2);
   {
     constexpr Fac f = row_factors<R>(P);
     constexpr int H = P / 2 + 1;
     hipLaunchKernelGGL((kmul34_kernel<R, P, f.n1, f.n2>), dim3(H * H), dim3(4 * cmax(f.n1, f.n2)), 0, s, X2, kp, tw,
-                       n, nrhs);
+                       n, ld, nrhs);
     LS_HIP(hipGetLastError());
   }
   LS_MARK(3);
-  LS_TRY((launch_col<R, R, P, COL_INV>(X2, X1, nullptr, tw, P, n, n, (long)P * n, n2, nb * P, (R)1, s)));
+  LS_TRY((launch_col<R, R, P, COL_INV>(X2, X1, nullptr, tw, P, n, ColShape{n, ld, ld, (long)P * ld, w1}, nb * P, (R)1,
+                                       s)));
   LS_MARK(4);
-  if (minus_conv)
-    LS_TRY((launch_col<R, IO, P, COL_P5>(X1, y, nullptr, tw, P, n, n2, (long)P * n2, n3, nb, (R)-1, s)));
-  else
-    LS_TRY((launch_col<R, IO, P, COL_P5>(X1, y, x, tw, P, n, n2, (long)P * n2, n3, nb, (R)1, s)));
+  LS_TRY((launch_col<R, IO, P, COL_P5>(X1, y, minus_conv ? nullptr : x, tw, P, n,
+                                       ColShape{n2, w1, n2, P * w1, n3, n, ld}, nb, minus_conv ? (R)-1 : (R)1, s)));
   LS_MARK(5);
 #undef LS_MARK
   return LS_OK;

@@ -155,3 +155,25 @@ def test_full_size_sampled(lib, prec, tol, n):
     got = np.array([y[(slice(None),) + p] for p in pts])
     scale = np.abs(ref).max()
     assert np.abs(got - ref).max() <= tol * scale
+
+
+@pytest.mark.parametrize("form", ["dyadic", "paper"])
+@pytest.mark.parametrize("n", [33, 41, 65])
+def test_apply_with_padded_workspace_rows(lib, n, form):
+    """Above n = 32 the workspace rows are padded to whole 128-byte lines (16
+    complex64 or 8 complex128 values): grids one past such a length, in every
+    precision, both forms, and the right-hand side."""
+    from oracle import paper_form as pf
+    from paper_1804_02297_amd.binding import Plan
+    k = I.wavenumber_for(n)
+    m = I.medium_bumps(n, 4)
+    x = I.random_field(2, n, 700 + n)
+    ref = op.apply_fft(n, k, m, x) if form == "dyadic" else pf.apply_fft_paper(n, k, m, x)
+    plan = Plan(n, k, _dev(m), max_rhs=2)
+    plan.set_form(form)
+    print(f"n={n} {form}", flush=True)
+    assert _rel(plan.apply(_dev(x)).cpu().numpy(), ref) <= 1e-12
+    assert _rel(plan.apply(_dev(x), prec="mixed").cpu().numpy(), ref) <= 1e-5
+    assert _rel(plan.apply(_dev(x.astype(np.complex64)), prec="c64").cpu().numpy(), ref) <= 1e-5
+    assert _rel(plan.rhs_from_incident(_dev(x)).cpu().numpy(), x - ref) <= 1e-12
+    plan.close()
