@@ -85,7 +85,8 @@ ls_status ls_apply(ls_plan* plan, const void* x_dev, void* y_dev, int nrhs, ls_p
  * HIP events recorded on hip_stream between the passes: 0 dim-1 forward with
  * the m scaling, 1 dim-2 forward, 2 dim-3 forward + 3x3 symbol multiply +
  * dim-3 inverse, 3 dim-2 inverse, 4 dim-1 inverse with the identity term.
- * Synchronises hip_stream.  For profiling and the roofline report. */
+ * Where passes 1 to 3 run as one kernel (short transforms) all their time is
+ * in pass_ms[2].  Synchronises hip_stream.  For profiling and the roofline report. */
 ls_status ls_apply_timed(ls_plan* plan, const void* x_dev, void* y_dev, int nrhs, ls_prec prec,
                          void* hip_stream, double* pass_ms);
 

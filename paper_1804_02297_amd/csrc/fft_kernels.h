@@ -724,6 +724,211 @@ __global__ __launch_bounds__(4 * cmax(N1, N2)) void kmul34_kernel(C<R>* __restri
   }
 }
 
+// ---- passes 2 to 4 of one (q1) plane in LDS (short transforms) -----------------
+// A workgroup takes one right-hand side and one q1: the dim-2 forward transform
+// of its NF fields, per row q2 the dim-3 transform, the symbol multiply and the
+// dim-3 inverse, and the dim-2 inverse of the three results, the plane in LDS
+// all the while.  NF = 3: the dyadic form; 4: the paper's form (field 3 is p.x).
+// What bounds it: at these sizes the three separate passes are launches of a
+// few microseconds each, and in batches they move 18 of the 27 plane volumes
+// that cross the workspace; this kernel reads 2 and writes 2.
+// A row of LDS is one q2: NF n values (columns c n + i3), at least the P + N2 of
+// a row transform's exchange, which runs in the row itself once its values are
+// in registers.  RS = 8 mod 16 spreads the rows over the banks.  In the column
+// steps neighbouring threads take neighbouring columns; a row is worked on by
+// JL lanes of one wave.  The symbol is read from the caches (its octant is at
+// most 3.4 MB in FP64 at P = 64).  Above the LDS limit (P > 64; P > 96 in FP32)
+// the separate passes run.  Whole apply, complex128, against the three passes:
+// n = 16 one rhs 22.4 -> 17.4 us (three launches instead of five), 16 rhs
+// 102 -> 24 us; n = 32 16 rhs 210 -> 111 us (complex64 138 -> 60).
+template <typename R, int P, int NF>
+struct PlaneCfg {
+  static constexpr Fac f = col_factors(P);
+  static constexpr int TPL = cmax(f.n1, f.n2);
+  static constexpr int JL = TPL <= 4 ? 4 : TPL <= 8 ? 8 : 16;
+  // a thread per row lane, up to 512; half of them at P = 48 in FP64, where the rows' values,
+  // symbol and transforms need more than the 256 registers that six waves leave (194 spilled)
+  static constexpr int ROWS = sizeof(R) == 8 && P == 48 ? P / 2 : P;
+  static constexpr int NT = cmax(64, ROWS * JL < 512 ? (ROWS * JL + 63) / 64 * 64 : 512);
+  static constexpr int CPB = NT / TPL;                       // columns per batch of the dim-2 steps
+  static constexpr int W = cmax(NF * P / 2, P + f.n2);
+  static constexpr int RS = (W + 7) / 16 * 16 + 8;
+  static constexpr bool FITS = TPL <= 16 && (P * RS + P) * 2 * (int)sizeof(R) <= 160 * 1024;
+};
+
+template <typename R, int P, int NF>
+__global__ __launch_bounds__((PlaneCfg<R, P, NF>::NT)) void plane_kernel(const C<R>* X, C<R>* Y,   // may be one array
+                                                                         const C<R>* __restrict__ Kh,
+                                                                         const C<R>* __restrict__ tw, int n, int B,
+                                                                         long in_rs, int out_ld) {
+  using Cfg = PlaneCfg<R, P, NF>;
+  constexpr int N1 = Cfg::f.n1, N2 = Cfg::f.n2, TPL = Cfg::TPL, JL = Cfg::JL, NT = Cfg::NT, CPB = Cfg::CPB,
+                RS = Cfg::RS, H = P / 2 + 1;
+  constexpr int KIN = (N2 + 1) / 2;          // t = j + N1 k < n <= P/2
+  constexpr int QOUT = (N1 + 1) / 2;
+  constexpr int NS = NF == 3 ? 6 : 4;        // symbol components
+  __shared__ C<R> S[P * RS];
+  __shared__ C<R> twl[P];
+  const int tid = threadIdx.x;
+  const int b = blockIdx.x / P, q1 = blockIdx.x % P;
+  for (int e = tid; e < P; e += NT) twl[e] = tw[e];
+  auto field = [&](int c) { return c < 3 ? 3 * b + c : 3 * B + b; };
+  const int ct = tid % CPB, cj = tid / CPB;
+  __syncthreads();
+  // dim 2 forward: rows i2 < n of the plane in, slots (step 1) and rows q2 (step 3) of LDS out
+  for (int col0 = 0; col0 < NF * n; col0 += CPB) {
+    const int col = col0 + ct;
+    const bool live = col < NF * n;
+    if (live && cj < N1) {
+      const int c = col / n;
+      const C<R>* src = X + ((long)field(c) * P + q1) * in_rs + (col - c * n);
+      C<R> v[N2];
+#pragma unroll
+      for (int k = 0; k < KIN; ++k) {
+        const int row = cj + N1 * k;
+        v[k] = row < n ? src[(long)row * n] : cmk<R>(0, 0);
+      }
+      DftZ<N2, -1, R, KIN>::run(v);
+#pragma unroll
+      for (int q = 0; q < N2; ++q) S[(cj * N2 + q) * RS + col] = q == 0 ? v[q] : v[q] * twl[cj * q];
+    }
+    __syncthreads();
+    if (live && cj < N2) {
+      C<R> w[N1];
+#pragma unroll
+      for (int jj = 0; jj < N1; ++jj) w[jj] = S[(jj * N2 + cj) * RS + col];
+      Dft<N1, -1, R>::run(w);
+#pragma unroll
+      for (int a = 0; a < N1; ++a) S[(cj + N2 * a) * RS + col] = w[a];
+    }
+  }
+  __syncthreads();
+  // dim 3, row by row (kmul_kernel's steps, JL lanes a row)
+  const bool s1 = 2 * q1 > P;
+  const int f1 = s1 ? P - q1 : q1;
+  const int j = tid % JL;
+#pragma unroll 1
+  for (int q2 = tid / JL; q2 < P; q2 += NT / JL) {
+    C<R>* row = S + q2 * RS;
+    const bool s2 = 2 * q2 > P;
+    const C<R>* kg = Kh + ((long)f1 * H + (s2 ? P - q2 : q2)) * NS * H;
+    C<R> x[NF][KIN], u[NF][N1];
+    if (j < N1) {
+#pragma unroll
+      for (int c = 0; c < NF; ++c)
+#pragma unroll
+        for (int k = 0; k < KIN; ++k) {
+          const int t = j + N1 * k;
+          x[c][k] = t < n ? row[c * n + t] : cmk<R>(0, 0);
+        }
+    }
+    wave_lds_sync();
+#pragma unroll
+    for (int c = 0; c < NF; ++c) {
+      if (j < N1) {
+        C<R> v[N2];
+#pragma unroll
+        for (int k = 0; k < KIN; ++k) v[k] = x[c][k];
+        DftZ<N2, -1, R, KIN>::run(v);
+#pragma unroll
+        for (int q = 0; q < N2; ++q) row[q * (N1 + 1) + j] = q == 0 ? v[q] : v[q] * twl[j * q];
+      }
+      wave_lds_sync();
+      if (j < N2) {
+#pragma unroll
+        for (int a = 0; a < N1; ++a) u[c][a] = row[j * (N1 + 1) + a];
+        Dft<N1, -1, R>::run(u[c]);
+      }
+      wave_lds_sync();
+    }
+    if (j < N2) {
+      const R sy = s2 ? (R)-1 : (R)1, sx = s1 ? (R)-1 : (R)1, sxy = s1 != s2 ? (R)-1 : (R)1;
+#pragma unroll
+      for (int a = 0; a < N1; ++a) {
+        const int q3 = j + N2 * a;
+        const bool hi = 2 * q3 > P;
+        const int f3 = hi ? P - q3 : q3;
+        const R s3 = hi ? (R)-1 : (R)1;
+        if constexpr (NF == 3) {
+          const C<R> kxx = kg[f3], kyy = kg[H + f3], kzz = kg[2 * H + f3];
+          const C<R> kxy = cscale(kg[3 * H + f3], sxy), kxz = cscale(kg[4 * H + f3], sx * s3),
+                     kyz = cscale(kg[5 * H + f3], sy * s3);
+          const C<R> ux = u[0][a], uy = u[1][a], uz = u[2][a];
+          u[0][a] = cfma(kxz, uz, cfma(kxy, uy, kxx * ux));
+          u[1][a] = cfma(kyz, uz, cfma(kyy, uy, kxy * ux));
+          u[2][a] = cfma(kzz, uz, cfma(kyz, uy, kxz * ux));
+        } else {
+          const C<R> g0 = kg[f3], g1 = cscale(kg[H + f3], sx), g2 = cscale(kg[2 * H + f3], sy),
+                     g3 = cscale(kg[3 * H + f3], s3), w = u[NF - 1][a];
+          u[0][a] = g0 * u[0][a] + g1 * w;
+          u[1][a] = g0 * u[1][a] + g2 * w;
+          u[2][a] = g0 * u[2][a] + g3 * w;
+        }
+        if (N1 > 4 && (sizeof(R) == 8 || (a & 1))) asm volatile("" ::: "memory");   // bound the symbol loads in flight
+      }
+    }
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      if (j < N2) {
+        Dft<N1, 1, R>::run(u[c]);
+#pragma unroll
+        for (int t2 = 0; t2 < N1; ++t2)
+          row[j * (N1 + 1) + t2] = t2 == 0 ? u[c][t2] : u[c][t2] * cconj(twl[j * t2]);
+      }
+      wave_lds_sync();
+      if (j < N1) {
+        C<R> v[N2];
+#pragma unroll
+        for (int q = 0; q < N2; ++q) v[q] = row[q * (N1 + 1) + j];
+        Dft<N2, 1, R>::run(v);
+#pragma unroll
+        for (int k = 0; k < KIN; ++k) x[c][k] = v[k];
+      }
+      wave_lds_sync();
+    }
+    if (j < N1) {
+#pragma unroll
+      for (int c = 0; c < 3; ++c)
+#pragma unroll
+        for (int k = 0; k < KIN; ++k) {
+          const int t = j + N1 * k;
+          if (t < n) row[c * n + t] = x[c][k];
+        }
+    }
+  }
+  __syncthreads();
+  // dim 2 inverse: rows q2 of LDS in, rows i2 < n of the plane out
+  for (int col0 = 0; col0 < 3 * n; col0 += CPB) {
+    const int col = col0 + ct;
+    const bool live = col < 3 * n;
+    C<R> v[N2];
+    if (live && cj < N1) {
+#pragma unroll
+      for (int k = 0; k < N2; ++k) v[k] = S[(cj + N1 * k) * RS + col];
+      Dft<N2, 1, R>::run(v);
+    }
+    __syncthreads();
+    if (live && cj < N1) {
+#pragma unroll
+      for (int q = 0; q < N2; ++q) S[(cj * N2 + q) * RS + col] = q == 0 ? v[q] : v[q] * cconj(twl[cj * q]);
+    }
+    __syncthreads();
+    if (live && cj < N2) {
+      const int c = col / n;
+      C<R>* dst = Y + ((long)(3 * b + c) * P + q1) * n * out_ld + (col - c * n);
+      C<R> w[N1];
+#pragma unroll
+      for (int jj = 0; jj < N1; ++jj) w[jj] = S[(jj * N2 + cj) * RS + col];
+      Dft<N1, 1, R>::run(w);
+#pragma unroll
+      for (int a = 0; a < QOUT; ++a) {
+        const int i2 = cj + N2 * a;
+        if (i2 < n) dst[(long)i2 * out_ld] = w[a];
+      }
+    }
+  }
+}
+
 // ---- launch helpers -----------------------------------------------------------
 // Workgroups of `kern` (with `threads` threads) that the current device holds at
 // once: the grid of a persistent launch.  Occupancy is queried once per kernel
@@ -858,6 +1063,25 @@ static ls_status launch_kmul(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int
   return launch_kmul_w<R, P, 1>(X, Kh, tw, n, ld, B, persist, s);
 }
 
+// Whether passes 2 to 4 run as one plane_kernel launch.  At P = 96 (FP32, one
+// workgroup per CU, three rounds of rows) only from eight right-hand sides on:
+// n = 48 16 rhs 265 us against 314 with three passes, 4 rhs 88 both, n = 40 one
+// rhs 42 against 36.
+template <typename R, int P, int NF>
+constexpr bool use_plane(int nrhs) {
+  return PlaneCfg<R, P, NF>::FITS && (P <= 64 || nrhs >= 8);
+}
+
+// Passes 2 to 4 as one plane_kernel launch: X1 rows of in_rs in, Y1 [3B][P][n][out_ld] out.
+template <typename R, int P, int NF>
+static ls_status launch_plane(const C<R>* X, C<R>* Y, const C<R>* Kh, const C<R>* tw, int n, int B, long in_rs,
+                              int out_ld, hipStream_t s) {
+  if ((long)B * P > 0x7fffffffL) return LS_EINVAL;
+  hipLaunchKernelGGL((plane_kernel<R, P, NF>), dim3((unsigned)(B * P)), dim3(PlaneCfg<R, P, NF>::NT), 0, s, X, Y, Kh,
+                     tw, n, B, in_rs, out_ld);
+  return hipGetLastError() == hipSuccess ? LS_OK : LS_EHIP;
+}
+
 template <typename R, int P>
 static ls_status launch_rowfft(C<R>* X, const C<R>* tw, long nlines, hipStream_t s) {
   constexpr Fac f = col_factors(P);
@@ -901,19 +1125,29 @@ static ls_status run_passes(ApplyPlan& ap, const void* x, void* y, int nrhs, con
   LS_TRY((launch_col_rt<R, IO, P, COL_P1>(tn.half_runs & 1, pe, x, X1, m, tw, n, P, ColShape{n2, n2, r1, n3, P * r1},
                                           nb, (R)1, s)));
   LS_MARK(1);
-  // pass 2: along dim 2, batch (b, c, q1), lines = n
-  LS_TRY((launch_col_rt<R, R, P, COL_FWD>(tn.half_runs & 2, pe, X1, X2, nullptr, tw, n, P,
-                                          ColShape{n, n, ld, r1, (long)P * ld}, nb * P, (R)1, s)));
-  LS_MARK(2);
-  // pass 3: along dim 3 with the 3x3 multiply
-  LS_TRY((launch_kmul<R, P>(X2, kh, tw, n, ld, nrhs, tn.kmul_w, pe3, s)));
-  LS_MARK(3);
-  // pass 4: inverse along dim 2
-  LS_TRY((launch_col_rt<R, R, P, COL_INV>(tn.half_runs & 4, pe, X2, X1, nullptr, tw, P, n,
-                                          ColShape{n, ld, ld, (long)P * ld, w1}, nb * P, (R)1, s)));
-  LS_MARK(4);
+  C<R>* Y1 = X1;
+  if (use_plane<R, P, 3>(nrhs)) {
+    // passes 2 to 4 (timed as pass 3), in place when the rows of X1 and Y1 are alike
+    if (r1 != w1) Y1 = X2;
+    LS_MARK(2);
+    if constexpr (PlaneCfg<R, P, 3>::FITS) LS_TRY((launch_plane<R, P, 3>(X1, Y1, kh, tw, n, nrhs, r1, ld, s)));
+    LS_MARK(3);
+    LS_MARK(4);
+  } else {
+    // pass 2: along dim 2, batch (b, c, q1), lines = n
+    LS_TRY((launch_col_rt<R, R, P, COL_FWD>(tn.half_runs & 2, pe, X1, X2, nullptr, tw, n, P,
+                                            ColShape{n, n, ld, r1, (long)P * ld}, nb * P, (R)1, s)));
+    LS_MARK(2);
+    // pass 3: along dim 3 with the 3x3 multiply
+    LS_TRY((launch_kmul<R, P>(X2, kh, tw, n, ld, nrhs, tn.kmul_w, pe3, s)));
+    LS_MARK(3);
+    // pass 4: inverse along dim 2
+    LS_TRY((launch_col_rt<R, R, P, COL_INV>(tn.half_runs & 4, pe, X2, X1, nullptr, tw, P, n,
+                                            ColShape{n, ld, ld, (long)P * ld, w1}, nb * P, (R)1, s)));
+    LS_MARK(4);
+  }
   // pass 5: inverse along dim 1, y = x + v, or y = -K*(m x) when minus_conv
-  LS_TRY((launch_col_rt<R, IO, P, COL_P5>(tn.half_runs & 8, pe, X1, y, minus_conv ? nullptr : x, tw, P, n,
+  LS_TRY((launch_col_rt<R, IO, P, COL_P5>(tn.half_runs & 8, pe, Y1, y, minus_conv ? nullptr : x, tw, P, n,
                                           ColShape{n2, w1, n2, P * w1, n3, n, ld}, nb, minus_conv ? (R)-1 : (R)1, s)));
   LS_MARK(5);
 #undef LS_MARK
@@ -944,21 +1178,30 @@ static ls_status run_passes34(ApplyPlan& ap, const void* x, void* y, int nrhs, c
   LS_TRY((launch_col<R, R, P, COL_FWD>(W, X1 + nb * P * r1, nullptr, tw, n, P, ColShape{n2, n2, r1, n3, P * r1}, nrhs,
                                        (R)1, s)));
   LS_MARK(1);
-  LS_TRY((launch_col<R, R, P, COL_FWD>(X1, X2, nullptr, tw, n, P, ColShape{n, n, ld, r1, (long)P * ld}, 4L * nrhs * P,
-                                       (R)1, s)));
-  LS_MARK(2);
-  {
-    constexpr Fac f = row_factors<R>(P);
-    constexpr int H = P / 2 + 1;
-    hipLaunchKernelGGL((kmul34_kernel<R, P, f.n1, f.n2>), dim3(H * H), dim3(4 * cmax(f.n1, f.n2)), 0, s, X2, kp, tw,
-                       n, ld, nrhs);
-    LS_HIP(hipGetLastError());
+  C<R>* Y1 = X1;
+  if (use_plane<R, P, 4>(nrhs)) {
+    if (r1 != w1) Y1 = X2;
+    LS_MARK(2);
+    if constexpr (PlaneCfg<R, P, 4>::FITS) LS_TRY((launch_plane<R, P, 4>(X1, Y1, kp, tw, n, nrhs, r1, ld, s)));
+    LS_MARK(3);
+    LS_MARK(4);
+  } else {
+    LS_TRY((launch_col<R, R, P, COL_FWD>(X1, X2, nullptr, tw, n, P, ColShape{n, n, ld, r1, (long)P * ld}, 4L * nrhs * P,
+                                         (R)1, s)));
+    LS_MARK(2);
+    {
+      constexpr Fac f = row_factors<R>(P);
+      constexpr int H = P / 2 + 1;
+      hipLaunchKernelGGL((kmul34_kernel<R, P, f.n1, f.n2>), dim3(H * H), dim3(4 * cmax(f.n1, f.n2)), 0, s, X2, kp, tw,
+                         n, ld, nrhs);
+      LS_HIP(hipGetLastError());
+    }
+    LS_MARK(3);
+    LS_TRY((launch_col<R, R, P, COL_INV>(X2, X1, nullptr, tw, P, n, ColShape{n, ld, ld, (long)P * ld, w1}, nb * P, (R)1,
+                                         s)));
+    LS_MARK(4);
   }
-  LS_MARK(3);
-  LS_TRY((launch_col<R, R, P, COL_INV>(X2, X1, nullptr, tw, P, n, ColShape{n, ld, ld, (long)P * ld, w1}, nb * P, (R)1,
-                                       s)));
-  LS_MARK(4);
-  LS_TRY((launch_col<R, IO, P, COL_P5>(X1, y, minus_conv ? nullptr : x, tw, P, n,
+  LS_TRY((launch_col<R, IO, P, COL_P5>(Y1, y, minus_conv ? nullptr : x, tw, P, n,
                                        ColShape{n2, w1, n2, P * w1, n3, n, ld}, nb, minus_conv ? (R)-1 : (R)1, s)));
   LS_MARK(5);
 #undef LS_MARK

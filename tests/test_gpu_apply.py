@@ -177,3 +177,33 @@ def test_apply_with_padded_workspace_rows(lib, n, form):
     assert _rel(plan.apply(_dev(x.astype(np.complex64)), prec="c64").cpu().numpy(), ref) <= 1e-5
     assert _rel(plan.rhs_from_incident(_dev(x)).cpu().numpy(), x - ref) <= 1e-12
     plan.close()
+
+
+@pytest.mark.parametrize("form", ["dyadic", "paper"])
+@pytest.mark.parametrize("n,nrhs", [(3, 2), (6, 1), (7, 3), (9, 2), (12, 1), (13, 2), (16, 2), (17, 1), (24, 2), (25, 1),
+                                    (32, 2), (33, 8), (48, 8), (48, 3)])
+def test_apply_short_transforms(lib, n, nrhs, form):
+    """Transform lengths whose dim-2 and dim-3 passes run as one kernel per
+    plane (P = 8 to 64; 96 in FP32 from eight rhs on), at the smallest and
+    largest n of each length, every precision, both forms; and the timed call,
+    which runs the same kernels."""
+    from oracle import paper_form as pf
+    from paper_1804_02297_amd.binding import Plan
+    k = I.wavenumber_for(n)
+    m = I.medium_bumps(n, 3)
+    x = I.random_field(nrhs, n, 800 + n)
+    ref = op.apply_fft(n, k, m, x) if form == "dyadic" else pf.apply_fft_paper(n, k, m, x)
+    plan = Plan(n, k, _dev(m), max_rhs=nrhs)
+    plan.set_form(form)
+    print(f"n={n} nrhs={nrhs} {form}", flush=True)
+    y = plan.apply(_dev(x))
+    assert _rel(y.cpu().numpy(), ref) <= 1e-12
+    assert _rel(plan.apply(_dev(x), prec="mixed").cpu().numpy(), ref) <= 1e-5
+    assert _rel(plan.apply(_dev(x.astype(np.complex64)), prec="c64").cpu().numpy(), ref) <= 1e-5
+    yt = torch.empty_like(y)
+    assert len(plan.apply_timed(_dev(x), yt)) == 5
+    assert torch.equal(yt, y)
+    xi = _dev(x)
+    plan.apply(xi, xi)                     # in place
+    assert torch.equal(xi, y)
+    plan.close()
