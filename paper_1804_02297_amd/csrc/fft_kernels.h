@@ -44,7 +44,7 @@ constexpr Fac row_factors(int P) {
 }
 constexpr int cmax(int a, int b) { return a > b ? a : b; }
 // lanes per job of pass 3 (see kmul_kernel)
-constexpr int job_lanes(int tpl) { return (tpl > 16 && tpl <= 32) ? 32 : tpl; }
+constexpr int job_lanes(int tpl) { return tpl > 16 && tpl <= 32 ? 32 : tpl > 8 && tpl <= 16 ? 16 : tpl; }
 // Lines per workgroup of the strided passes: a LS_COL_RUN_BYTES run per row
 // (one or two 128-byte cache lines), LDS <= 64 KB.
 #ifndef LS_COL_RUN_BYTES
@@ -178,9 +178,11 @@ __global__ __launch_bounds__(T * cmax(N1, N2)) void col_fft_kernel(
 // (xx, yy, zz, xy, xz, yz), already divided by P^3.
 //
 // A team is 4 jobs x JL threads: the up-to-four lines (+-f1, +-f2) of one
-// right-hand side, JL = TPL (the larger factor of P) or, for 16 < TPL <= 32,
-// 32 so that a job is half a wavefront (TPL = 24 at P = 384: 8 idle lanes per
-// job, as the 96-lane team already had in its second wave).  A workgroup
+// right-hand side, JL = TPL (the larger factor of P) or, for 8 < TPL <= 32,
+// 16 or 32 so that no job straddles two wavefronts (TPL = 24 at P = 384: 8 idle
+// lanes per job, as the 96-lane team already had in its second wave; TPL = 12
+// at P = 96 in four padded jobs of a wave instead of a 48-lane team behind
+// barriers: complex128 apply of 16 rhs at n = 48 555 -> 506 us).  A workgroup
 // holds W teams that share one octant line of Khat in LDS and take
 // right-hand sides b = team, team + W, ...  When no job straddles two
 // wavefronts (JL = 16 or 32) its exchanges need only wavefront-level
@@ -1054,7 +1056,7 @@ static ls_status launch_kmul(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int
     return hipGetLastError() == hipSuccess ? LS_OK : LS_EHIP;
   }
   if (wt <= 0) wt = 2;
-  if constexpr (4 * TPL == 64) {
+  if constexpr (job_lanes(TPL) == 16) {
     if (wt >= 4 && B >= 4) return launch_kmul_w<R, P, 4>(X, Kh, tw, n, ld, B, persist, s);
     if (wt >= 2 && B >= 2) return launch_kmul_w<R, P, 2>(X, Kh, tw, n, ld, B, persist, s);
   } else if constexpr (job_lanes(TPL) == 32) {
