@@ -901,31 +901,59 @@ __global__ __launch_bounds__(256) void sol_out_tile_kernel(C<double>* __restrict
   }
 }
 
-// children's update vectors into the pivot rows (x) or the update vector (u)
-// of every front of a level, for child `slot`; 256 / rhs_lanes(nrhs) rows per workgroup pass
+// Where each front's rows get their children's updates from: cinv[d.ci + slot
+// (nf / NC) + p] = the boundary point of child `slot` at front point p, or -1.
+template <int NC>
+__global__ __launch_bounds__(256) void child_map_kernel(const FrontDev* __restrict__ fr, int nfronts,
+                                                        const int* __restrict__ ib, int* __restrict__ cinv) {
+  for (int q = blockIdx.x; q < nfronts; q += gridDim.x) {
+    const FrontDev d = fr[q];
+    const int np = d.nf / NC;
+    for (int e = threadIdx.x; e < 2 * np; e += blockDim.x) cinv[d.ci + e] = -1;
+    __syncthreads();
+    for (int slot = 0; slot < 2; ++slot) {
+      const int cid = slot ? d.child[1] : d.child[0];
+      if (cid < 0) continue;
+      const FrontDev c = fr[cid];
+      for (int e = threadIdx.x; e < c.nb / NC; e += blockDim.x) cinv[d.ci + (long)slot * np + ib[c.xm + e]] = e;
+    }
+  }
+}
+
+// The children's update vectors added to the pivot rows (x) and set as the
+// update vector (u; zero where no child reaches) of every front of a level:
+// each row takes child 0's value, then child 1's, through cinv, in one launch
+// and with nothing to clear beforehand (adding the children in turn took two
+// launches of about 5 us a level and a clearing pass over u).
+// 256 / rhs_lanes(nrhs) rows per workgroup pass.
 template <typename R, int NC>
 __global__ __launch_bounds__(256) void fwd_child_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl,
-                                                        int nlvl, int slot, const int* __restrict__ ib, int nrhs,
+                                                        int nlvl, const int* __restrict__ cinv, int nrhs,
                                                         R* __restrict__ Xr, R* __restrict__ Xi, R* __restrict__ Ur,
                                                         R* __restrict__ Ui) {
+  const int lanes = rhs_lanes(nrhs), rpp = 256 / lanes;
   for (int q = blockIdx.y; q < nlvl; q += gridDim.y) {
-    // the child index read from global memory: indexing the copy's child[]
-    // with the runtime slot would put the whole FrontDev copy on the stack
-    const int cid = fr[lvl[q]].child[slot];
-    if (cid < 0) continue;
     const FrontDev d = fr[lvl[q]];
-    const FrontDev c = fr[cid];
-    const int lanes = rhs_lanes(nrhs), rpp = 256 / lanes;
-    for (int rr = blockIdx.x * rpp + threadIdx.x / lanes; rr < c.nb; rr += gridDim.x * rpp) {
-      const int pos = NC * ib[c.xm + rr / NC] + rr % NC;
-      const bool piv = pos < d.np;
-      const long src = (c.u + rr) * nrhs;
-      const long dst = piv ? (long)(d.e0 + pos) * nrhs : (d.u + pos - d.np) * nrhs;
-      R* Tr = piv ? Xr : Ur;
-      R* Ti = piv ? Xi : Ui;
+    const int* ci = cinv + d.ci;
+    const int np = d.nf / NC;
+    for (int row = blockIdx.x * rpp + threadIdx.x / lanes; row < d.nf; row += gridDim.x * rpp) {
+      const int p = row / NC, e0 = ci[p], e1 = ci[np + p];
+      const bool piv = row < d.np;
+      if (piv && e0 < 0 && e1 < 0) continue;
+      const long s0 = (d.cu[0] + (long)NC * e0 + row % NC) * nrhs, s1 = (d.cu[1] + (long)NC * e1 + row % NC) * nrhs;
+      const long dst = (piv ? (long)d.e0 + row : d.u + row - d.np) * nrhs;
       for (int r = threadIdx.x % lanes; r < nrhs; r += lanes) {
-        Tr[dst + r] += Ur[src + r];
-        Ti[dst + r] += Ui[src + r];
+        R vr = piv ? Xr[dst + r] : R(0), vi = piv ? Xi[dst + r] : R(0);
+        if (e0 >= 0) {
+          vr += Ur[s0 + r];
+          vi += Ui[s0 + r];
+        }
+        if (e1 >= 0) {
+          vr += Ur[s1 + r];
+          vi += Ui[s1 + r];
+        }
+        (piv ? Xr : Ur)[dst + r] = vr;
+        (piv ? Xi : Ui)[dst + r] = vi;
       }
     }
   }
@@ -1827,195 +1855,235 @@ __global__ __launch_bounds__(SPLIT ? 128 : 256) __attribute__((amdgpu_waves_per_
   }
 }
 
-// Few right-hand sides (at most kGemvRhs): the products of fwd_sb_kernel
-// (FWD) and bwd_sb_kernel as matrix-vector products, kGemvLanes lanes per
-// row with the block's vector in LDS (the 64-rhs MFMA tiles would compute mostly zero
-// columns).  Same grid and the same rows read and written as those kernels.
+// Up to kGemvRhs right-hand sides: the products of fwd_sb_kernel (FWD) and
+// bwd_sb_kernel as matrix-vector products, kGemvLanes lanes per row with the
+// block's vector in LDS (the MFMA tiles would compute mostly zero columns).
+// Same grid and the same rows read and written as those kernels.
+// What bounds it: memory at the wide levels (the 4096 leaf fronts of a 2-D
+// n = 479 factor: about 3 TB/s on row pieces of 0.5 to 0.7 KB), a chain of
+// latencies at the top of the tree (4 to 5 us a launch).  Every factor value of
+// a row (sw <= 192: twelve a lane and plane) is loaded before the first wait,
+// ahead of the vector's staging, and the descriptor in one go; the steps' count
+// is uniform, so loads and LDS reads are addressed by constant offsets (with a
+// clamp per load the kernels were bound by issuing address arithmetic); the
+// zero blocks of M and H are not read (thin_kernel).  2-D preconditioner apply, n = 479,
+// one rhs: 1450 to 923 us, the leaf level's three launches 525 to 355 us.
 constexpr int kGemvRhs = 4;
 constexpr int kGemvLanes = 16;   // lanes per row: four rows per wave, 128-byte row segments per load
-constexpr int kGemvRows = 256 / kGemvLanes;   // rows per workgroup (one pass): more workgroups per front
-template <typename R, bool FWD>
-__global__ __launch_bounds__(256) void sb_gemv_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl,
-                                                      int nlvl, int kb0, const R* __restrict__ fac, int nrhs,
-                                                      R* __restrict__ Xr, R* __restrict__ Xi, R* __restrict__ Zr,
-                                                      R* __restrict__ Zi, R* __restrict__ Ur, R* __restrict__ Ui) {
-  constexpr int NZB = kSB / kGemvRows;
-  __shared__ R vr_[kSB * kGemvRhs], vi_[kSB * kGemvRhs];
-  const int tid = threadIdx.x, sub = tid % kGemvLanes;
-  const bool brole = (int)blockIdx.x < NZB;      // rows of the block (M or H) or rows outside it
-  // the block's vector: x rows (forward) or y rows (backward) of the block
-  const R* Vr = FWD ? Xr : Zr;
-  const R* Vi = FWD ? Xi : Zi;
-  for (int q = blockIdx.y; q < nlvl; q += gridDim.y) {
-    const FrontDev d = fr[lvl[q]];
-    if (kb0 >= d.np) continue;
-    const int sw = min(kSB, d.np - kb0);
-    const long nf = d.nf, np = d.np;
-    long i0;
-    int cnt;
-    if (brole) {
-      i0 = (long)blockIdx.x * kGemvRows;
-      if (i0 >= sw) continue;
-      cnt = (int)min((long)kGemvRows, sw - i0);
-    } else if (FWD) {
-      i0 = kb0 + sw + (long)(blockIdx.x - NZB) * kGemvRows;   // rows below the block
-      if (i0 >= nf) continue;
-      cnt = (int)min((long)kGemvRows, nf - i0);
-    } else {
-      i0 = (long)(blockIdx.x - NZB) * kGemvRows;              // rows above the block
-      if (i0 >= kb0) continue;
-      cnt = (int)min((long)kGemvRows, kb0 - i0);
-    }
-    for (int e = tid; e < sw * nrhs; e += 256) {
-      const int k = e / nrhs, r = e % nrhs;
-      vr_[k * kGemvRhs + r] = Vr[(d.e0 + kb0 + k) * (long)nrhs + r];
-      vi_[k * kGemvRhs + r] = Vi[(d.e0 + kb0 + k) * (long)nrhs + r];
-    }
-    __syncthreads();
-    const R* Br = fac + (FWD ? d.m : d.h) + (long)(kb0 / kSB) * 2 * kSB * kSB;   // M (forward) or H
-    const R* Bi = Br + kSB * kSB;
-    for (int row = tid / kGemvLanes; row < cnt; row += 256 / kGemvLanes) {
-      const long gi = i0 + row;
-      const R* ar;
-      const R* ai;
-      if (brole) {
-        ar = Br + gi * kSB;
-        ai = Bi + gi * kSB;
-      } else if (!FWD || gi < np) {
-        ar = fac + d.p + gi * nf + kb0;
-        ai = fac + d.p + np * nf + gi * nf + kb0;
-      } else {
-        ar = fac + d.l + (gi - np) * np + kb0;
-        ai = fac + d.l + (long)d.nb * np + (gi - np) * np + kb0;
+constexpr int kGemvRows = 256 / kGemvLanes;   // rows per workgroup: more workgroups per front
+
+// A lane's factor values of up to UN whole steps of kGemvLanes columns of a
+// row (n of them used, the same n in the whole wave): every load is issued
+// before the first wait and addressed by a constant offset.
+template <typename R, int NR, int UN>
+struct GemvRow {
+  R a[UN], b[UN];
+  __device__ __forceinline__ void load(const R* p, const R* q, int n) {
+    static_for<0, UN>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      if (i < n) {
+        a[i] = p[i * kGemvLanes];
+        b[i] = q[i * kGemvLanes];
       }
-      R sr[kGemvRhs], si[kGemvRhs];
+    });
+  }
+  // s[r] += sum over the steps, columns ascending, of the row times the vector in LDS ([column][rhs], re and im)
+  __device__ __forceinline__ void add(const C<R>* v, int n, R (&sr)[NR], R (&si)[NR]) {
+    static_for<0, UN>([&](auto I) {
+      constexpr int i = decltype(I)::value;
+      if (i < n)
 #pragma unroll
-      for (int r = 0; r < kGemvRhs; ++r) sr[r] = si[r] = R(0);
-      for (int k = sub; k < sw; k += kGemvLanes) {
-        const R a = ar[k], b = ai[k];
-#pragma unroll
-        for (int r = 0; r < kGemvRhs; ++r) {
-          if (r < nrhs) {
-            const R xr = vr_[k * kGemvRhs + r], xi = vi_[k * kGemvRhs + r];
-            sr[r] += a * xr - b * xi;
-            si[r] += a * xi + b * xr;
-          }
+        for (int r = 0; r < NR; ++r) {
+          const C<R> x = v[i * kGemvLanes * NR + r];
+          sr[r] += a[i] * x.re - b[i] * x.im;
+          si[r] += a[i] * x.im + b[i] * x.re;
         }
-      }
+    });
+  }
+};
+
+template <typename R>
+__device__ __forceinline__ R row_sum(R x) {
+  x += row_ror<8>(x);
+  x += row_ror<4>(x);
+  x += row_ror<2>(x);
+  return x + row_ror<1>(x);
+}
+
+// The row's sums over its kGemvLanes lanes; lane r < NR ends with rhs r's.
+template <typename R, int NR>
+__device__ __forceinline__ void gemv_reduce(const R (&sr)[NR], const R (&si)[NR], int sub, R& vr, R& vi) {
+  static_assert(kGemvLanes == 16, "a DPP row");
+  vr = row_sum(sr[0]);
+  vi = row_sum(si[0]);
 #pragma unroll
-      for (int r = 0; r < kGemvRhs; ++r)
-        if (r < nrhs)
-#pragma unroll
-          for (int off = kGemvLanes / 2; off > 0; off >>= 1) {
-            sr[r] += __shfl_xor(sr[r], off);
-            si[r] += __shfl_xor(si[r], off);
-          }
-      if (sub < nrhs) {
-        R vr = sr[0], vi = si[0];
-#pragma unroll
-        for (int r = 1; r < kGemvRhs; ++r)
-          if (sub == r) {
-            vr = sr[r];
-            vi = si[r];
-          }
-        const int r = sub;
-        if (brole) {
-          // z (forward) or x (backward) rows of the block
-          R* Or = FWD ? Zr : Xr;
-          R* Oi = FWD ? Zi : Xi;
-          Or[(d.e0 + kb0 + gi) * nrhs + r] = vr;
-          Oi[(d.e0 + kb0 + gi) * nrhs + r] = vi;
-        } else if (FWD) {
-          const long dst = gi < np ? (d.e0 + gi) * nrhs + r : (d.u + gi - np) * nrhs + r;
-          R* Tr = gi < np ? Xr : Ur;
-          R* Ti = gi < np ? Xi : Ui;
-          Tr[dst] -= vr;
-          Ti[dst] -= vi;
-        } else {
-          Zr[(d.e0 + gi) * nrhs + r] -= vr;
-          Zi[(d.e0 + gi) * nrhs + r] -= vi;
-        }
-      }
+  for (int r = 1; r < NR; ++r) {
+    const R tr = row_sum(sr[r]), ti = row_sum(si[r]);
+    if (sub == r) {
+      vr = tr;
+      vi = ti;
     }
-    __syncthreads();   // the vector is restaged for the next front
   }
 }
 
-// Few right-hand sides: bwd_u12_kernel as matrix-vector products,
-// kGemvLanes lanes per pivot row over the split's kKS boundary columns (gathered x in LDS); the
-// same outputs (in place with one split, else the split's partial sums).
-template <typename R>
+// UN * kGemvLanes: the widest super-block of the level, at most kSB.  Workgroup
+// blockIdx.x takes the 16-row tiles blockIdx.x + i gridDim.x of the block
+// (M or H) and of the rows outside it.
+template <typename R, bool FWD, int NR, int UN>
+__global__ __launch_bounds__(256) void sb_gemv_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl,
+                                                      int nlvl, int kb0, const R* __restrict__ fac,
+                                                      R* __restrict__ Xr, R* __restrict__ Xi, R* __restrict__ Zr,
+                                                      R* __restrict__ Zi, R* __restrict__ Ur, R* __restrict__ Ui) {
+  __shared__ C<R> v_[UN * kGemvLanes * NR];
+  const int tid = threadIdx.x, sub = tid % kGemvLanes, row = tid / kGemvLanes;
+  // the block's vector: x rows (forward) or y rows (backward) of the block
+  const R* Vr = FWD ? Xr : Zr;
+  const R* Vi = FWD ? Xi : Zi;
+  bool first = true;
+  for (int q = blockIdx.y; q < nlvl; q += gridDim.y) {
+    const FrontDev d = fr[lvl[q]];
+    asm volatile("" ::"s"(d.np), "s"(d.nb), "s"(d.nf), "s"(d.e0), "s"(d.p), "s"(d.l), "s"(d.u), "s"(d.m), "s"(d.h));
+    if (kb0 >= d.np) continue;
+    const int sw = min(kSB, d.np - kb0), mt = (sw + kGemvRows - 1) / kGemvRows;
+    const int out0 = FWD ? kb0 + sw : 0, outs = (FWD ? d.nf : kb0) - out0;   // rows below (forward) or above the block
+    const int nt = mt + (outs + kGemvRows - 1) / kGemvRows;
+    const long nf = d.nf, np = d.np;
+    bool staged = false;
+    for (int t = blockIdx.x; t < nt; t += gridDim.x) {
+      const bool brole = t < mt;
+      const int i0 = (brole ? t : t - mt) * kGemvRows, cnt = min(kGemvRows, (brole ? sw : outs) - i0);
+      const long gi = (brole ? 0 : out0) + i0 + min(row, cnt - 1);
+      const R* ar;
+      long im;
+      int k0 = 0, k1 = sw;
+      if (brole) {
+        ar = fac + (FWD ? d.m : d.h) + (long)(kb0 / kSB) * 2 * kSB * kSB + gi * kSB;   // M (forward) or H
+        im = (long)kSB * kSB;
+        if (FWD)
+          k1 = min(sw, (i0 / kT + 1) * kT);
+        else
+          k0 = i0;
+      } else if (!FWD || gi < np) {
+        ar = fac + d.p + gi * nf + kb0;
+        im = np * nf;
+      } else {
+        ar = fac + d.l + (gi - np) * np + kb0;
+        im = (long)d.nb * np;
+      }
+      ar += k0 + sub;
+      const int ns = (k1 - k0) / kGemvLanes, kt = k0 + ns * kGemvLanes + sub;   // whole steps, then a part of one
+      GemvRow<R, NR, UN> g;
+      g.load(ar, ar + im, ns);
+      GemvRow<R, NR, 1> tail;
+      if (kt < k1) tail.load(ar + ns * kGemvLanes, ar + im + ns * kGemvLanes, 1);
+      // the row this lane updates, read ahead of the products
+      const bool bnd = FWD && !brole && gi >= np;
+      R* const Tr = brole ? (FWD ? Zr : Xr) : bnd ? Ur : FWD ? Xr : Zr;
+      R* const Ti = brole ? (FWD ? Zi : Xi) : bnd ? Ui : FWD ? Xi : Zi;
+      const long dst = (brole ? d.e0 + kb0 + gi : bnd ? d.u + gi - np : d.e0 + gi) * NR + min(sub, NR - 1);
+      const C<R> old = brole ? C<R>{} : C<R>{Tr[dst], Ti[dst]};
+      if (!staged) {
+        if (!first) __syncthreads();   // the previous front's reads of the vector are done
+        first = false;
+        for (int e = tid; e < sw * NR; e += 256)
+          v_[e] = {Vr[(d.e0 + kb0) * (long)NR + e], Vi[(d.e0 + kb0) * (long)NR + e]};
+        __syncthreads();
+        staged = true;
+      }
+      R sr[NR] = {}, si[NR] = {};
+      g.add(v_ + (k0 + sub) * NR, ns, sr, si);
+      if (kt < k1) tail.add(v_ + kt * NR, 1, sr, si);
+      R vr, vi;
+      gemv_reduce<R, NR>(sr, si, sub, vr, vi);
+      if (sub < NR && row < cnt) {
+        Tr[dst] = brole ? vr : old.re - vr;
+        Ti[dst] = brole ? vi : old.im - vi;
+      }
+    }
+  }
+}
+
+// Up to kGemvRhs right-hand sides: bwd_u12_kernel as matrix-vector products,
+// kGemvLanes lanes per pivot row over the split's kKS boundary columns
+// (gathered x in LDS), in rounds of UN kGemvLanes columns with two rounds'
+// loads in flight; the same outputs (in place with one split, else the split's
+// partial sums).  The boundary's indices are loaded ahead of the factor, so the
+// gather does not wait for it.
+template <typename R, int NR, int UN>
 __global__ __launch_bounds__(256) void u12_gemv_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl,
                                                        int nlvl, int nks_max, long np_max,
-                                                       const R* __restrict__ fac, const int* __restrict__ ib, int nrhs,
+                                                       const R* __restrict__ fac, const int* __restrict__ ib,
                                                        const R* __restrict__ Xr, const R* __restrict__ Xi,
                                                        R* __restrict__ Zr, R* __restrict__ Zi, R* __restrict__ Pr,
                                                        R* __restrict__ Pi) {
-  __shared__ R vr_[kKS * kGemvRhs], vi_[kKS * kGemvRhs];
-  const int tid = threadIdx.x, sub = tid % kGemvLanes;
+  constexpr int RK = UN * kGemvLanes, GI = kKS * NR / 256;
+  __shared__ C<R> v_[kKS * NR];
+  const int tid = threadIdx.x, sub = tid % kGemvLanes, row = tid / kGemvLanes;
   const int ks = blockIdx.z;
+  bool first = true;
   for (int q = blockIdx.y; q < nlvl; q += gridDim.y) {
     const FrontDev d = fr[lvl[q]];
+    asm volatile("" ::"s"(d.np), "s"(d.nb), "s"(d.nf), "s"(d.e0), "s"(d.p), "s"(d.bm));
     const long np = d.np, nf = d.nf, nb = d.nb;
     const int nks = (int)((nb + kKS - 1) / kKS);
     if (ks >= nks) continue;
-    const long i0 = (long)blockIdx.x * kGemvRows;
-    if (i0 >= np) continue;
-    const int cnt = (int)min((long)kGemvRows, np - i0);
     const long j0 = (long)ks * kKS;
-    const int nj = (int)min((long)kKS, nb - j0);
-    for (int e = tid; e < nj * nrhs; e += 256) {
-      const int j = e / nrhs, r = e % nrhs;
-      const long x = ib[d.bm + j0 + j];
-      vr_[j * kGemvRhs + r] = Xr[x * nrhs + r];
-      vi_[j * kGemvRhs + r] = Xi[x * nrhs + r];
-    }
-    __syncthreads();
-    for (int row = tid / kGemvLanes; row < cnt; row += 256 / kGemvLanes) {
-      const long gi = i0 + row;
-      const R* ar = fac + d.p + gi * nf + np + j0;
-      const R* ai = fac + d.p + np * nf + gi * nf + np + j0;
-      R sr[kGemvRhs], si[kGemvRhs];
+    const int nj = (int)min((long)kKS, nb - j0), ns = nj / kGemvLanes, jt = ns * kGemvLanes + sub;
+    bool staged = false;
+    for (long i0 = (long)blockIdx.x * kGemvRows; i0 < np; i0 += (long)gridDim.x * kGemvRows) {
+      int bi[GI];
+      if (!staged)
 #pragma unroll
-      for (int r = 0; r < kGemvRhs; ++r) sr[r] = si[r] = R(0);
-      for (int j = sub; j < nj; j += kGemvLanes) {
-        const R a = ar[j], b = ai[j];
+        for (int i = 0; i < GI; ++i) bi[i] = ib[d.bm + j0 + min((tid + 256 * i) / NR, nj - 1)];
+      const int cnt = (int)min((long)kGemvRows, np - i0);
+      const long gi = i0 + min(row, cnt - 1);
+      const R* ar = fac + d.p + gi * nf + np + j0 + sub;
+      const R* ai = ar + np * nf;
+      GemvRow<R, NR, UN> g, h;
+      GemvRow<R, NR, 1> tail;
+      g.load(ar, ai, ns);
+      h.load(ar + RK, ai + RK, ns - UN);
+      if (jt < nj) tail.load(ar + ns * kGemvLanes, ai + ns * kGemvLanes, 1);
+      const long dst = (d.e0 + gi) * NR + min(sub, NR - 1);
+      const R tr = nks == 1 ? Zr[dst] : R(0), ti = nks == 1 ? Zi[dst] : R(0);
+      if (!staged) {
+        if (!first) __syncthreads();   // the previous front's reads of the vector are done
+        first = false;
 #pragma unroll
-        for (int r = 0; r < kGemvRhs; ++r) {
-          if (r < nrhs) {
-            const R xr = vr_[j * kGemvRhs + r], xi = vi_[j * kGemvRhs + r];
-            sr[r] += a * xr - b * xi;
-            si[r] += a * xi + b * xr;
+        for (int i = 0; i < GI; ++i) {
+          const int e = tid + 256 * i;
+          if (e < nj * NR) {
+            const long x = (long)bi[i] * NR + e % NR;
+            v_[e] = {Xr[x], Xi[x]};
           }
         }
+        __syncthreads();
+        staged = true;
       }
-#pragma unroll
-      for (int r = 0; r < kGemvRhs; ++r)
-        if (r < nrhs)
-#pragma unroll
-          for (int off = kGemvLanes / 2; off > 0; off >>= 1) {
-            sr[r] += __shfl_xor(sr[r], off);
-            si[r] += __shfl_xor(si[r], off);
-          }
-      if (sub < nrhs) {
-        R vr = sr[0], vi = si[0];
-#pragma unroll
-        for (int r = 1; r < kGemvRhs; ++r)
-          if (sub == r) {
-            vr = sr[r];
-            vi = si[r];
-          }
+      R sr[NR] = {}, si[NR] = {};
+      const C<R>* v = v_ + sub * NR;
+      for (int k = 0; k < ns; k += 2 * UN, v += 2 * RK * NR) {
+        ar += 2 * RK;
+        ai += 2 * RK;
+        g.add(v, ns - k, sr, si);
+        g.load(ar, ai, ns - k - 2 * UN);
+        h.add(v + RK * NR, ns - k - UN, sr, si);
+        h.load(ar + RK, ai + RK, ns - k - 3 * UN);
+      }
+      if (jt < nj) tail.add(v_ + jt * NR, 1, sr, si);
+      R vr, vi;
+      gemv_reduce<R, NR>(sr, si, sub, vr, vi);
+      if (sub < NR && row < cnt) {
         if (nks == 1) {
-          Zr[(d.e0 + gi) * nrhs + sub] -= vr;
-          Zi[(d.e0 + gi) * nrhs + sub] -= vi;
+          Zr[dst] = tr - vr;
+          Zi[dst] = ti - vi;
         } else {
-          const long o = (((long)q * nks_max + ks) * np_max + gi) * nrhs + sub;
+          const long o = (((long)q * nks_max + ks) * np_max + gi) * NR + sub;
           Pr[o] = vr;
           Pi[o] = vi;
         }
       }
     }
-    __syncthreads();   // the gathered vector is restaged for the next front
   }
 }
 
@@ -2039,6 +2107,7 @@ struct GpuSolver {
   std::vector<int> lvl_np, lvl_nf;     // largest np / nf per level
   std::vector<size_t> lvl_elems;       // level buffer elements (R) per level
   DevBuf fd, lvl_d, ib, fac;
+  DevBuf cinv;                         // children's rows per front point (child_map_kernel)
   DevBuf ipm;                          // inverse of the final elimination order (natural -> position)
   long u_rows = 0;                     // sum of nb over the nodes
   DevBuf X, Z, U;                      // solve work, sized for cap_rhs
@@ -2195,6 +2264,40 @@ void launch_sb(bool fwd, unsigned gx, unsigned gy, int nrhs, hipStream_t s, cons
                        Xi, Zr, Zi);
 }
 
+// f(integral_constant<int, NR>) for nrhs = NR <= kGemvRhs
+template <typename F>
+void with_rhs(int nrhs, F&& f) {
+  static_assert(kGemvRhs == 4, "one kernel per count");
+  switch (nrhs) {
+    case 1: f(std::integral_constant<int, 1>{}); break;
+    case 2: f(std::integral_constant<int, 2>{}); break;
+    case 3: f(std::integral_constant<int, 3>{}); break;
+    default: f(std::integral_constant<int, 4>{}); break;
+  }
+}
+
+// Workgroups per front of the matrix-vector kernels: a row tile each where the
+// level's fronts are few, else about kGemvGrid in all, so that a workgroup of a
+// wide level keeps its front's descriptor and vector for several tiles.
+// Same apply with 2048 / 4096 / 8192 / a tile each: 936 / 923 / 948 / 1262 us
+// (the last before the constant offsets: the levels of 2048 fronts and fewer
+// took 10 to 45 us a launch, now 5 to 24).
+constexpr long kGemvGrid = 4096;
+inline unsigned gemv_grid(long tiles, int nl) {
+  return (unsigned)std::max(1L, std::min(tiles, (kGemvGrid + nl - 1) / nl));
+}
+
+template <typename R, bool FWD>
+void launch_sb_gemv(long tiles, unsigned gy, long sw, int nrhs, hipStream_t s, const FrontDev* fr, const int* lvl,
+                    int nl, int kb0, const R* fac, R* Xr, R* Xi, R* Zr, R* Zi, R* Ur, R* Ui) {
+  with_rhs(nrhs, [&](auto NR) {
+    constexpr int nr = decltype(NR)::value;
+    auto* k = sw <= 8 * kGemvLanes ? sb_gemv_kernel<R, FWD, nr, 8> : sb_gemv_kernel<R, FWD, nr, kSB / kGemvLanes>;
+    hipLaunchKernelGGL(k, dim3(gemv_grid(tiles, nl), gy), dim3(256), 0, s, fr, lvl, nl, kb0, fac, Xr, Xi, Zr, Zi, Ur,
+                       Ui);
+  });
+}
+
 template <typename R>
 ls_status solve_numeric(GpuSolver& g, const C<double>* b, C<double>* xo, int nrhs, hipStream_t s) {
   const int L = (int)g.levels.size();
@@ -2226,6 +2329,7 @@ ls_status solve_numeric(GpuSolver& g, const C<double>* b, C<double>* xo, int nrh
   const FrontDev* fr = g.fd.as<FrontDev>();
   const int* ib = g.ib.as<int>();
   const R* fac = g.fac.as<R>();
+  const int* cinv = g.cinv.as<int>();
   const unsigned gz = (unsigned)((nrhs + kSR - 1) / kSR);
   const int rpp = 256 / rhs_lanes(nrhs);     // rows per workgroup pass of the gather kernels
   if (nrhs >= kSolTileRhs)
@@ -2233,36 +2337,26 @@ ls_status solve_numeric(GpuSolver& g, const C<double>* b, C<double>* xo, int nrh
                        dim3(256), 0, s, b, N, nrhs, (const int*)g.ipm.as<int>(), Xr, Xi);
   else
     hipLaunchKernelGGL(sol_in_kernel<R>, dim3(grid_for(N, rpp, 65535)), dim3(256), 0, s, b, N, nrhs, ib, Xr, Xi);
-  hipLaunchKernelGGL(zero_kernel<R>, dim3(grid_for(2 * std::max(1L, g.u_rows) * nrhs, 256, 1 << 16)), dim3(256), 0,
-                     s, Ur, 2 * std::max(1L, g.u_rows) * nrhs);
   for (int dep = L - 1; dep >= 0; --dep) {
     const int nl = (int)g.levels[dep].size();
     const int* lvl = g.lvl_d.as<int>() + g.lvl_off[dep];
     const unsigned gy = (unsigned)std::min(nl, 65535);
     const long mnf = g.lvl_nf[dep], mnp = g.lvl_np[dep];
-    if (dep + 1 < L)
-      for (int slot = 0; slot < 2; ++slot) {
-        long mcnb = 0;
-        for (int id : g.levels[dep])
-          if (g.fh[id].child[slot] >= 0) mcnb = std::max(mcnb, (long)g.fh[g.fh[id].child[slot]].nb);
-        if (mcnb == 0) continue;
-        // one front per workgroup row (a front loop would chain descriptor loads)
-        const long gxc = std::max(1L, std::min((mcnb + rpp - 1) / rpp, std::max(1L, 65536L / nl)));
-        if (g.nc == 3)
-          hipLaunchKernelGGL((fwd_child_kernel<R, 3>), dim3((unsigned)gxc, gy), dim3(256), 0, s, fr, lvl, nl, slot,
-                             ib, nrhs, Xr, Xi, Ur, Ui);
-        else
-          hipLaunchKernelGGL((fwd_child_kernel<R, 2>), dim3((unsigned)gxc, gy), dim3(256), 0, s, fr, lvl, nl, slot,
-                             ib, nrhs, Xr, Xi, Ur, Ui);
-      }
+    {
+      // one front per workgroup row (a front loop would chain descriptor loads)
+      const long gxc = std::max(1L, std::min((mnf + rpp - 1) / rpp, std::max(1L, 65536L / nl)));
+      if (g.nc == 3)
+        hipLaunchKernelGGL((fwd_child_kernel<R, 3>), dim3((unsigned)gxc, gy), dim3(256), 0, s, fr, lvl, nl, cinv, nrhs,
+                           Xr, Xi, Ur, Ui);
+      else
+        hipLaunchKernelGGL((fwd_child_kernel<R, 2>), dim3((unsigned)gxc, gy), dim3(256), 0, s, fr, lvl, nl, cinv, nrhs,
+                           Xr, Xi, Ur, Ui);
+    }
     for (long kb0 = 0; kb0 < mnp; kb0 += kSB) {
       const unsigned gx = (unsigned)(kSB / kRB + std::max(0L, (mnf - kb0 - 1 + kRB - 1) / kRB));
-      if (nrhs <= kGemvRhs) {
-        const unsigned gxg =
-            (unsigned)(kSB / kGemvRows + std::max(0L, (mnf - kb0 - 1 + kGemvRows - 1) / kGemvRows));
-        hipLaunchKernelGGL((sb_gemv_kernel<R, true>), dim3(gxg, gy), dim3(256), 0, s, fr, lvl, nl, (int)kb0, fac,
-                           nrhs, Xr, Xi, Zr, Zi, Ur, Ui);
-      }
+      if (nrhs <= kGemvRhs)
+        launch_sb_gemv<R, true>((mnf - kb0 + kGemvRows - 1) / kGemvRows + 1, gy, mnp - kb0, nrhs, s, fr, lvl, nl,
+                                (int)kb0, fac, Xr, Xi, Zr, Zi, Ur, Ui);
       else
         launch_sb<R>(true, gx, gy, nrhs, s, fr, lvl, nl, (int)kb0, fac, Xr, Xi, Zr, Zi, Ur, Ui);
     }
@@ -2274,10 +2368,12 @@ ls_status solve_numeric(GpuSolver& g, const C<double>* b, C<double>* xo, int nrh
     const long mnp = g.lvl_np[dep];
     const unsigned gu = (unsigned)std::max(1L, (mnp + kRB - 1) / kRB);
     if (nrhs <= kGemvRhs)
-      hipLaunchKernelGGL(u12_gemv_kernel<R>, dim3((unsigned)std::max(1L, (mnp + kGemvRows - 1) / kGemvRows), gy,
-                                                  nks[dep]),
-                         dim3(256), 0, s, fr, lvl, nl, nks[dep], mnp, fac, ib, nrhs, (const R*)Xr, (const R*)Xi, Zr,
-                         Zi, Pr, Pi);
+      with_rhs(nrhs, [&](auto NR) {
+        constexpr int nr = decltype(NR)::value;
+        auto* k = g.lvl_nf[dep] <= 12 * kGemvLanes ? u12_gemv_kernel<R, nr, 4> : u12_gemv_kernel<R, nr, 8>;
+        hipLaunchKernelGGL(k, dim3(gemv_grid((mnp + kGemvRows - 1) / kGemvRows, nl), gy, nks[dep]), dim3(256), 0, s, fr,
+                           lvl, nl, nks[dep], mnp, fac, ib, (const R*)Xr, (const R*)Xi, Zr, Zi, Pr, Pi);
+      });
     else if (nrhs <= kThinRhs)
       launch_thin<R, 2>((mnp + 15) / 16, gy, (unsigned)nks[dep], s, fr, lvl, nl, 0, nks[dep], mnp, fac, ib, nrhs, Xr,
                         Xi, Zr, Zi, Ur, Ui, Pr, Pi);
@@ -2290,11 +2386,10 @@ ls_status solve_numeric(GpuSolver& g, const C<double>* b, C<double>* xo, int nrh
     for (long kb0 = ((mnp - 1) / kSB) * kSB; kb0 >= 0; kb0 -= kSB) {
       const unsigned gx = (unsigned)(kSB / kRB + (kb0 + kRB - 1) / kRB);
       if (nrhs <= kGemvRhs) {
-        const unsigned gxg = (unsigned)(kSB / kGemvRows + (kb0 + kGemvRows - 1) / kGemvRows);
-        hipLaunchKernelGGL((sb_gemv_kernel<R, false>), dim3(gxg, gy), dim3(256), 0, s, fr, lvl, nl, (int)kb0, fac,
-                           nrhs, Xr, Xi, Zr, Zi, Ur, Ui);
-      }
-      else
+        const long sw = std::min((long)kSB, mnp - kb0);
+        launch_sb_gemv<R, false>((sw + kb0 + kGemvRows - 1) / kGemvRows, gy, sw, nrhs, s, fr, lvl, nl, (int)kb0, fac, Xr,
+                                 Xi, Zr, Zi, Ur, Ui);
+      } else
         launch_sb<R>(false, gx, gy, nrhs, s, fr, lvl, nl, (int)kb0, fac, Xr, Xi, Zr, Zi, Ur, Ui);
     }
   }
@@ -2339,7 +2434,14 @@ ls_status gpu_factor_grid(const int dims[3], int nc, const C<double>* rows_dev, 
   g->flops = sym.flops;
   const long fac_elems = sym.fac_elems;
   const IntMap& ibh = sym.ibh;
+  long cinv_elems = 0;
+  for (FrontDev& d : g->fh) {
+    d.ci = cinv_elems;
+    cinv_elems += 2L * (d.nf / nc);
+    for (int slot = 0; slot < 2; ++slot) d.cu[slot] = d.child[slot] >= 0 ? g->fh[d.child[slot]].u : 0;
+  }
   const size_t rs = fp32 ? sizeof(float) : sizeof(double);
+  LS_TRY(g->cinv.alloc((size_t)cinv_elems * sizeof(int)));
   LS_TRY(g->fac.alloc((size_t)(fac_elems + kThinPad) * rs));
   LS_TRY(g->ib.alloc(ibh.size() * sizeof(int)));
   LS_TRY(g->ipm.alloc((size_t)std::max(1L, g->N) * sizeof(int)));
@@ -2351,6 +2453,14 @@ ls_status gpu_factor_grid(const int dims[3], int nc, const C<double>* rows_dev, 
   LS_HIP(hipMemcpyAsync(g->fd.p, g->fh.data(), g->fh.size() * sizeof(FrontDev), hipMemcpyHostToDevice, s));
   LS_HIP(hipMemcpyAsync(g->lvl_d.p, lv.data(), lv.size() * sizeof(int), hipMemcpyHostToDevice, s));
   g->bytes = (size_t)fac_elems * rs;
+  const int nfr = (int)g->fh.size();
+  if (nc == 3)
+    hipLaunchKernelGGL(child_map_kernel<3>, dim3(std::min(nfr, 65535)), dim3(256), 0, s, g->fd.as<FrontDev>(), nfr,
+                       g->ib.as<int>(), g->cinv.as<int>());
+  else
+    hipLaunchKernelGGL(child_map_kernel<2>, dim3(std::min(nfr, 65535)), dim3(256), 0, s, g->fd.as<FrontDev>(), nfr,
+                       g->ib.as<int>(), g->cinv.as<int>());
+  LS_HIP(hipGetLastError());
   if (fp32)
     LS_TRY(factor_numeric<float>(*g, rows_dev, s));
   else

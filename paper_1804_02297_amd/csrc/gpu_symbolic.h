@@ -35,6 +35,8 @@ struct FrontDev {
   long u;    // solve: first row of the node's update vector
   long m;    // factor: per super-block forward map M (z = M x on the block), [kSB][kSB] re, then im
   long h;    // factor: per super-block backward map H = U_block^-1, same layout
+  long ci;      // ints of the children's map: per child and front point, the child's boundary point or -1
+  long cu[2];   // the children's first rows of the update vector
 };
 
 // Leaves ints uninitialised on resize: the index maps (hundreds of MB at the

@@ -235,3 +235,28 @@ def test_gpu_factor_pivots_inside_tiles(lib, prec, n):
     print(f"n={n} {prec} residual {res:.2e}", flush=True)
     assert res <= (1e-12 if prec == "c128" else 1e-4)
     sp.close()
+
+
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+@pytest.mark.parametrize("n", [15, 24])
+def test_few_rhs_solves_on_larger_fronts(lib, prec, n):
+    """One to four right-hand sides (matrix-vector kernels): fronts of several
+    super-blocks, split boundary products, columns that end inside a step of
+    16 and levels whose workgroups take several row tiles (n = 24), against
+    the MFMA tiles of a 33-rhs solve, to rounding, and among themselves bit for
+    bit."""
+    from paper_1804_02297_amd.binding import SparseGpu
+    g = np.random.Generator(np.random.PCG64(60 + n))
+    rows = 0.1 * (g.standard_normal((n ** 3, 3, 27, 3)) + 1j * g.standard_normal((n ** 3, 3, 27, 3)))
+    for r in range(3):
+        rows[:, r, 13, r] += 3.0
+    sp = SparseGpu(n, rows, prec=prec)
+    b = I.random_field(33, n, 82)
+    full = sp.solve(_dev(b)).cpu().numpy()
+    tol = 1e-12 if prec == "c128" else 2e-5
+    single = np.stack([sp.solve(_dev(b[i:i + 1])).cpu().numpy()[0] for i in range(4)])
+    print(f"n={n} {prec} {np.abs(full[:4] - single).max() / np.abs(single).max():.2e}", flush=True)
+    assert np.abs(full[:4] - single).max() <= tol * np.abs(single).max()
+    for nr in (2, 3, 4):
+        assert np.array_equal(sp.solve(_dev(b[:nr])).cpu().numpy(), single[:nr]), nr
+    sp.close()
