@@ -18,7 +18,8 @@
 //                         Rayleigh-Ritz with a cyclic Jacobi on the 8x8 block.
 //   beta_kernel         : beta = B^H alpha.
 //   assemble_rows_kernel: S rows per point, slots indexed by neighbour offset.
-//   qapply_kernel       : z = Q v, a 27-point 3x3-block stencil.
+//   qapply_class_kernel,
+//   qapply_kernel       : z = Q v, a 27-point 3x3-block stencil (per class, per point).
 #include "common.h"
 #include "kernel_eval.h"
 #include "stencil.h"
@@ -471,15 +472,119 @@ __global__ void assemble_rows_kernel(int n, const C<double>* __restrict__ m, con
 }
 
 // z = Q v: z_r(i) = sum_{a in tau(i)} sum_c conj(alpha[(a,c), r]) v_c(i + a).  Fields [rhs][3][n^3].
-// A thread takes one point and RB right-hand sides, so that each 3 x 3 block
-// of the point's coefficients is read once per RB rhs: per-point stencils
-// hold 243 coefficients (3.9 KB) for every point, and one thread per (point,
-// rhs) read them once per rhs (17 ms for 64 rhs at n = 64 against 2.7 ms
-// with the 27 shared class stencils; 5.3 ms with eight rhs per thread).  Per
-// (point, rhs, r) the sum runs over (a, c) in the same order for every RB.
+// Per (point, rhs, r) the sum runs over (a, c) in the same order in both kernels.
+
+// The 27 class stencils.  A workgroup's points all belong to one class, a box
+// of the grid, so the coefficients are scalar loads, and a thread takes PT
+// neighbours along i1 of one rhs: PT + 2 planes of v read for PT points, a row
+// of them ahead of the sums.  972 FP64 FMAs a point (45 us for 16 rhs at
+// n = 48); the waits for the scalar loads are what is left.  With one point a
+// lane in grid order classes met inside a wave and every lane loaded its
+// coefficients itself, 324 16-byte loads a point at 16 cycles each: 299 us for
+// 16 rhs at n = 48, 47 us at n = 32, now 97 and 41 (PT = 1: 111 and 52; PT = 4:
+// 96 and 45, but 22 us for one rhs at n = 32 against 15).
+// Items of a class: the first of each PT points of its box, i3 fastest, rhs slowest.
+__host__ __device__ inline int class_extent(int c, int n) { return c == CLS_IN ? n - 2 : 1; }
+template <int PT>
+__host__ __device__ inline int class_items(int kappa, int n) {
+  return (class_extent(kappa / 9, n) + PT - 1) / PT * class_extent(kappa / 3 % 3, n) * class_extent(kappa % 3, n);
+}
+template <int PT>
+__host__ __device__ inline long class_groups(int kappa, int n, int nrhs) {
+  return ((long)class_items<PT>(kappa, n) * nrhs + 255) / 256;
+}
+
+template <int PT>
+__global__ __launch_bounds__(256) void qapply_class_kernel(int n, int nrhs, const C<double>* __restrict__ alpha,
+                                                           long cstride, const C<double>* __restrict__ v,
+                                                           C<double>* __restrict__ z) {
+  long grp = blockIdx.x;
+  int kappa = 0;
+  for (; kappa < 26; ++kappa) {
+    const long g = class_groups<PT>(kappa, n, nrhs);
+    if (grp < g) break;
+    grp -= g;
+  }
+  const int c1 = kappa / 9, c2 = kappa / 3 % 3, c3 = kappa % 3;
+  const int e2 = class_extent(c2, n), e3 = class_extent(c3, n), items = class_items<PT>(kappa, n);
+  const long first = grp * 256;
+  const int rhs0 = (int)(first / items);
+  const unsigned in0 = (unsigned)(first - (long)rhs0 * items) + threadIdx.x;
+  const int rhs = rhs0 + (int)(in0 / (unsigned)items), it = (int)(in0 % (unsigned)items);
+  if (rhs >= nrhs) return;
+  const auto origin = [&](int c) { return c == CLS_LO ? 0 : c == CLS_IN ? 1 : n - 1; };
+  const int i3 = origin(c3) + it % e3, i2 = origin(c2) + it / e3 % e2, i1 = origin(c1) + PT * (it / e3 / e2);
+  const int lo1 = c1 == CLS_LO ? 0 : -1, hi1 = c1 == CLS_HI ? 0 : 1;
+  const int lo2 = c2 == CLS_LO ? 0 : -1, hi2 = c2 == CLS_HI ? 0 : 1;
+  const int lo3 = c3 == CLS_LO ? 0 : -1;
+  const int n2 = hi2 - lo2 + 1;
+  const int np = c1 == CLS_IN ? PT : 1;                      // points of the class's threads
+  const int last = min(np, n - 1 - i1) + hi1 - 1;            // last plane that one of this thread's points needs
+  const long n3 = (long)n * n * n;
+  const C<double>* vb = v + ((long)rhs * 3 * n3 + ((long)i1 * n + i2) * n + i3);
+  const C<double>* al = alpha + kappa * cstride;
+  C<double> acc[PT][3];
+#pragma unroll
+  for (int p = 0; p < PT; ++p)
+#pragma unroll
+    for (int r = 0; r < 3; ++r) acc[p][r] = cmk(0.0, 0.0);
+  // row t: plane lo1 + t / n2, row lo2 + t % n2 of it; the next row of v is loaded ahead of a row's sums
+  const int rows = (hi1 - lo1 + np) * n2;
+  struct Row {
+    C<double> v[3][3];
+  };
+  const auto load = [&](Row& w, int t, auto n3t, auto lo3) {
+    const int s1 = lo1 + t / n2, s2 = lo2 + t % n2;
+    const C<double>* vp = vb + ((long)min(s1, c1 == CLS_IN ? last : hi1) * n + s2) * n + lo3;
+#pragma unroll
+    for (int j = 0; j < n3t; ++j)
+#pragma unroll
+      for (int c = 0; c < 3; ++c) w.v[j][c] = vp[c * n3 + j];
+  };
+  const auto add = [&](const Row& w, int t, auto n3t) {
+    const int s1 = lo1 + t / n2;
+#pragma unroll
+    for (int p = 0; p < PT; ++p) {
+      const int t1 = s1 - p;
+      if (t1 < lo1 || t1 > hi1 || p >= np) continue;
+      const C<double>* al1 = al + (t - p * n2) * n3t * 9;
+#pragma unroll
+      for (int j = 0; j < n3t; ++j)
+#pragma unroll
+        for (int c = 0; c < 3; ++c)
+#pragma unroll
+          for (int r = 0; r < 3; ++r) acc[p][r] = cfma(cconj(al1[9 * j + 3 * c + r]), w.v[j][c], acc[p][r]);
+    }
+  };
+  const auto all = [&](auto n3t, auto lo3) {
+    Row w0, w1;
+    load(w0, 0, n3t, lo3);
+    for (int t = 0; t < rows; t += 2) {
+      load(w1, min(t + 1, rows - 1), n3t, lo3);
+      add(w0, t, n3t);
+      if (t + 1 == rows) break;
+      load(w0, min(t + 2, rows - 1), n3t, lo3);
+      add(w1, t + 1, n3t);
+    }
+  };
+  if (c3 == CLS_IN)
+    all(std::integral_constant<int, 3>{}, std::integral_constant<int, -1>{});
+  else
+    all(std::integral_constant<int, 2>{}, lo3);
+#pragma unroll
+  for (int p = 0; p < PT; ++p) {
+    if (p >= np || (c1 == CLS_IN && i1 + p > n - 2)) break;
+#pragma unroll
+    for (int r = 0; r < 3; ++r) z[((long)rhs * 3 + r) * n3 + ((long)(i1 + p) * n + i2) * n + i3] = acc[p][r];
+  }
+}
+
+// Per-point stencils: one point and RB right-hand sides per thread, so that the
+// point's 243 coefficients (3.9 KB) are read once per RB rhs (one thread per
+// (point, rhs) took 17 ms for 64 rhs at n = 64, eight rhs per thread 5.3 ms).
 template <int RB>
 __global__ __launch_bounds__(256) void qapply_kernel(int n, int nrhs, const ClassGeom* __restrict__ geoms,
-                                                     const C<double>* __restrict__ alpha, long cstride, long pstride,
+                                                     const C<double>* __restrict__ alpha, long pstride,
                                                      const C<double>* __restrict__ v, C<double>* __restrict__ z) {
   const long n3 = (long)n * n * n;
   const long id = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -490,7 +595,7 @@ __global__ __launch_bounds__(256) void qapply_kernel(int n, int nrhs, const Clas
   const int i3 = (int)(p % n), i2 = (int)((p / n) % n), i1 = (int)(p / ((long)n * n));
   const int kappa = 9 * class_dim(i1, n) + 3 * class_dim(i2, n) + class_dim(i3, n);
   const ClassGeom& g = geoms[kappa];
-  const C<double>* al = alpha + (pstride ? p * pstride : kappa * cstride);
+  const C<double>* al = alpha + p * pstride;
   C<double> acc[RB][3];
 #pragma unroll
   for (int j = 0; j < RB; ++j)
@@ -607,21 +712,22 @@ ls_status assemble_rows(StencilData& sd, int n, const C<double>* m, hipStream_t 
 
 ls_status q_apply(const StencilData& sd, int n, const C<double>* v, C<double>* z, int nrhs, hipStream_t s) {
   const long n3 = (long)n * n * n;
-  const bool pp = sd.have_point;
-  const C<double>* al = pp ? sd.palpha.as<C<double>>() : sd.alpha.as<C<double>>();
-  const long ps = pp ? 81L * 3 : 0L;
-  // the 27 class stencils stay in cache: one (point, rhs) per thread, eight
-  // waves per SIMD (taking eight rhs per thread there measured 3.4 against
-  // 2.7 ms for 64 rhs at n = 64)
-  if (pp && nrhs >= 8)
+  const long ps = 81L * 3;
+  const C<double>* al = sd.have_point ? sd.palpha.as<C<double>>() : sd.alpha.as<C<double>>();
+  if (!sd.have_point) {
+    constexpr int PT = 2;
+    long groups = 0;
+    for (int kappa = 0; kappa < 27; ++kappa) groups += class_groups<PT>(kappa, n, nrhs);
+    hipLaunchKernelGGL(qapply_class_kernel<PT>, dim3((unsigned)groups), dim3(256), 0, s, n, nrhs, al, ps, v, z);
+  } else if (nrhs >= 8)
     hipLaunchKernelGGL(qapply_kernel<8>, dim3((unsigned)((n3 * ((nrhs + 7) / 8) + 255) / 256)), dim3(256), 0, s, n,
-                       nrhs, sd.geoms.as<ClassGeom>(), al, 81L * 3, ps, v, z);
-  else if (pp && nrhs >= 4)
+                       nrhs, sd.geoms.as<ClassGeom>(), al, ps, v, z);
+  else if (nrhs >= 4)
     hipLaunchKernelGGL(qapply_kernel<4>, dim3((unsigned)((n3 * ((nrhs + 3) / 4) + 255) / 256)), dim3(256), 0, s, n,
-                       nrhs, sd.geoms.as<ClassGeom>(), al, 81L * 3, ps, v, z);
+                       nrhs, sd.geoms.as<ClassGeom>(), al, ps, v, z);
   else
     hipLaunchKernelGGL(qapply_kernel<1>, dim3((unsigned)((n3 * nrhs + 255) / 256)), dim3(256), 0, s, n, nrhs,
-                       sd.geoms.as<ClassGeom>(), al, 81L * 3, ps, v, z);
+                       sd.geoms.as<ClassGeom>(), al, ps, v, z);
   return hipGetLastError() == hipSuccess ? LS_OK : LS_EHIP;
 }
 

@@ -93,3 +93,18 @@ def test_zero_contrast_preconditioner_is_identity(lib):
     v = I.random_field(1, n, 2)
     z = plan.precond(_dev(v)).cpu().numpy()
     assert np.abs(z - v).max() <= 1e-10 * np.abs(v).max()
+
+
+@pytest.mark.parametrize("n,nrhs", [(4, 7), (5, 1), (11, 3), (18, 16)])
+def test_class_stencil_product_over_boxes(lib, n, nrhs):
+    """Q v with the class stencils by the classes' boxes: extents n - 2 odd and
+    even (a thread's second point missing), boxes of less than a workgroup and
+    workgroups that cross right-hand sides.  Without contrast S = Q, so
+    S^-1 Q v = v up to the factor's rounding."""
+    plan = _plan(n, np.zeros((n, n, n), complex), max_rhs=nrhs)
+    plan.stencil_fit()
+    plan.factor()
+    v = I.random_field(nrhs, n, 12)
+    z = plan.precond(_dev(v)).cpu().numpy()
+    print(f"n={n} x{nrhs} {np.abs(z - v).max() / np.abs(v).max():.2e}", flush=True)
+    assert np.abs(z - v).max() <= 1e-10 * np.abs(v).max()
