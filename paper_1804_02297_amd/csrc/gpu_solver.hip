@@ -576,29 +576,39 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) =
   }
 }
 
-// 64 x 64 complex tile product acc += A B on MFMA: A [64][lda] (rows x K) and
-// B [K][ldb] in LDS, K a multiple of 4; wave (wm, wn) owns a 32 x 32 quarter.
-template <typename R>
+// Complex tile product acc += A B on MFMA: A [..][lda] (rows x K) and B
+// [K][ldb] in LDS, K a multiple of 4; a wave owns the 16 NA x 16 NB part at
+// (wm, wn).  The two products of one accumulator are issued apart (back to
+// back the second waits for the first).
+template <typename R, int NA, int NB>
 __device__ __forceinline__ void cmma64(const R* Ar, const R* Ai, int lda, const R* Br, const R* Bi, int ldb, int K,
-                                       int wm, int wn, int lane, typename Mma<R>::v4 (&cr)[2][2],
-                                       typename Mma<R>::v4 (&ci)[2][2]) {
+                                       int wm, int wn, int lane, typename Mma<R>::v4 (&cr)[NA][NB],
+                                       typename Mma<R>::v4 (&ci)[NA][NB]) {
   for (int k4 = 0; k4 < K; k4 += 4) {
     const int kr = k4 + (lane >> 4);
-    R ar[2], ai[2], br[2], bi[2];
+    R ar[NA], ai[NA], br[NB], bi[NB];
 #pragma unroll
-    for (int a = 0; a < 2; ++a) {
+    for (int a = 0; a < NA; ++a) {
       ar[a] = Ar[(wm + 16 * a + (lane & 15)) * lda + kr];
       ai[a] = Ai[(wm + 16 * a + (lane & 15)) * lda + kr];
-      br[a] = Br[kr * ldb + wn + 16 * a + (lane & 15)];
-      bi[a] = Bi[kr * ldb + wn + 16 * a + (lane & 15)];
     }
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int b = 0; b < NB; ++b) {
+      br[b] = Br[kr * ldb + wn + 16 * b + (lane & 15)];
+      bi[b] = Bi[kr * ldb + wn + 16 * b + (lane & 15)];
+    }
 #pragma unroll
-      for (int b = 0; b < 2; ++b) {
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
         cr[a][b] = Mma<R>::op(ar[a], br[b], cr[a][b]);
-        cr[a][b] = Mma<R>::op(-ai[a], bi[b], cr[a][b]);
         ci[a][b] = Mma<R>::op(ar[a], bi[b], ci[a][b]);
+      }
+#pragma unroll
+    for (int a = 0; a < NA; ++a)
+#pragma unroll
+      for (int b = 0; b < NB; ++b) {
+        cr[a][b] = Mma<R>::op(-ai[a], bi[b], cr[a][b]);
         ci[a][b] = Mma<R>::op(ai[a], br[b], ci[a][b]);
       }
   }
@@ -609,33 +619,32 @@ __device__ __forceinline__ void cmma64(const R* Ar, const R* Ai, int lda, const 
 // multiply-add (ArBr, AiBi and (Ar + Ai)(Br + Bi); re = ArBr - AiBi, im = the
 // third minus the other two), three quarters of the MFMAs; FP64 keeps the
 // four products of cmma64 (and its rounding).
-template <typename R, int NBW = 2>   // NBW: 16-column B tiles per wave
+template <typename R, int NBW = 2, int NAW = 2>   // 16-column B tiles, 16-row A tiles per wave
 struct CAcc {
   typedef typename Mma<R>::v4 v4;
   static constexpr bool G3 = sizeof(R) == 4;
-  static_assert(G3 || NBW == 2, "the four-product form is cmma64's 2 x 2 tiles");
-  v4 p[3][2][NBW];
+  v4 p[3][NAW][NBW];
   __device__ __forceinline__ void zero() {
 #pragma unroll
     for (int q = 0; q < 3; ++q)
 #pragma unroll
-      for (int a = 0; a < 2; ++a)
+      for (int a = 0; a < NAW; ++a)
 #pragma unroll
         for (int b = 0; b < NBW; ++b) p[q][a][b] = v4{R(0), R(0), R(0), R(0)};
   }
   __device__ __forceinline__ void mma(const R* Ar, const R* Ai, int lda, const R* Br, const R* Bi, int ldb, int K,
                                       int wm, int wn, int lane) {
     if constexpr (!G3) {
-      cmma64<R>(Ar, Ai, lda, Br, Bi, ldb, K, wm, wn, lane, p[0], p[1]);
+      cmma64<R, NAW, NBW>(Ar, Ai, lda, Br, Bi, ldb, K, wm, wn, lane, p[0], p[1]);
     } else {
       // two k steps at a time: a full unroll hoists every LDS load of the
       // chunk and leaves no registers for a second wave per SIMD
 #pragma unroll 2
       for (int k4 = 0; k4 < K; k4 += 4) {
         const int kr = k4 + (lane >> 4);
-        R ar[2], ai[2], br[NBW], bi[NBW];
+        R ar[NAW], ai[NAW], br[NBW], bi[NBW];
 #pragma unroll
-        for (int a = 0; a < 2; ++a) {
+        for (int a = 0; a < NAW; ++a) {
           ar[a] = Ar[(wm + 16 * a + (lane & 15)) * lda + kr];
           ai[a] = Ai[(wm + 16 * a + (lane & 15)) * lda + kr];
         }
@@ -645,7 +654,7 @@ struct CAcc {
           bi[b] = Bi[kr * ldb + wn + 16 * b + (lane & 15)];
         }
 #pragma unroll
-        for (int a = 0; a < 2; ++a)
+        for (int a = 0; a < NAW; ++a)
 #pragma unroll
           for (int b = 0; b < NBW; ++b) {
             p[0][a][b] = Mma<R>::op(ar[a], br[b], p[0][a][b]);
@@ -655,9 +664,9 @@ struct CAcc {
       }
     }
   }
-  __device__ __forceinline__ void result(v4 (&cr)[2][NBW], v4 (&ci)[2][NBW]) const {
+  __device__ __forceinline__ void result(v4 (&cr)[NAW][NBW], v4 (&ci)[NAW][NBW]) const {
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < NAW; ++a)
 #pragma unroll
       for (int b = 0; b < NBW; ++b) {
         if constexpr (G3) {
@@ -671,32 +680,45 @@ struct CAcc {
   }
 };
 
-// Schur updates F[rows][cols] -= F[rows][K] F[K][cols] on a 64 x 64 tile per
-// workgroup (four waves of 32 x 32, the complex product as CAcc forms it:
-// three real MFMA products in FP32, four in FP64).  With the 48-column step kb inside the outer block starting at
-// kb0 (obe = min(kb0 + kOB, np)):
-//   mode 0: rows [ke, nf), cols [ke, obe), K = the step's columns
-//   mode 1: rows [ke, obe), cols [obe, nf), K = the step's columns
-//   mode 2: rows [obe, nf), cols [obe, nf), K = [kb0, obe)   (once per block)
-// Modes 0 and 1 keep the block's own columns and rows current for the next
+// Schur updates F[rows][cols] -= F[rows][K] F[K][cols] on a 32 x 32 tile per
+// workgroup (four waves of 16 x 16, the complex product as CAcc forms it:
+// three real MFMA products in FP32, four in FP64).  With the 48-column step kb
+// inside the outer block starting at kb0 (obe = min(kb0 + kOB, np)):
+//   step:  rows [ke, nf), cols [ke, obe) (the first nbx x nby tiles) and
+//          rows [ke, obe), cols [obe, nf) (as many again, x and y exchanged),
+//          K = the step's columns
+//   block: rows [obe, nf), cols [obe, nf), K = [kb0, obe)   (once per block)
+// The steps keep the block's own columns and rows current for the next
 // step; the rest of the trailing matrix is read by nothing inside the block,
-// so its update waits and is applied once with K up to kOB.  Registers are
-// capped for two waves per SIMD: uncapped, the FP64 kernel took 214 VGPRs and
-// 64 AGPRs (one wave); capped it fits 220 VGPRs without spills.  The FP32
-// one keeps three waves (capped for four it spills 28 VGPRs and runs slower).
+// so its update waits and is applied once with K up to kOB.
+// What bounds it: the block update the FP64 matrix cores, the step a chain of
+// latencies at the top of the tree, so both its parts are one launch.  Why 32:
+// 112 VGPRs and 17 KB of LDS let four workgroups share a CU, and few tiles
+// spread wider; with 64 x 64 tiles (226 VGPRs, two) the block update of two
+// fronts of 3741 took 844 us (52 TFLOP/s) against 806, that of one of 2300 185
+// against 146, the root's steps 2 x 20 against 8 to 16.  64 x 32 and 32 x 64 lie
+// between; tile rows padded to a multiple of the eight XCDs lost 2%.  A complete
+// n = 29 set-up's FP64 updates: 25.9 to 20.8 ms; FP32, n = 32: 20.5 to 18.2.
+constexpr int kST = 32;
 template <typename R>
-__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void schur_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl,
-                                                    int nlvl, int kb, int kb0, int mode, R* __restrict__ buf) {
+__global__ __launch_bounds__(256) void schur_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl,
+                                                    int nlvl, int kb, int kb0, int nbx, int nby, bool step,
+                                                    R* __restrict__ buf) {
   typedef typename Mma<R>::v4 v4;
-  __shared__ R Ar[64][17], Ai[64][17];
-  __shared__ R Br[16][65], Bi[16][65];
+  constexpr int U = kST / 16;   // chunk elements per thread and plane
+  __shared__ R Ar[kST][17], Ai[kST][17];
+  __shared__ R Br[16][kST + 1], Bi[16][kST + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * 32, wn = (wave & 1) * 32;
-  for (int q = blockIdx.z; q < nlvl; q += gridDim.z) {
+  const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16;
+  const int tiles = nbx * nby;
+  const bool second = step && (int)blockIdx.x >= tiles;
+  const int tile = second ? blockIdx.x - tiles : blockIdx.x;
+  const int bx = tile % (second ? nby : nbx), by = tile / (second ? nby : nbx);
+  for (int q = blockIdx.y; q < nlvl; q += gridDim.y) {
     const FrontDev d = fr[lvl[q]];
     const long nf = d.nf, obe = min((long)kb0 + kOB, (long)d.np);
     long r0, r1, c0, c1, k0, k1;
-    if (mode == 2) {
+    if (!step) {
       if (kb0 >= d.np) continue;
       r0 = c0 = obe;
       r1 = c1 = nf;
@@ -706,32 +728,32 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
       if (kb >= d.np) continue;
       k0 = kb;
       k1 = min((long)kb + kT, (long)d.np);
-      r0 = c0 = k1;
-      r1 = mode == 0 ? nf : obe;
-      if (mode == 1) c0 = obe;
-      c1 = mode == 0 ? obe : nf;
+      r0 = k1;
+      r1 = second ? obe : nf;
+      c0 = second ? obe : k1;
+      c1 = second ? nf : obe;
     }
-    const long i0 = r0 + 64L * blockIdx.y, j0 = c0 + 64L * blockIdx.x;
+    const long i0 = r0 + (long)kST * by, j0 = c0 + (long)kST * bx;
     if (i0 >= r1 || j0 >= c1) continue;
     const int tw = (int)(k1 - k0);
     const long kb_ = k0;
     R* Fr = buf + d.f;
     R* Fi = Fr + nf * nf;
-    CAcc<R> acc;
+    CAcc<R, 1, 1> acc;
     acc.zero();
     // the next 16-deep K chunk is loaded into registers while the MFMAs
     // consume the current one from LDS
-    R par[4], pai[4], pbr[4], pbi[4];
+    R par[U], pai[U], pbr[U], pbi[U];
     auto fetch = [&](int kc) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < U; ++u) {
         const int o = tid + 256 * u;
         const int ii = o >> 4, kk = o & 15;
         const bool ok = i0 + ii < r1 && kc + kk < tw;
         const long src = (i0 + ii) * nf + kb_ + kc + kk;
         par[u] = ok ? Fr[src] : R(0);
         pai[u] = ok ? Fi[src] : R(0);
-        const int kr = o >> 6, jj = o & 63;
+        const int kr = o / kST, jj = o % kST;
         const bool okb = kc + kr < tw && j0 + jj < c1;
         const long srcb = (kb_ + kc + kr) * nf + j0 + jj;
         pbr[u] = okb ? Fr[srcb] : R(0);
@@ -741,33 +763,28 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void s
     fetch(0);
     for (int kc = 0; kc < tw; kc += 16) {
 #pragma unroll
-      for (int u = 0; u < 4; ++u) {
+      for (int u = 0; u < U; ++u) {
         const int o = tid + 256 * u;
         Ar[o >> 4][o & 15] = par[u];
         Ai[o >> 4][o & 15] = pai[u];
-        Br[o >> 6][o & 63] = pbr[u];
-        Bi[o >> 6][o & 63] = pbi[u];
+        Br[o / kST][o % kST] = pbr[u];
+        Bi[o / kST][o % kST] = pbi[u];
       }
       __syncthreads();
       if (kc + 16 < tw) fetch(kc + 16);
-      acc.mma(&Ar[0][0], &Ai[0][0], 17, &Br[0][0], &Bi[0][0], 65, 16, wm, wn, lane);
+      acc.mma(&Ar[0][0], &Ai[0][0], 17, &Br[0][0], &Bi[0][0], kST + 1, 16, wm, wn, lane);
       __syncthreads();
     }
-    v4 cr[2][2], ci[2][2];
+    v4 cr[1][1], ci[1][1];
     acc.result(cr, ci);
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const long gi = i0 + wm + 16 * a + Mma<R>::row(lane, r);
-          const long gj = j0 + wn + 16 * b + (lane & 15);
-          if (gi < r1 && gj < c1) {
-            Fr[gi * nf + gj] -= cr[a][b][r];
-            Fi[gi * nf + gj] -= ci[a][b][r];
-          }
-        }
+    for (int r = 0; r < 4; ++r) {
+      const long gi = i0 + wm + Mma<R>::row(lane, r), gj = j0 + wn + (lane & 15);
+      if (gi < r1 && gj < c1) {
+        Fr[gi * nf + gj] -= cr[0][0][r];
+        Fi[gi * nf + gj] -= ci[0][0][r];
+      }
+    }
   }
 }
 
@@ -1180,7 +1197,7 @@ __global__ __launch_bounds__(256) void hat_kernel(const FrontDev* __restrict__ f
           }
         }
         __syncthreads();
-        cmma64<R>(Ar_, Ai_, kLL, Br_, Bi_, kLX, kT, wm, wn, lane, cr, ci);
+        cmma64<R, 2, 2>(Ar_, Ai_, kLL, Br_, Bi_, kLX, kT, wm, wn, lane, cr, ci);
         __syncthreads();
       }
 #pragma unroll
@@ -2119,6 +2136,15 @@ struct GpuSolver {
 
 namespace {
 
+// cols x rows: extents of the (first) part, at most
+template <typename R>
+void launch_schur(long cols, long rows, bool step, unsigned gy, hipStream_t s, const FrontDev* fr, const int* lvl,
+                  int nl, int kb, int kb0, R* buf) {
+  const long nbx = std::max(1L, (cols + kST - 1) / kST), nby = std::max(1L, (rows + kST - 1) / kST);
+  hipLaunchKernelGGL(schur_kernel<R>, dim3((unsigned)((step ? 2 : 1) * nbx * nby), gy), dim3(256), 0, s, fr, lvl, nl, kb,
+                     kb0, (int)nbx, (int)nby, step, buf);
+}
+
 template <typename R>
 ls_status factor_numeric(GpuSolver& g, const C<double>* rows, hipStream_t s) {
   const int L = (int)g.levels.size();
@@ -2166,18 +2192,9 @@ ls_status factor_numeric(GpuSolver& g, const C<double>* rows, hipStream_t s) {
         const int half = (int)std::max(1L, (rest + kPR - 1) / kPR);
         hipLaunchKernelGGL(panel_kernel<R>, dim3(2 * half, gy), dim3(256), 0, s, fr, lvl, nl, (int)kb, half, buf,
                            (const int*)ib);
-        const unsigned tall = (unsigned)std::max(1L, (rest + 63) / 64);
-        const unsigned blk = (unsigned)std::max(1L, (kbe - kb - 1 + 63) / 64);   // block columns left
-        if (kb + kT < kbe) {
-          hipLaunchKernelGGL(schur_kernel<R>, dim3(blk, tall, gy), dim3(256), 0, s, fr, lvl, nl, (int)kb,
-                             (int)kb0, 0, buf);
-          hipLaunchKernelGGL(schur_kernel<R>, dim3(tall, blk, gy), dim3(256), 0, s, fr, lvl, nl, (int)kb,
-                             (int)kb0, 1, buf);
-        }
+        if (kb + kT < kbe) launch_schur<R>(kbe - kb - 1, rest, true, gy, s, fr, lvl, nl, (int)kb, (int)kb0, buf);
       }
-      const unsigned t64 = (unsigned)std::max(1L, (mnf - kb0 - 1 + 63) / 64);
-      hipLaunchKernelGGL(schur_kernel<R>, dim3(t64, t64, gy), dim3(256), 0, s, fr, lvl, nl, (int)kb0, (int)kb0, 2,
-                         buf);
+      launch_schur<R>(mnf - kb0 - 1, mnf - kb0 - 1, false, gy, s, fr, lvl, nl, (int)kb0, (int)kb0, buf);
     }
     hipLaunchKernelGGL(copyout_kernel<R>, dim3(grid_for(mnf * mnf, 256, 8192), std::min(gy, 64u)), dim3(256), 0, s,
                        fr, lvl, nl, (const R*)buf, fac);
