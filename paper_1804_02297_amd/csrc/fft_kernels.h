@@ -223,6 +223,19 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
   // registers already did.
   constexpr bool SPLIT3 = (N1 % 2 == 0);
   constexpr bool SIGNED = SPLIT3;
+  // Where a job has twice as many lanes as columns (P = 96, 128, 384), two
+  // adjacent lanes share a column's length-N2 DFT by one radix-2 step, M =
+  // N2 / 2, instead of every second lane idling:
+  //   forward (inputs k < M nonzero since n <= P/2), lane h: the outputs 2 q' + h
+  //     = DFT_M(x_k W_N2^{kh})[q'], both lanes reading the same inputs
+  //   inverse, lane h: the outputs t1 = 2 t' + h = DFT_M^-1((Y[q'] + (-1)^h Y[q' + M])
+  //     W_N2^{-q'h})[t'], of which t1 < M are kept
+  // VALU issue bounds this pass; before and after: complex64 n = 64, 16 rhs 300
+  // to 243 us (whole apply 635 to 603), n = 150, 2 rhs 1237 to 1135 us (2453 to
+  // 2337); complex128 n = 59 one rhs whole apply 103 to 99 us, n = 48, 16 rhs 506
+  // to 486 us.
+  constexpr bool PAIR = WAVE_TEAM && N2 % 4 == 0 && 2 * N1 <= JL;
+  constexpr int M = N2 / 2;
   __shared__ C<R> ke[3 * H];                    // xx, yy, zz
   __shared__ C<R> ko[(SIGNED ? 4 : 1) * 3 * H]; // xy, xz, yz (per line when SIGNED)
   __shared__ C<R> twl[P];
@@ -277,6 +290,13 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
     };
 
     constexpr int KIN = (N2 + 1) / 2;     // t = j + N1 k < n <= P/2
+    const int col = j >> 1, h = j & 1;    // PAIR: column and half
+    const bool pair = active && j < 2 * N1;
+    const R sg = h ? (R)-1 : (R)1;
+    C<R> wh[PAIR ? M : 1];                // W_N2^{kh}
+    if constexpr (PAIR)
+#pragma unroll
+      for (int k = 1; k < M; ++k) wh[k] = twl[h ? k * N1 : 0];
     for (int b = team; b < B; b += W) {
       C<R>* base = X + (long)b * 3 * plane + lineoff;
       // FP32 at P = 256: all loads of the three components are issued before
@@ -307,7 +327,20 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
 #pragma unroll
       for (int c = 0; c < 3; ++c) {
         // forward step 1: thread j < N1 owns t = j + N1 k
-        if (active && j < N1) {
+        if constexpr (PAIR) {
+          if (pair) {
+            C<R> v[M];
+#pragma unroll
+            for (int k = 0; k < M; ++k) {
+              const int tt = col + N1 * k;
+              const C<R> x = (tt < n) ? ld_stream(base + c * plane + tt) : cmk<R>(0, 0);
+              v[k] = k == 0 ? x : x * wh[k];
+            }
+            Dft<M, -1, R>::run(v);
+#pragma unroll
+            for (int q = 0; q < M; ++q) myex[(2 * q + h) * (N1 + 1) + col] = v[q] * twl[col * (2 * q + h)];
+          }
+        } else if (active && j < N1) {
           C<R> v[N2];
 #pragma unroll
           for (int k = 0; k < KIN; ++k) {
@@ -381,7 +414,23 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
         }
         tsync();
         // inverse step 3': thread t2 = j < N1 produces t = j + N1 t1
-        if (active && j < N1) {
+        if constexpr (PAIR) {
+          if (pair) {
+            C<R> v[M];
+#pragma unroll
+            for (int q = 0; q < M; ++q) {
+              const C<R> a = myex[q * (N1 + 1) + col], bb = myex[(q + M) * (N1 + 1) + col];
+              const C<R> d = cmk(a.re + sg * bb.re, a.im + sg * bb.im);
+              v[q] = q == 0 ? d : d * cconj(wh[q]);
+            }
+            Dft<M, 1, R>::run(v);
+#pragma unroll
+            for (int t1 = 0; t1 < M / 2; ++t1) {
+              const int tt = col + N1 * (2 * t1 + h);
+              if (tt < n) st_stream(base + c * plane + tt, v[t1]);
+            }
+          }
+        } else if (active && j < N1) {
           C<R> v[N2];
 #pragma unroll
           for (int q = 0; q < N2; ++q) v[q] = myex[q * (N1 + 1) + j];

@@ -207,3 +207,21 @@ def test_apply_short_transforms(lib, n, nrhs, form):
     plan.apply(xi, xi)                     # in place
     assert torch.equal(xi, y)
     plan.close()
+
+
+@pytest.mark.parametrize("n,nrhs", [(48, 1), (48, 4), (49, 3), (63, 1), (64, 5)])
+def test_apply_paired_lanes(lib, n, nrhs):
+    """Transform lengths whose pass 3 gives two lanes to a column (P = 96 and
+    128), at their smallest and largest n, one to several teams a workgroup, in
+    every precision (P = 384 is the n = 192 case above)."""
+    from paper_1804_02297_amd.binding import Plan
+    k = I.wavenumber_for(n)
+    m = I.medium_bumps(n, 3)
+    x = I.random_field(nrhs, n, 900 + n)
+    ref = op.apply_fft(n, k, m, x)
+    plan = Plan(n, k, _dev(m), max_rhs=nrhs)
+    print(f"n={n} nrhs={nrhs}", flush=True)
+    assert _rel(plan.apply(_dev(x)).cpu().numpy(), ref) <= 1e-12
+    assert _rel(plan.apply(_dev(x), prec="mixed").cpu().numpy(), ref) <= 1e-5
+    assert _rel(plan.apply(_dev(x.astype(np.complex64)), prec="c64").cpu().numpy(), ref) <= 1e-5
+    plan.close()
