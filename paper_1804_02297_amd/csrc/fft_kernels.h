@@ -788,7 +788,8 @@ __global__ __launch_bounds__(4 * cmax(N1, N2)) void kmul34_kernel(C<R>* __restri
 // in registers.  RS = 8 mod 16 spreads the rows over the banks.  In the column
 // steps neighbouring threads take neighbouring columns; a row is worked on by
 // JL lanes of one wave.  The symbol is read from the caches (its octant is at
-// most 3.4 MB in FP64 at P = 64).  Above the LDS limit (P > 64; P > 96 in FP32)
+// most 3.4 MB in FP64 at P = 64).  Above P = 64 (the LDS limit in FP64; at P = 96 in
+// FP32, one workgroup per CU, it gained 6% for 16 rhs and lost 17% for one)
 // the separate passes run.  Whole apply, complex128, against the three passes:
 // n = 16 one rhs 22.4 -> 17.4 us (three launches instead of five), 16 rhs
 // 102 -> 24 us; n = 32 16 rhs 210 -> 111 us (complex64 138 -> 60).
@@ -804,7 +805,7 @@ struct PlaneCfg {
   static constexpr int CPB = NT / TPL;                       // columns per batch of the dim-2 steps
   static constexpr int W = cmax(NF * P / 2, P + f.n2);
   static constexpr int RS = (W + 7) / 16 * 16 + 8;
-  static constexpr bool FITS = TPL <= 16 && (P * RS + P) * 2 * (int)sizeof(R) <= 160 * 1024;
+  static constexpr bool FITS = P <= 64 && (P * RS + P) * 2 * (int)sizeof(R) <= 160 * 1024;
 };
 
 template <typename R, int P, int NF>
@@ -1114,15 +1115,6 @@ static ls_status launch_kmul(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int
   return launch_kmul_w<R, P, 1>(X, Kh, tw, n, ld, B, persist, s);
 }
 
-// Whether passes 2 to 4 run as one plane_kernel launch.  At P = 96 (FP32, one
-// workgroup per CU, three rounds of rows) only from eight right-hand sides on:
-// n = 48 16 rhs 265 us against 314 with three passes, 4 rhs 88 both, n = 40 one
-// rhs 42 against 36.
-template <typename R, int P, int NF>
-constexpr bool use_plane(int nrhs) {
-  return PlaneCfg<R, P, NF>::FITS && (P <= 64 || nrhs >= 8);
-}
-
 // Passes 2 to 4 as one plane_kernel launch: X1 rows of in_rs in, Y1 [3B][P][n][out_ld] out.
 template <typename R, int P, int NF>
 static ls_status launch_plane(const C<R>* X, C<R>* Y, const C<R>* Kh, const C<R>* tw, int n, int B, long in_rs,
@@ -1177,11 +1169,11 @@ static ls_status run_passes(ApplyPlan& ap, const void* x, void* y, int nrhs, con
                                           nb, (R)1, s)));
   LS_MARK(1);
   C<R>* Y1 = X1;
-  if (use_plane<R, P, 3>(nrhs)) {
+  if constexpr (PlaneCfg<R, P, 3>::FITS) {
     // passes 2 to 4 (timed as pass 3), in place when the rows of X1 and Y1 are alike
     if (r1 != w1) Y1 = X2;
     LS_MARK(2);
-    if constexpr (PlaneCfg<R, P, 3>::FITS) LS_TRY((launch_plane<R, P, 3>(X1, Y1, kh, tw, n, nrhs, r1, ld, s)));
+    LS_TRY((launch_plane<R, P, 3>(X1, Y1, kh, tw, n, nrhs, r1, ld, s)));
     LS_MARK(3);
     LS_MARK(4);
   } else {
@@ -1230,10 +1222,10 @@ static ls_status run_passes34(ApplyPlan& ap, const void* x, void* y, int nrhs, c
                                        (R)1, s)));
   LS_MARK(1);
   C<R>* Y1 = X1;
-  if (use_plane<R, P, 4>(nrhs)) {
+  if constexpr (PlaneCfg<R, P, 4>::FITS) {
     if (r1 != w1) Y1 = X2;
     LS_MARK(2);
-    if constexpr (PlaneCfg<R, P, 4>::FITS) LS_TRY((launch_plane<R, P, 4>(X1, Y1, kp, tw, n, nrhs, r1, ld, s)));
+    LS_TRY((launch_plane<R, P, 4>(X1, Y1, kp, tw, n, nrhs, r1, ld, s)));
     LS_MARK(3);
     LS_MARK(4);
   } else {

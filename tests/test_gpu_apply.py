@@ -184,7 +184,7 @@ def test_apply_with_padded_workspace_rows(lib, n, form):
                                     (32, 2), (33, 8), (48, 8), (48, 3)])
 def test_apply_short_transforms(lib, n, nrhs, form):
     """Transform lengths whose dim-2 and dim-3 passes run as one kernel per
-    plane (P = 8 to 64; 96 in FP32 from eight rhs on), at the smallest and
+    plane (P = 8 to 64; above, P = 96 and three passes), at the smallest and
     largest n of each length, every precision, both forms; and the timed call,
     which runs the same kernels."""
     from oracle import paper_form as pf
