@@ -176,6 +176,9 @@ __global__ __launch_bounds__(T * cmax(N1, N2)) void col_fft_kernel(
 // ---- pass 3: contiguous-dimension FFT, 3x3 Khat multiply, inverse -----------
 // X: [B][3][P][P][ld] (q1, q2, i3; ld >= n).  Kh: octant [H][H][6][H], components
 // (xx, yy, zz, xy, xz, yz), already divided by P^3.
+// NF = 4, the paper's form: four fields (m x_1, m x_2, m x_3 at 3 b + c, p.x at
+// 3 B + b), Kh [H][H][4][H] (k^2 Ghat, G^1, G^2, G^3), v_c = k^2 Ghat u_c + G^c what
+// into 3 b + c.  k^2 G is even in every coordinate, G^d odd in coordinate d.
 //
 // A team is 4 jobs x JL threads: the up-to-four lines (+-f1, +-f2) of one
 // right-hand side, JL = TPL (the larger factor of P) or, for 8 < TPL <= 32,
@@ -197,7 +200,7 @@ __device__ __forceinline__ void wave_lds_sync() {
   __builtin_amdgcn_wave_barrier();
 }
 
-template <typename R, int P, int N1, int N2, int W, bool PERSIST = false>
+template <typename R, int P, int N1, int N2, int W, int NF, bool PERSIST = false>
 __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C<R>* __restrict__ X,
                                                                                const C<R>* __restrict__ Kh,
                                                                                const C<R>* __restrict__ tw,
@@ -236,7 +239,7 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
   // to 486 us.
   constexpr bool PAIR = WAVE_TEAM && N2 % 4 == 0 && 2 * N1 <= JL;
   constexpr int M = N2 / 2;
-  __shared__ C<R> ke[3 * H];                    // xx, yy, zz
+  __shared__ C<R> ke[3 * H];                    // xx, yy, zz; NF = 4: k^2 Ghat in the first H
   __shared__ C<R> ko[(SIGNED ? 4 : 1) * 3 * H]; // xy, xz, yz (per line when SIGNED)
   __shared__ C<R> twl[P];
   __shared__ C<R> ex[W * 4 * EXS];
@@ -257,16 +260,18 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
     const long plane = (long)P * P * ld;        // one component of one rhs
     const long lineoff = ((long)q1 * P + q2) * ld;
 
-    const C<R>* kg = Kh + ((long)f1 * H + f2) * 6 * H;
+    constexpr int NC = NF == 3 ? 6 : 4;         // symbol components
+    const C<R>* kg = Kh + ((long)f1 * H + f2) * NC * H;
     for (int e = tid; e < 3 * H; e += W * TEAM) {
-      ke[e] = kg[e];
-      const C<R> o = kg[3 * H + e];
+      if (NF == 3 || e < H) ke[e] = kg[e];
+      const C<R> o = kg[(NC - 3) * H + e];
       if constexpr (SIGNED) {
-        const int comp = e / H;                 // 0 xy, 1 xz, 2 yz
+        const int comp = e / H;                 // 0 xy, 1 xz, 2 yz; NF = 4: G^1, G^2, G^3
 #pragma unroll
         for (int l = 0; l < 4; ++l) {
           const bool m1 = l & 1, m2 = l >> 1;
-          const bool neg = (comp == 0) ? (m1 != m2) : (comp == 1 ? m1 : m2);
+          const bool neg = NF == 4 ? (comp == 0 ? m1 : comp == 1 && m2)
+                                   : (comp == 0) ? (m1 != m2) : (comp == 1 ? m1 : m2);
           ko[l * 3 * H + e] = neg ? cmk<R>(-o.re, -o.im) : o;
         }
       } else {
@@ -293,39 +298,43 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
     const int col = j >> 1, h = j & 1;    // PAIR: column and half
     const bool pair = active && j < 2 * N1;
     const R sg = h ? (R)-1 : (R)1;
-    C<R> wh[PAIR ? M : 1];                // W_N2^{kh}
-    if constexpr (PAIR)
+    // W_N2^{kh}, in registers (but for four FP64 fields, whose values fill two waves' registers)
+    constexpr bool WREG = PAIR && !(NF == 4 && sizeof(R) == 8);
+    C<R> wreg[WREG ? M : 1];
+    if constexpr (WREG)
 #pragma unroll
-      for (int k = 1; k < M; ++k) wh[k] = twl[h ? k * N1 : 0];
+      for (int k = 1; k < M; ++k) wreg[k] = twl[h ? k * N1 : 0];
+    const auto wh = [&](int k) { return WREG ? wreg[WREG ? k : 0] : twl[h ? k * N1 : 0]; };
     for (int b = team; b < B; b += W) {
-      C<R>* base = X + (long)b * 3 * plane + lineoff;
+      // the fields of rhs b: 3 b + c, and at NF = 4 field 3 B + b
+      const auto base = [&](int c) { return X + (c < 3 ? (long)b * 3 + c : (long)B * 3 + b) * plane + lineoff; };
       // FP32 at P = 256: all loads of the three components are issued before
       // any arithmetic.  Without the prefetch registers the kernel fits more
       // waves per SIMD, which wins elsewhere (P = 128, 16 rhs: 0.33 against
       // 0.41 ms, three waves; P = 384: 5.6 against 10.4 ms, two waves instead
       // of one); at P = 256 it still fits only two, and the prefetch wins (1.05
       // against 1.12 ms).  FP64 has no registers to spare for it.
-      constexpr bool PREFETCH = sizeof(R) == 4 && P == 256;
-      C<R> pre[3][KIN];
+      constexpr bool PREFETCH = sizeof(R) == 4 && P == 256 && NF == 3;
+      C<R> pre[NF][KIN];
       if (PREFETCH && active && j < N1) {
         if (2 * n == P) {     // every t = j + N1 k < P/2 is a grid point: no bounds, no zero fill
 #pragma unroll
-          for (int c = 0; c < 3; ++c)
+          for (int c = 0; c < NF; ++c)
 #pragma unroll
-            for (int k = 0; k < KIN; ++k) pre[c][k] = ld_stream(base + c * plane + j + N1 * k);
+            for (int k = 0; k < KIN; ++k) pre[c][k] = ld_stream(base(c) + j + N1 * k);
         } else {
 #pragma unroll
-          for (int c = 0; c < 3; ++c)
+          for (int c = 0; c < NF; ++c)
 #pragma unroll
             for (int k = 0; k < KIN; ++k) {
               const int tt = j + N1 * k;
-              pre[c][k] = (tt < n) ? ld_stream(base + c * plane + tt) : cmk<R>(0, 0);
+              pre[c][k] = (tt < n) ? ld_stream(base(c) + tt) : cmk<R>(0, 0);
             }
         }
       }
-      C<R> u[3][N1];
+      C<R> u[NF][N1];
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
+      for (int c = 0; c < NF; ++c) {
         // forward step 1: thread j < N1 owns t = j + N1 k
         if constexpr (PAIR) {
           if (pair) {
@@ -333,8 +342,8 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
 #pragma unroll
             for (int k = 0; k < M; ++k) {
               const int tt = col + N1 * k;
-              const C<R> x = (tt < n) ? ld_stream(base + c * plane + tt) : cmk<R>(0, 0);
-              v[k] = k == 0 ? x : x * wh[k];
+              const C<R> x = (tt < n) ? ld_stream(base(c) + tt) : cmk<R>(0, 0);
+              v[k] = k == 0 ? x : x * wh(k);
             }
             Dft<M, -1, R>::run(v);
 #pragma unroll
@@ -345,7 +354,7 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
 #pragma unroll
           for (int k = 0; k < KIN; ++k) {
             const int tt = j + N1 * k;
-            v[k] = PREFETCH ? pre[c][k] : ((tt < n) ? ld_stream(base + c * plane + tt) : cmk<R>(0, 0));
+            v[k] = PREFETCH ? pre[c][k] : ((tt < n) ? ld_stream(base(c) + tt) : cmk<R>(0, 0));
           }
           DftZ<N2, -1, R, KIN>::run(v);
           // twl[0] = 1 exactly, so lane j = 0 needs no exception
@@ -364,6 +373,22 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
       if (active && j < N2) {
 #pragma unroll
         for (int a = 0; a < N1; ++a) {
+          if constexpr (NF == 4) {
+            const int q3 = N2 * a + j;
+            const bool hi = SPLIT3 ? 2 * a >= N1 : 2 * q3 > P;
+            const int f3 = hi ? P - q3 : q3;
+            const C<R> g0 = ke[f3], g3 = kol[2 * H + f3], w = u[NF - 1][a];
+            C<R> g1 = kol[f3], g2 = kol[H + f3];
+            if (!SIGNED) {
+              g1 = cscale(g1, sx);
+              g2 = cscale(g2, sy);
+            }
+            u[0][a] = cfma(g1, w, g0 * u[0][a]);
+            u[1][a] = cfma(g2, w, g0 * u[1][a]);
+            u[2][a] = cfma(hi ? cmk<R>(-g3.re, -g3.im) : g3, w, g0 * u[2][a]);
+            if ((a & 3) == 3) asm volatile("" ::: "memory");   // bound the LDS prefetch depth
+            continue;
+          }
           C<R> kxx, kyy, kzz, kxy, kxz, kyz;
           if constexpr (SPLIT3) {
             const bool hi = 2 * a >= N1;                       // q3 >= P/2
@@ -421,13 +446,13 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
             for (int q = 0; q < M; ++q) {
               const C<R> a = myex[q * (N1 + 1) + col], bb = myex[(q + M) * (N1 + 1) + col];
               const C<R> d = cmk(a.re + sg * bb.re, a.im + sg * bb.im);
-              v[q] = q == 0 ? d : d * cconj(wh[q]);
+              v[q] = q == 0 ? d : d * cconj(wh(q));
             }
             Dft<M, 1, R>::run(v);
 #pragma unroll
             for (int t1 = 0; t1 < M / 2; ++t1) {
               const int tt = col + N1 * (2 * t1 + h);
-              if (tt < n) st_stream(base + c * plane + tt, v[t1]);
+              if (tt < n) st_stream(base(c) + tt, v[t1]);
             }
           }
         } else if (active && j < N1) {
@@ -438,7 +463,7 @@ __global__ __launch_bounds__(W * 4 * job_lanes(cmax(N1, N2))) void kmul_kernel(C
 #pragma unroll
           for (int t1 = 0; t1 < (N2 + 1) / 2; ++t1) {
             const int tt = j + N1 * t1;
-            if (tt < n) st_stream(base + c * plane + tt, v[t1]);
+            if (tt < n) st_stream(base(c) + tt, v[t1]);
           }
         }
         tsync();
@@ -484,12 +509,13 @@ __device__ __forceinline__ double pair_swap(double x) {
   return __longlong_as_double(((long long)hi << 32) | (unsigned int)lo);
 }
 
-template <typename R, int W, bool PERSIST = false>
+template <typename R, int W, int NF, bool PERSIST = false>
 __global__ __launch_bounds__(W * 128) void kmul2_kernel(C<R>* __restrict__ X, const C<R>* __restrict__ Kh,
                                                          const C<R>* __restrict__ tw, int n, int ld, int B) {
   constexpr int P = 256, N = 16, H = P / 2 + 1;
   constexpr int EXS = N * (N + 1);            // padded exchange of one job
-  __shared__ C<R> kl[6 * H];
+  constexpr int NC = NF == 3 ? 6 : 4;         // symbol components
+  __shared__ C<R> kl[NC * H];
   __shared__ C<R> twl[P];
   __shared__ C<R> ex[W * 4 * EXS];
   // a PERSIST launch (gridDim.x < H^2) takes octant lines grid-stride
@@ -510,8 +536,8 @@ __global__ __launch_bounds__(W * 128) void kmul2_kernel(C<R>* __restrict__ X, co
     const long plane = (long)P * P * ld;
     const long lineoff = ((long)q1 * P + q2) * ld;
 
-    const C<R>* kg = Kh + ((long)f1 * H + f2) * 6 * H;
-    for (int e = tid; e < 6 * H; e += W * 128) kl[e] = kg[e];
+    const C<R>* kg = Kh + ((long)f1 * H + f2) * NC * H;
+    for (int e = tid; e < NC * H; e += W * 128) kl[e] = kg[e];
     for (int e = tid; e < P; e += W * 128) twl[e] = tw[e];
     const R sxy = (s1 != s2) ? (R)-1 : (R)1;
     const R sx = s1 ? (R)-1 : (R)1;
@@ -526,16 +552,17 @@ __global__ __launch_bounds__(W * 128) void kmul2_kernel(C<R>* __restrict__ X, co
     auto hi = [&](C<R> z, int k) { const C<R> w = z * ctw<R, 16, 1>(k); return h ? w : z; };
 
     for (int b = team; b < B; b += W) {
-      C<R>* base = X + (long)b * 3 * plane + lineoff;
-      C<R> u[3][8];                             // frequencies col + 16 h + 32 s'
+      // the fields of rhs b: 3 b + c, and at NF = 4 field 3 B + b
+      const auto base = [&](int c) { return X + (c < 3 ? (long)b * 3 + c : (long)B * 3 + b) * plane + lineoff; };
+      C<R> u[NF][8];                            // frequencies col + 16 h + 32 s'
 #pragma unroll
-      for (int c = 0; c < 3; ++c) {
+      for (int c = 0; c < NF; ++c) {
         if (active) {
           C<R> v[8];
 #pragma unroll
           for (int k = 0; k < 8; ++k) {
             const int tt = col + N * k;
-            const C<R> x = (tt < n) ? ld_stream(base + c * plane + tt) : cmk<R>(0, 0);
+            const C<R> x = (tt < n) ? ld_stream(base(c) + tt) : cmk<R>(0, 0);
             v[k] = (k == 0) ? x : hf(x, k);
           }
           Dft<8, -1, R>::run(v);
@@ -567,6 +594,15 @@ __global__ __launch_bounds__(W * 128) void kmul2_kernel(C<R>* __restrict__ X, co
           const bool fl3 = 2 * q3 > P;
           const int f3 = fl3 ? P - q3 : q3;
           const R s3 = fl3 ? (R)-1 : (R)1;
+          if constexpr (NF == 4) {
+            const C<R> g0 = kl[f3], g1 = cscale(kl[H + f3], sx), g2 = cscale(kl[2 * H + f3], sy);
+            const C<R> g3 = cscale(kl[3 * H + f3], s3), w = u[NF - 1][ss];
+            u[0][ss] = cfma(g1, w, g0 * u[0][ss]);
+            u[1][ss] = cfma(g2, w, g0 * u[1][ss]);
+            u[2][ss] = cfma(g3, w, g0 * u[2][ss]);
+            if ((ss & 3) == 3) asm volatile("" ::: "memory");   // bound the LDS prefetch depth
+            continue;
+          }
           const C<R> kxx = kl[0 * H + f3], kyy = kl[1 * H + f3], kzz = kl[2 * H + f3];
           const C<R> kxy = cscale(kl[3 * H + f3], sxy);
           const C<R> kxz = cscale(kl[4 * H + f3], sx * s3);
@@ -609,7 +645,7 @@ __global__ __launch_bounds__(W * 128) void kmul2_kernel(C<R>* __restrict__ X, co
 #pragma unroll
           for (int t1 = 0; t1 < 4; ++t1) {
             const int tt = col + N * (2 * t1 + h);
-            if (tt < n) st_stream(base + c * plane + tt, v[t1]);
+            if (tt < n) st_stream(base(c) + tt, v[t1]);
           }
         }
         wave_lds_sync();
@@ -669,110 +705,6 @@ __global__ void pdot_kernel(const C<IO>* __restrict__ x, const C<R>* __restrict_
   const long b = id / n3, e = id % n3;
   const C<IO>* xb = x + b * 3 * n3;
   w[id] = p[e] * ccast<R>(xb[e]) + p[n3 + e] * ccast<R>(xb[n3 + e]) + p[2 * n3 + e] * ccast<R>(xb[2 * n3 + e]);
-}
-
-// Pass 3 of the paper's form: along dim 3 for each (q1, q2) line, the forward
-// transform of the four fields (m x_1, m x_2, m x_3 at fields 3b + c, p.x at
-// field 3B + b), v_c = k^2 Ghat u_c + G^c hat w, and the inverse transform of
-// the three v_c into fields 3b + c.  k^2 G is even in every coordinate, G^d
-// odd in coordinate d: a mirrored line flips the sign of G^1 (q1), G^2 (q2),
-// and a frequency past P/2 that of G^3.  One team of four jobs per workgroup.
-template <typename R, int P, int N1, int N2>
-__global__ __launch_bounds__(4 * cmax(N1, N2)) void kmul34_kernel(C<R>* __restrict__ X,
-                                                                  const C<R>* __restrict__ Kp,
-                                                                  const C<R>* __restrict__ tw, int n, int ld, int B) {
-  constexpr int H = P / 2 + 1;
-  constexpr int TPL = cmax(N1, N2);
-  constexpr int EXS = N1 * N2 + N2;
-  __shared__ C<R> kl[4 * H];
-  __shared__ C<R> twl[P];
-  __shared__ C<R> ex[4 * EXS];
-  const int f1 = blockIdx.x / H;
-  const int f2 = blockIdx.x % H;
-  const int tid = threadIdx.x;
-  const int job = tid / TPL;
-  const int j = tid % TPL;
-  const int s1 = job & 1, s2 = job >> 1;
-  const bool edge1 = (f1 == 0) || (2 * f1 == P);
-  const bool edge2 = (f2 == 0) || (2 * f2 == P);
-  const bool active = !((s1 && edge1) || (s2 && edge2));
-  const int q1 = s1 ? P - f1 : f1;
-  const int q2 = s2 ? P - f2 : f2;
-  const long plane = (long)P * P * ld;
-  const long lineoff = ((long)q1 * P + q2) * ld;
-  const C<R>* kg = Kp + ((long)f1 * H + f2) * 4 * H;
-  for (int e = tid; e < 4 * H; e += blockDim.x) kl[e] = kg[e];
-  for (int e = tid; e < P; e += blockDim.x) twl[e] = tw[e];
-  const R sx = s1 ? (R)-1 : (R)1;
-  const R sy = s2 ? (R)-1 : (R)1;
-  __syncthreads();
-  C<R>* myex = ex + job * EXS;
-  constexpr int KIN = (N2 + 1) / 2;
-  for (int b = 0; b < B; ++b) {
-    C<R>* base[4];
-#pragma unroll
-    for (int c = 0; c < 3; ++c) base[c] = X + ((long)b * 3 + c) * plane + lineoff;
-    base[3] = X + ((long)B * 3 + b) * plane + lineoff;
-    C<R> u[4][N1];
-#pragma unroll
-    for (int c = 0; c < 4; ++c) {
-      if (active && j < N1) {
-        C<R> v[N2];
-#pragma unroll
-        for (int k = 0; k < KIN; ++k) {
-          const int tt = j + N1 * k;
-          v[k] = (tt < n) ? base[c][tt] : cmk<R>(0, 0);
-        }
-        DftZ<N2, -1, R, KIN>::run(v);
-#pragma unroll
-        for (int q = 0; q < N2; ++q) myex[q * (N1 + 1) + j] = (j * q == 0) ? v[q] : v[q] * twl[j * q];
-      }
-      __syncthreads();
-      if (active && j < N2) {
-#pragma unroll
-        for (int a = 0; a < N1; ++a) u[c][a] = myex[j * (N1 + 1) + a];
-        Dft<N1, -1, R>::run(u[c]);
-      }
-      __syncthreads();
-    }
-    if (active && j < N2) {
-#pragma unroll
-      for (int a = 0; a < N1; ++a) {
-        const int q3 = j + N2 * a;
-        const bool fl3 = 2 * q3 > P;
-        const int f3 = fl3 ? P - q3 : q3;
-        const R s3 = fl3 ? (R)-1 : (R)1;
-        const C<R> g0 = kl[f3];
-        const C<R> g1 = cscale(kl[H + f3], sx), g2 = cscale(kl[2 * H + f3], sy), g3 = cscale(kl[3 * H + f3], s3);
-        const C<R> w = u[3][a];
-        u[0][a] = g0 * u[0][a] + g1 * w;
-        u[1][a] = g0 * u[1][a] + g2 * w;
-        u[2][a] = g0 * u[2][a] + g3 * w;
-      }
-    }
-#pragma unroll
-    for (int c = 0; c < 3; ++c) {
-      if (active && j < N2) {
-        Dft<N1, 1, R>::run(u[c]);
-#pragma unroll
-        for (int t2 = 0; t2 < N1; ++t2)
-          myex[j * (N1 + 1) + t2] = (j * t2 == 0) ? u[c][t2] : u[c][t2] * cconj(twl[j * t2]);
-      }
-      __syncthreads();
-      if (active && j < N1) {
-        C<R> v[N2];
-#pragma unroll
-        for (int q = 0; q < N2; ++q) v[q] = myex[q * (N1 + 1) + j];
-        Dft<N2, 1, R>::run(v);
-#pragma unroll
-        for (int t1 = 0; t1 < (N2 + 1) / 2; ++t1) {
-          const int tt = j + N1 * t1;
-          if (tt < n) base[c][tt] = v[t1];
-        }
-      }
-      __syncthreads();
-    }
-  }
 }
 
 // ---- passes 2 to 4 of one (q1) plane in LDS (short transforms) -----------------
@@ -1063,12 +995,12 @@ static ls_status launch_col_rt(bool half, bool persist, const void* in, void* ou
                                                  persist);
 }
 
-template <typename R, int P, int W>
+template <typename R, int P, int NF, int W>
 static ls_status launch_kmul_w(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int ld, int B, bool persist, hipStream_t s) {
   constexpr Fac f = row_factors<R>(P);
   constexpr int H = P / 2 + 1;
   constexpr int threads = W * 4 * job_lanes(cmax(f.n1, f.n2));
-  const auto kern = persist ? kmul_kernel<R, P, f.n1, f.n2, W, true> : kmul_kernel<R, P, f.n1, f.n2, W, false>;
+  const auto kern = persist ? kmul_kernel<R, P, f.n1, f.n2, W, NF, true> : kmul_kernel<R, P, f.n1, f.n2, W, NF, false>;
   long grid = (long)H * H;
   if (persist) {
     const long r = resident_workgroups(reinterpret_cast<const void*>(kern), threads);
@@ -1084,7 +1016,7 @@ static ls_status launch_kmul_w(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, i
 // and eight (1.30 ms): small workgroups let several workgroups per CU sit in
 // different phases (loads, arithmetic, stores), which one large workgroup
 // cannot.  The autotuner may pick another count per plan.
-template <typename R, int P>
+template <typename R, int P, int NF>
 static ls_status launch_kmul(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int ld, int B, int wt, bool persist,
                             hipStream_t s) {
   constexpr Fac f = row_factors<R>(P);
@@ -1093,8 +1025,8 @@ static ls_status launch_kmul(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int
     // FP64: paired lanes; teams are two wavefronts, one or two per workgroup
     constexpr int H = P / 2 + 1;
     const bool two = wt >= 2 && B >= 2;
-    const auto kern = two ? (persist ? kmul2_kernel<R, 2, true> : kmul2_kernel<R, 2, false>)
-                          : (persist ? kmul2_kernel<R, 1, true> : kmul2_kernel<R, 1, false>);
+    const auto kern = two ? (persist ? kmul2_kernel<R, 2, NF, true> : kmul2_kernel<R, 2, NF, false>)
+                          : (persist ? kmul2_kernel<R, 1, NF, true> : kmul2_kernel<R, 1, NF, false>);
     const int threads = two ? 256 : 128;
     long grid = (long)H * H;
     if (persist) {
@@ -1107,12 +1039,12 @@ static ls_status launch_kmul(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int
   }
   if (wt <= 0) wt = 2;
   if constexpr (job_lanes(TPL) == 16) {
-    if (wt >= 4 && B >= 4) return launch_kmul_w<R, P, 4>(X, Kh, tw, n, ld, B, persist, s);
-    if (wt >= 2 && B >= 2) return launch_kmul_w<R, P, 2>(X, Kh, tw, n, ld, B, persist, s);
+    if (wt >= 4 && B >= 4) return launch_kmul_w<R, P, NF, 4>(X, Kh, tw, n, ld, B, persist, s);
+    if (wt >= 2 && B >= 2) return launch_kmul_w<R, P, NF, 2>(X, Kh, tw, n, ld, B, persist, s);
   } else if constexpr (job_lanes(TPL) == 32) {
-    if (wt >= 2 && B >= 2) return launch_kmul_w<R, P, 2>(X, Kh, tw, n, ld, B, persist, s);
+    if (wt >= 2 && B >= 2) return launch_kmul_w<R, P, NF, 2>(X, Kh, tw, n, ld, B, persist, s);
   }
-  return launch_kmul_w<R, P, 1>(X, Kh, tw, n, ld, B, persist, s);
+  return launch_kmul_w<R, P, NF, 1>(X, Kh, tw, n, ld, B, persist, s);
 }
 
 // Passes 2 to 4 as one plane_kernel launch: X1 rows of in_rs in, Y1 [3B][P][n][out_ld] out.
@@ -1182,7 +1114,7 @@ static ls_status run_passes(ApplyPlan& ap, const void* x, void* y, int nrhs, con
                                             ColShape{n, n, ld, r1, (long)P * ld}, nb * P, (R)1, s)));
     LS_MARK(2);
     // pass 3: along dim 3 with the 3x3 multiply
-    LS_TRY((launch_kmul<R, P>(X2, kh, tw, n, ld, nrhs, tn.kmul_w, pe3, s)));
+    LS_TRY((launch_kmul<R, P, 3>(X2, kh, tw, n, ld, nrhs, tn.kmul_w, pe3, s)));
     LS_MARK(3);
     // pass 4: inverse along dim 2
     LS_TRY((launch_col_rt<R, R, P, COL_INV>(tn.half_runs & 4, pe, X2, X1, nullptr, tw, P, n,
@@ -1232,13 +1164,7 @@ static ls_status run_passes34(ApplyPlan& ap, const void* x, void* y, int nrhs, c
     LS_TRY((launch_col<R, R, P, COL_FWD>(X1, X2, nullptr, tw, n, P, ColShape{n, n, ld, r1, (long)P * ld}, 4L * nrhs * P,
                                          (R)1, s)));
     LS_MARK(2);
-    {
-      constexpr Fac f = row_factors<R>(P);
-      constexpr int H = P / 2 + 1;
-      hipLaunchKernelGGL((kmul34_kernel<R, P, f.n1, f.n2>), dim3(H * H), dim3(4 * cmax(f.n1, f.n2)), 0, s, X2, kp, tw,
-                         n, ld, nrhs);
-      LS_HIP(hipGetLastError());
-    }
+    LS_TRY((launch_kmul<R, P, 4>(X2, kp, tw, n, ld, nrhs, 0, false, s)));
     LS_MARK(3);
     LS_TRY((launch_col<R, R, P, COL_INV>(X2, X1, nullptr, tw, P, n, ColShape{n, ld, ld, (long)P * ld, w1}, nb * P, (R)1,
                                          s)));
