@@ -29,16 +29,17 @@ namespace {
 
 constexpr int kRed = 256;        // threads per reduction block
 
-// partial[b][blk] = sum over the block's elements of conj(V_q) w for q < nv
-// V: nv vectors of length len (stride vstride), w: length len; batched over
-// right-hand sides b with strides.
+// partial[b][q][blk] = sum over the block's elements of conj(V_q) w of rhs
+// b = blockIdx.z for q < nv (V: nv vectors of length len, stride vstride; the
+// right-hand sides' V and w bstride apart)
 __global__ void multidot_kernel(const C<double>* __restrict__ V, long vstride, int nv,
-                                const C<double>* __restrict__ w, long len, int nblk,
+                                const C<double>* __restrict__ w, long len, long bstride, int nblk,
                                 C<double>* __restrict__ partial) {
   __shared__ double sr[kRed], si[kRed];
   const int q = blockIdx.y;
   const int blk = blockIdx.x;
-  const C<double>* v = V + (long)q * vstride;
+  const C<double>* v = V + (long)q * vstride + blockIdx.z * bstride;
+  w += blockIdx.z * bstride;
   double ar = 0.0, ai = 0.0;
   for (long e = (long)blk * kRed + threadIdx.x; e < len; e += (long)nblk * kRed) {
     const C<double> a = v[e], b = w[e];
@@ -55,19 +56,31 @@ __global__ void multidot_kernel(const C<double>* __restrict__ V, long vstride, i
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) partial[(long)q * nblk + blk] = cmk(sr[0], si[0]);
+  if (threadIdx.x == 0) partial[((long)blockIdx.z * nv + q) * nblk + blk] = cmk(sr[0], si[0]);
 }
 
-__global__ void sum_partials_kernel(const C<double>* __restrict__ partial, int nblk, int nv,
-                                    C<double>* __restrict__ out) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  if (q >= nv) return;
+// out[b hstride + q] = the 64 block partials of (b, q) added in block order,
+// partial k at partial[b pb + q pq + k pk].  A wave per sum: its lanes load the
+// partials at once and lane 0 adds them from LDS (one thread loading 64 in
+// turn waited for most of them: 18.7 us after a Gram-Schmidt pass of 16 rhs,
+// 6.7 us after a norm, now 4 to 5).
+constexpr int kSumBlk = 64;
+__global__ __launch_bounds__(256) void sum_partials_kernel(const C<double>* __restrict__ partial, long pb, long pq,
+                                                           long pk, int nv, C<double>* __restrict__ out,
+                                                           long hstride) {
+  __shared__ C<double> v[4][kSumBlk];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int q = blockIdx.x * 4 + wv;
+  v[wv][lane] = partial[blockIdx.y * pb + min(q, nv - 1) * pq + lane * pk];
+  __syncthreads();
+  if (lane != 0 || q >= nv) return;
   double r = 0.0, i = 0.0;
-  for (int b = 0; b < nblk; ++b) {
-    r += partial[(long)q * nblk + b].re;
-    i += partial[(long)q * nblk + b].im;
+#pragma unroll
+  for (int k = 0; k < kSumBlk; ++k) {
+    r += v[wv][k].re;
+    i += v[wv][k].im;
   }
-  out[q] = cmk(r, i);
+  out[blockIdx.y * hstride + q] = cmk(r, i);
 }
 
 // w -= sum_q V_q h_q
@@ -80,35 +93,50 @@ __global__ void subtract_combo_kernel(const C<double>* __restrict__ V, long vstr
   w[e] = acc;
 }
 
-// x += sum_q Z_q y_q
-__global__ void add_combo_kernel(const C<double>* __restrict__ Z, long zstride, int nv,
-                                 const C<double>* __restrict__ y, C<double>* __restrict__ x, long len) {
+constexpr int kList = 32;   // right-hand sides a listed launch takes
+
+// x += sum_q Z_q y_q for the listed right-hand sides (vectors len apart, y ystride apart)
+struct ComboList {
+  int b[kList], nv[kList];
+};
+__global__ void add_combo_kernel(const C<double>* __restrict__ Z, long zstride, ComboList l,
+                                 const C<double>* __restrict__ y, long ystride, C<double>* __restrict__ x, long len) {
   const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= len) return;
-  C<double> acc = x[e];
-  for (int q = 0; q < nv; ++q) acc = acc + Z[(long)q * zstride + e] * y[q];
-  x[e] = acc;
+  const int b = l.b[blockIdx.y], nv = l.nv[blockIdx.y];
+  const long o = b * len + e;
+  C<double> acc = x[o];
+  for (int q = 0; q < nv; ++q) acc = acc + Z[(long)q * zstride + o] * y[b * ystride + q];
+  x[o] = acc;
 }
 
-__global__ void scale_copy_kernel(const C<double>* __restrict__ a, double s, C<double>* __restrict__ b, long len) {
+// dst = s src for the listed right-hand sides (vectors len apart)
+struct ScaleList {
+  double s[kList];
+  int b[kList];
+};
+__global__ void scale_copy_kernel(const C<double>* __restrict__ src, ScaleList l, C<double>* __restrict__ dst,
+                                  long len) {
   const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < len) b[e] = cscale(a[e], s);
+  const long o = (long)l.b[blockIdx.y] * len + e;
+  if (e < len) dst[o] = cscale(src[o], l.s[blockIdx.y]);
 }
 
 // r = g - r  (r holds A x on entry)
 __global__ void residual_kernel(const C<double>* __restrict__ g, C<double>* __restrict__ r, long len) {
-  const long e = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (e < len) r[e] = g[e] - r[e];
+  for (long e = (long)blockIdx.x * blockDim.x + threadIdx.x; e < len; e += (long)gridDim.x * blockDim.x)
+    r[e] = g[e] - r[e];
 }
 
 inline unsigned blocks_for(long len, int t) { return (unsigned)((len + t - 1) / t); }
+inline unsigned grid_stride_blocks(long len) { return (unsigned)std::min((len + 255) / 256, 1L << 20); }
 
 // ---- fused Gram-Schmidt passes over a run of right-hand sides ----------------
 // The two classical Gram-Schmidt passes and the norm of one Arnoldi step read
 // each Krylov vector three times instead of four and the new vector once per
 // pass instead of once per Krylov vector, and one launch covers every rhs of
 // a contiguous run.  The sums are the same as multidot's, in another order.
-constexpr int kOrthBlk = 64;    // blocks per rhs
+constexpr int kOrthBlk = kSumBlk;   // blocks per rhs
 constexpr int kMaxV = 32;       // Krylov vectors a fused pass handles
 
 __device__ __forceinline__ double wave_sum(double v) {
@@ -185,29 +213,20 @@ __global__ __launch_bounds__(256) void orth_pass_kernel(const C<double>* __restr
   }
 }
 
-// out[b hstride + q] = the nblk block partials of rhs b = b0 + blockIdx.x added in block order
-__global__ void orth_sum_kernel(const C<double>* __restrict__ partial, int nblk, int nv, int b0,
-                                C<double>* __restrict__ out, long hstride) {
-  const int b = b0 + blockIdx.x, q = threadIdx.x;
-  if (q >= nv) return;
-  double r = 0.0, i = 0.0;
-  for (int k = 0; k < nblk; ++k) {
-    const C<double> v = partial[((long)blockIdx.x * nblk + k) * kMaxV + q];
-    r += v.re;
-    i += v.im;
-  }
-  out[(long)b * hstride + q] = cmk(r, i);
-}
-
 }  // namespace
 
-// sums conj(V_q) . w for q < nv into hout (device), blocking
-ls_status multidot(const C<double>* V, long vstride, int nv, const C<double>* w, long len, C<double>* partial,
-                   C<double>* hdev, hipStream_t s) {
-  const int nblk = 64;
-  hipLaunchKernelGGL(multidot_kernel, dim3(nblk, nv), dim3(kRed), 0, s, V, vstride, nv, w, len, nblk, partial);
-  LS_HIP(hipGetLastError());
-  hipLaunchKernelGGL(sum_partials_kernel, dim3(blocks_for(nv, 64)), dim3(64), 0, s, partial, nblk, nv, hdev);
+static void sum_partials(const C<double>* partial, long pb, long pq, long pk, int nv, int nb, C<double>* out,
+                         long hstride, hipStream_t s) {
+  hipLaunchKernelGGL(sum_partials_kernel, dim3((nv + 3) / 4, nb), dim3(256), 0, s, partial, pb, pq, pk, nv, out,
+                     hstride);
+}
+
+// sums conj(V_q) . w for q < nv of nb right-hand sides (bstride apart) into hdev (hstride apart)
+ls_status multidot(const C<double>* V, long vstride, int nv, const C<double>* w, long len, long bstride, int nb,
+                   C<double>* partial, C<double>* hdev, long hstride, hipStream_t s) {
+  hipLaunchKernelGGL(multidot_kernel, dim3(kSumBlk, nv, nb), dim3(kRed), 0, s, V, vstride, nv, w, len, bstride, kSumBlk,
+                     partial);
+  sum_partials(partial, (long)nv * kSumBlk, kSumBlk, 1, nv, nb, hdev, hstride, s);
   LS_HIP(hipGetLastError());
   return LS_OK;
 }
@@ -238,20 +257,38 @@ ls_status gmres_solve(GmresContext& ctx, const GmresOps& ops, const C<double>* g
   auto Zp = [&](int b, int q) { return Z + q * qstride + (long)b * len; };
   auto Wp = [&](int b) { return W + (long)b * len; };
 
-  // squared norms of nrhs vectors (w(b)) into hslot b, one copy and one wait
+  // squared norms of nrhs vectors (w + b len) into hslot b, one copy and one wait
   C<double>* hd = ctx.hdev.as<C<double>>();
-  auto norms = [&](const std::function<const C<double>*(int)>& w, std::vector<double>& out) -> ls_status {
-    for (int b = 0; b < nrhs; ++b)
-      LS_TRY(multidot(w(b), len, 1, w(b), len, ctx.partial.as<C<double>>(), hd + (size_t)b * hslot, s));
+  auto norms = [&](const C<double>* w, std::vector<double>& out) -> ls_status {
+    for (int b = 0; b < nrhs; b += 65535)
+      LS_TRY(multidot(w + b * len, len, 1, w + b * len, len, len, std::min(nrhs - b, 65535), ctx.partial.as<C<double>>(),
+                      hd + (size_t)b * hslot, (long)hslot, s));
     LS_HIP(hipMemcpyAsync(hhost.data(), hd, sizeof(C<double>) * hslot * nrhs, hipMemcpyDeviceToHost, s));
     LS_HIP(hipStreamSynchronize(s));
     for (int b = 0; b < nrhs; ++b) out[b] = sqrt(fmax(hhost[(size_t)b * hslot].re, 0.0));
     return LS_OK;
   };
+  // Krylov vector q of the listed rhs: W scaled; empties the list
+  std::vector<std::pair<int, double>> next;
+  auto scale_copies = [&](int q) -> ls_status {
+    for (size_t i = 0; i < next.size(); i += kList) {
+      const int cnt = (int)std::min(next.size() - i, (size_t)kList);
+      ScaleList l = {};
+      for (int k = 0; k < cnt; ++k) {
+        l.b[k] = next[i + k].first;
+        l.s[k] = next[i + k].second;
+      }
+      hipLaunchKernelGGL(scale_copy_kernel, dim3(blocks_for(len, 256), cnt), dim3(256), 0, s, (const C<double>*)W, l,
+                         V + q * qstride, len);
+      LS_HIP(hipGetLastError());
+    }
+    next.clear();
+    return LS_OK;
+  };
   std::vector<double> gnorm(nrhs), rel(nrhs);
   std::vector<int> iters(nrhs, 0), restarts(nrhs, 0);
   std::vector<char> done(nrhs, 0);
-  LS_TRY(norms([&](int b) { return g + (long)b * len; }, gnorm));
+  LS_TRY(norms(g, gnorm));
   for (int b = 0; b < nrhs; ++b) info[b] = ls_solve_info{0, 0, 0.0, 0.0, 0.0};
   LS_HIP(hipMemsetAsync(x, 0, (size_t)nrhs * vbytes, s));
   double t_host = 0.0;
@@ -262,11 +299,9 @@ ls_status gmres_solve(GmresContext& ctx, const GmresOps& ops, const C<double>* g
     LS_TRY(ops.apply(x, W, nrhs, LS_C128, s));
     std::vector<double> beta(nrhs);
     int active = 0;
-    for (int b = 0; b < nrhs; ++b) {
-      hipLaunchKernelGGL(residual_kernel, dim3(blocks_for(len, 256)), dim3(256), 0, s, g + (long)b * len, Wp(b), len);
-      LS_HIP(hipGetLastError());
-    }
-    LS_TRY(norms([&](int b) { return (const C<double>*)Wp(b); }, beta));
+    hipLaunchKernelGGL(residual_kernel, dim3(grid_stride_blocks(len * nrhs)), dim3(256), 0, s, g, W, len * nrhs);
+    LS_HIP(hipGetLastError());
+    LS_TRY(norms(W, beta));
     for (int b = 0; b < nrhs; ++b) {
       rel[b] = gnorm[b] > 0 ? beta[b] / gnorm[b] : 0.0;
       if (rel[b] <= tol || gnorm[b] == 0.0) done[b] = 1;
@@ -282,11 +317,10 @@ ls_status gmres_solve(GmresContext& ctx, const GmresOps& ops, const C<double>* g
     for (int b = 0; b < nrhs; ++b) {
       if (done[b]) continue;
       live[b] = 1;
-      hipLaunchKernelGGL(scale_copy_kernel, dim3(blocks_for(len, 256)), dim3(256), 0, s, Wp(b), 1.0 / beta[b],
-                         Vp(b, 0), len);
-      LS_HIP(hipGetLastError());
+      next.emplace_back(b, 1.0 / beta[b]);
       e[b][0] = cmk(beta[b], 0.0);
     }
+    LS_TRY(scale_copies(0));
     const bool mixed = (prec == LS_MIXED);
     for (int j = 0; j < m && total < maxit; ++j) {
       // gather live rhs: preconditioner and operator on the batch
@@ -318,15 +352,15 @@ ls_status gmres_solve(GmresContext& ctx, const GmresOps& ops, const C<double>* g
         C<double>* h1d = hd + (size_t)b * hslot;
         C<double>* h2d = h1d + (m + 1);
         C<double>* hnd = h2d + (m + 1);
-        LS_TRY(multidot(Vp(b, 0), qstride, j + 1, Wp(b), len, ctx.partial.as<C<double>>(), h1d, s));
+        LS_TRY(multidot(Vp(b, 0), qstride, j + 1, Wp(b), len, 0, 1, ctx.partial.as<C<double>>(), h1d, 0, s));
         hipLaunchKernelGGL(subtract_combo_kernel, dim3(blocks_for(len, 256)), dim3(256), 0, s, Vp(b, 0), qstride,
                            j + 1, (const C<double>*)h1d, Wp(b), len);
         LS_HIP(hipGetLastError());
-        LS_TRY(multidot(Vp(b, 0), qstride, j + 1, Wp(b), len, ctx.partial.as<C<double>>(), h2d, s));
+        LS_TRY(multidot(Vp(b, 0), qstride, j + 1, Wp(b), len, 0, 1, ctx.partial.as<C<double>>(), h2d, 0, s));
         hipLaunchKernelGGL(subtract_combo_kernel, dim3(blocks_for(len, 256)), dim3(256), 0, s, Vp(b, 0), qstride,
                            j + 1, (const C<double>*)h2d, Wp(b), len);
         LS_HIP(hipGetLastError());
-        return multidot(Wp(b), len, 1, Wp(b), len, ctx.partial.as<C<double>>(), hnd, s);
+        return multidot(Wp(b), len, 1, Wp(b), len, 0, 1, ctx.partial.as<C<double>>(), hnd, 0, s);
       };
       if (j + 1 <= kMaxV) {
         C<double>* part = ctx.partial.as<C<double>>();
@@ -343,16 +377,15 @@ ls_status gmres_solve(GmresContext& ctx, const GmresOps& ops, const C<double>* g
           const dim3 g(nblk, nb);
           hipLaunchKernelGGL((orth_pass_kernel<false, false>), g, dim3(256), 0, s, V, qstride, nv, W, len, b0,
                              (const C<double>*)nullptr, 0L, part);
-          hipLaunchKernelGGL(orth_sum_kernel, dim3(nb), dim3(kMaxV), 0, s, (const C<double>*)part, nblk, nv, b0, hd,
-                             (long)hslot);
+          C<double>* hb = hd + (size_t)b0 * hslot;
+          const long pb = (long)nblk * kMaxV;
+          sum_partials(part, pb, 1, kMaxV, nv, nb, hb, (long)hslot, s);
           hipLaunchKernelGGL((orth_pass_kernel<true, false>), g, dim3(256), 0, s, V, qstride, nv, W, len, b0,
                              (const C<double>*)hd, (long)hslot, part);
-          hipLaunchKernelGGL(orth_sum_kernel, dim3(nb), dim3(kMaxV), 0, s, (const C<double>*)part, nblk, nv, b0,
-                             hd + (m + 1), (long)hslot);
+          sum_partials(part, pb, 1, kMaxV, nv, nb, hb + (m + 1), (long)hslot, s);
           hipLaunchKernelGGL((orth_pass_kernel<true, true>), g, dim3(256), 0, s, V, qstride, nv, W, len, b0,
                              (const C<double>*)(hd + (m + 1)), (long)hslot, part);
-          hipLaunchKernelGGL(orth_sum_kernel, dim3(nb), dim3(kMaxV), 0, s, (const C<double>*)part, nblk, 1, b0,
-                             hd + 2 * (m + 1), (long)hslot);
+          sum_partials(part, pb, 1, kMaxV, 1, nb, hb + 2 * (m + 1), (long)hslot, s);
           LS_HIP(hipGetLastError());
           i0 = i1;
         }
@@ -399,17 +432,17 @@ ls_status gmres_solve(GmresContext& ctx, const GmresOps& ops, const C<double>* g
         if (conv || refine || hn == 0.0) {
           live[b] = 0;
         } else if (j + 1 < m) {
-          hipLaunchKernelGGL(scale_copy_kernel, dim3(blocks_for(len, 256)), dim3(256), 0, s, Wp(b), 1.0 / hn,
-                             Vp(b, j + 1), len);
-          LS_HIP(hipGetLastError());
+          next.emplace_back(b, 1.0 / hn);
         }
       }
+      LS_TRY(scale_copies(j + 1));
     }
     // x += Z y for every rhs that ran this cycle
+    std::vector<int> ub;
     for (int b = 0; b < nrhs; ++b) {
       const int ju = jused[b];
       if (ju == 0) continue;
-      std::vector<C<double>> y(ju);
+      C<double>* y = hhost.data() + (size_t)b * hslot;
       for (int i = ju - 1; i >= 0; --i) {
         C<double> acc = e[b][i];
         for (int k2 = i + 1; k2 < ju; ++k2) acc = acc - H[b][(size_t)i * m + k2] * y[k2];
@@ -417,12 +450,21 @@ ls_status gmres_solve(GmresContext& ctx, const GmresOps& ops, const C<double>* g
         const double dd = d.re * d.re + d.im * d.im;
         y[i] = dd > 0 ? cscale(acc * cconj(d), 1.0 / dd) : cmk(0.0, 0.0);
       }
-      C<double>* yd = hd + (size_t)b * hslot;   // this rhs's own slot: no reuse before the copy lands
-      LS_HIP(hipMemcpyAsync(yd, y.data(), ju * sizeof(C<double>), hipMemcpyHostToDevice, s));
-      hipLaunchKernelGGL(add_combo_kernel, dim3(blocks_for(len, 256)), dim3(256), 0, s, Zp(b, 0), qstride, ju,
-                         (const C<double>*)yd, x + (long)b * len, len);
-      LS_HIP(hipGetLastError());
+      ub.push_back(b);
       restarts[b] += 1;
+    }
+    if (!ub.empty())
+      LS_HIP(hipMemcpyAsync(hd, hhost.data(), sizeof(C<double>) * hslot * nrhs, hipMemcpyHostToDevice, s));
+    for (size_t i = 0; i < ub.size(); i += kList) {
+      const int cnt = (int)std::min(ub.size() - i, (size_t)kList);
+      ComboList l = {};
+      for (int k = 0; k < cnt; ++k) {
+        l.b[k] = ub[i + k];
+        l.nv[k] = jused[ub[i + k]];
+      }
+      hipLaunchKernelGGL(add_combo_kernel, dim3(blocks_for(len, 256), cnt), dim3(256), 0, s, (const C<double>*)Z, qstride,
+                         l, (const C<double>*)hd, (long)hslot, x, len);
+      LS_HIP(hipGetLastError());
     }
   }
   LS_HIP(hipStreamSynchronize(s));

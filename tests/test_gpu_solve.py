@@ -134,3 +134,30 @@ def test_reciprocity_of_gpu_solutions(lib):
     ba = np.sum(Ei[1] * m[None] * E[0])
     print("reciprocity", ab, ba, flush=True)
     assert abs(ab - ba) <= 1e-8 * max(abs(ab), abs(ba))
+
+
+@pytest.mark.parametrize("restart", [4, 30])
+def test_solve_more_rhs_than_a_list(lib, restart):
+    """35 right-hand sides (the launches over listed rhs take 32), one of them
+    zero and one scaled far down, with several restarts and with none: every
+    residual recomputed by the oracle."""
+    from paper_1804_02297_amd.binding import Plan
+    n = 8
+    k = I.wavenumber_for(n)
+    m = I.medium_bumps(n, 3)
+    b = I.random_field(35, n, 64)
+    b[7] = 0.0
+    b[33] *= 1e-6
+    plan = Plan(n, k, _dev(m), max_rhs=35)
+    plan.stencil_fit()
+    plan.factor()
+    x, info, st = plan.solve(_dev(b), tol=1e-9, restart=restart)
+    assert st == 0
+    xh = x.cpu().numpy()
+    assert np.abs(xh[7]).max() == 0.0
+    keep = [i for i in range(35) if i != 7]
+    rel = _rel_resid(n, k, m, b[keep], xh[keep])
+    print(f"restart {restart} {rel.max():.2e}", flush=True)
+    assert rel.max() <= 1.01e-9
+    for q, i in enumerate(keep):
+        assert abs(info[i]["rel_resid"] - rel[q]) <= 1e-12
