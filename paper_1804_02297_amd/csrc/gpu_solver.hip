@@ -1029,9 +1029,13 @@ struct SolveCfg {
 //        the later tiles t' of the block);
 //   BWD: H = U_block^-1 (tiles from last to first: x_t <- U_t^-1 x_t, then
 //        x_t' -= U[t'][t] x_t for the earlier tiles).
-// Each workgroup runs the procedure on RZ columns of the identity in LDS
-// (grid.y: super-blocks, grid.z: column chunks), products on MFMA.
-template <typename R, bool FWD>
+// Each workgroup runs one procedure on RZ columns of the identity in LDS
+// (grid.y: super-blocks, grid.z: column chunks of M, then of H), products on MFMA.
+// What bounds it: the chain of tiles, so M and H are one launch, the tiles whose
+// part of the columns is still zero are not visited, and in FP64 (RZ = 32) the
+// four waves share the later tiles as two columns of waves: n = 29 set-up 4.6 to
+// 2.0 ms, 2-D n = 479 12.5 to 7.5 ms.
+template <typename R>
 __global__ __launch_bounds__(256) void sb_inverse_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl,
                                                          int nlvl, const R* __restrict__ buf, R* __restrict__ fac,
                                                          const int* __restrict__ ib) {
@@ -1040,7 +1044,11 @@ __global__ __launch_bounds__(256) void sb_inverse_kernel(const FrontDev* __restr
   __shared__ R Sr[kSB * LD], Si[kSB * LD];
   __shared__ int perm[kT];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const bool active = wave < RZ / 16;
+  constexpr int CW = RZ / 16, UW = 4 / CW;   // waves by columns, and by the tiles of an update
+  const int c16 = 16 * (wave % CW), uwave = wave / CW;
+  const auto run = [&](auto FW) {
+  constexpr bool FWD = decltype(FW)::value;
+  const int chunk = blockIdx.z % (kSB / RZ);
   for (int q = blockIdx.x; q < nlvl; q += gridDim.x) {
     const FrontDev d = fr[lvl[q]];
     const long nf = d.nf;
@@ -1049,7 +1057,7 @@ __global__ __launch_bounds__(256) void sb_inverse_kernel(const FrontDev* __restr
     for (int sb = blockIdx.y; (long)sb * kSB < d.np; sb += gridDim.y) {
       const int kb0 = sb * kSB;
       const int sw = min(kSB, d.np - kb0);
-      const int c0 = blockIdx.z * RZ;
+      const int c0 = chunk * RZ;
       if (c0 >= sw) continue;
       for (int o = tid; o < kSB * RZ; o += blockDim.x) {
         const int k = o / RZ, r = o % RZ;
@@ -1058,43 +1066,44 @@ __global__ __launch_bounds__(256) void sb_inverse_kernel(const FrontDev* __restr
       }
       __syncthreads();
       const int nt = (sw + kT - 1) / kT;
-      for (int s = 0; s < nt; ++s) {
+      // M is lower, H upper triangular by tiles: the columns are zero before their first / after their last tile
+      for (int s = FWD ? c0 / kT : nt - 1 - min(c0 + RZ - 1, sw - 1) / kT; s < nt; ++s) {
         const int t0 = FWD ? s * kT : (nt - 1 - s) * kT;
         const int tw = min(kT, sw - t0);
         const long kb = kb0 + t0;
         if (FWD && tid < tw) perm[tid] = ib[d.pv + kb + tid];
         __syncthreads();
-        if (active) {   // x_t <- L_t^-1 P_t x_t  or  U_t^-1 x_t, in place
+        if (uwave == 0) {   // x_t <- L_t^-1 P_t x_t  or  U_t^-1 x_t, in place
           v4 yr[3], yi[3];
           const R* T = fac + d.t + (kb / kT) * 4 * kTileElems + (FWD ? 0 : 2 * kTileElems);
-          mma48_gl<R>(T, T + kTileElems, kT, tw, tw, Sr, Si, LD, FWD ? perm : nullptr, t0, 16 * wave, lane, yr, yi);
+          mma48_gl<R>(T, T + kTileElems, kT, tw, tw, Sr, Si, LD, FWD ? perm : nullptr, t0, c16, lane, yr, yi);
 #pragma unroll
           for (int rt = 0; rt < 3; ++rt)
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
               const int i = 16 * rt + Mma<R>::row(lane, r);
               if (i < tw) {
-                Sr[(t0 + i) * LD + 16 * wave + (lane & 15)] = yr[rt][r];
-                Si[(t0 + i) * LD + 16 * wave + (lane & 15)] = yi[rt][r];
+                Sr[(t0 + i) * LD + c16 + (lane & 15)] = yr[rt][r];
+                Si[(t0 + i) * LD + c16 + (lane & 15)] = yi[rt][r];
               }
             }
         }
         __syncthreads();
-        if (active) {   // the other tiles of the block: x_t' -= F[t'][t] x_t
+        {   // the other tiles of the block: x_t' -= F[t'][t] x_t
           const int ua = FWD ? t0 + kT : 0, ue = FWD ? sw : t0;
-          for (int u0 = ua; u0 < ue; u0 += kT) {
+          for (int u0 = ua + kT * uwave; u0 < ue; u0 += kT * UW) {
             const int uw = min(kT, sw - u0);
             v4 yr[3], yi[3];
             const long a0 = (kb0 + u0) * nf + kb;
-            mma48_gl<R>(Fr + a0, Fi + a0, nf, uw, tw, Sr, Si, LD, nullptr, t0, 16 * wave, lane, yr, yi);
+            mma48_gl<R>(Fr + a0, Fi + a0, nf, uw, tw, Sr, Si, LD, nullptr, t0, c16, lane, yr, yi);
 #pragma unroll
             for (int rt = 0; rt < 3; ++rt)
 #pragma unroll
               for (int r = 0; r < 4; ++r) {
                 const int i = 16 * rt + Mma<R>::row(lane, r);
                 if (i < uw) {
-                  Sr[(u0 + i) * LD + 16 * wave + (lane & 15)] -= yr[rt][r];
-                  Si[(u0 + i) * LD + 16 * wave + (lane & 15)] -= yi[rt][r];
+                  Sr[(u0 + i) * LD + c16 + (lane & 15)] -= yr[rt][r];
+                  Si[(u0 + i) * LD + c16 + (lane & 15)] -= yi[rt][r];
                 }
               }
           }
@@ -1113,6 +1122,11 @@ __global__ __launch_bounds__(256) void sb_inverse_kernel(const FrontDev* __restr
       __syncthreads();
     }
   }
+  };
+  if (blockIdx.z < kSB / RZ)
+    run(std::true_type{});
+  else
+    run(std::false_type{});
 }
 
 // The factor entries outside a super-block that multiply its unknowns, folded
@@ -2203,10 +2217,8 @@ ls_status factor_numeric(GpuSolver& g, const C<double>* rows, hipStream_t s) {
                        (const R*)buf, fac);
     const unsigned nsb = (unsigned)((mnp + kSB - 1) / kSB);
     const unsigned ncc = (unsigned)(kSB / SolveCfg<R>::RZ);
-    hipLaunchKernelGGL((sb_inverse_kernel<R, true>), dim3(gy, nsb, ncc), dim3(256), 0, s, fr, lvl, nl,
-                       (const R*)buf, fac, (const int*)ib);
-    hipLaunchKernelGGL((sb_inverse_kernel<R, false>), dim3(gy, nsb, ncc), dim3(256), 0, s, fr, lvl, nl,
-                       (const R*)buf, fac, (const int*)ib);
+    hipLaunchKernelGGL(sb_inverse_kernel<R>, dim3(gy, nsb, 2 * ncc), dim3(256), 0, s, fr, lvl, nl, (const R*)buf, fac,
+                       (const int*)ib);
     const unsigned hy = std::min(65535u, nsb * (unsigned)(kSB / 64));
     const unsigned hx = (unsigned)std::max(1L, (mnf + kRB - 1) / kRB);
     hipLaunchKernelGGL((hat_kernel<R, 0>), dim3(hx, hy, gy), dim3(256), 0, s, fr, lvl, nl, (const R*)buf, fac);
