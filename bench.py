@@ -36,7 +36,7 @@ KERNEL_NAMES = ["col_fft_kernel (mode 0)", "col_fft_kernel (mode 1)", "kmul_kern
 # only while the apply sources are the ones that were profiled.
 MEASURED_TRAFFIC = {
     "sources": ["fft_kernels.h", "fft_apply.hip", "fft_inst_e.hip", "common.h", "cplx.h"],
-    "sha256": "0a5f922aa79cf46908be21d9e0d170265055a3eede956f350db5b0f55b453bf4",
+    "sha256": "ed6421d00571305dcaf4c84f86c327986cc05dbe81b48098106f348e98caa637",
     "workload": (128, 8, "c64"),
     "bytes": 3.3265e9,
     "profile": "profiles/ls_apply_n128_b8_c64.md",

@@ -12,6 +12,10 @@
 //   pass 4  dim 2 inverse  X2 -> Y1[b][c][q1][i2][i3]       P rows in, n out
 //   pass 5  dim 1 inverse  y = x + Y1                      P rows in, n out, identity fused
 //
+// For P <= 64 passes 2 to 4 of one (b, q1) plane are one launch with the plane
+// in LDS (plane_kernel).  For n > 32 the rows of X1, X2 and Y1 are padded to
+// whole 128-byte lines (work_ld, work_ld2).
+//
 // Zero padding is never materialised: forward passes read only the n
 // non-zero rows, inverse passes write only the n rows that are kept.
 //

@@ -1651,8 +1651,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) =
 // launch waits for.  Every output keeps the order of products of the LDS
 // kernels (K ascending in steps of four into the same accumulators), so blocks
 // of any size above kGemvRhs agree bit for bit.
-// Measured, 16 rhs: complex128 preconditioner apply at n = 48 25.4 -> 8.4 ms;
-// complex64 block FGMRES at n = 32 30.9 -> 17.0 ms; a launch at the top of the
+// Measured, 16 rhs: complex128 preconditioner apply at n = 48 25.4 -> 8.4 ms; a launch at the top of the
 // tree 23.5 (FP64) and 17 us (FP32) -> 14.7 and 8 us.
 constexpr int kThinRhs = 32;
 constexpr int kThinPad = 256;   // factor values past the end that thin_kernel may read

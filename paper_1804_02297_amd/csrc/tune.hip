@@ -16,6 +16,8 @@
 //     item, and a workgroup that waits for it idles its CU unless other
 //     workgroups are resident there, so it can prefer the ordinary grid
 //     where the strided passes gain).
+// Where passes 2 to 4 are one launch (P <= 64), only the chunk and the choices
+// of passes 1 and 5 have an effect.
 // The first two are searched jointly, then each pass's run length is halved
 // in turn and kept where it is faster, then the three persistent settings are
 // tried on the result; the three fastest choices are finally timed again,
