@@ -366,8 +366,9 @@ template <typename T>
 __device__ __forceinline__ C<T> ld_c(const void* p, long i) { return reinterpret_cast<const C<T>*>(p)[i]; }
 
 // pass A: block w -> (rhs b, row block rb); the three fields of its rows in
-// turn, from x, m and p loaded once into registers.
-template <typename R, typename IO, int PT, int NBT>
+// turn, from x, m and p loaded once into registers.  FEW: one field per block
+// (w -> (b, rb, field)), for launches that leave most of the chip idle.
+template <typename R, typename IO, int PT, int NBT, bool FEW>
 __global__ __launch_bounds__(kT2) void pass_a_kernel(const void* __restrict__ x, const C<R>* __restrict__ m,
                                                       const C<R>* __restrict__ p, C<R>* __restrict__ T, int n, int P_,
                                                       Radices rd_, int nb_, int nrb, int nwork,
@@ -379,7 +380,8 @@ __global__ __launch_bounds__(kT2) void pass_a_kernel(const void* __restrict__ x,
   C<R>* a = reinterpret_cast<C<R>*>(lds_raw);
   C<R>* bb = a + (size_t)nb * P;
   const Tw<R> tws = load_twiddles(bb + (size_t)nb * P, tw, P);
-  const int w = xcd_work_index(blockIdx.x, nwork);
+  const int wf = xcd_work_index(blockIdx.x, nwork), w = FEW ? wf / 3 : wf;
+  const int f0 = FEW ? wf % 3 : 0, f1 = FEW ? f0 + 1 : 3;
   const int rb = w % nrb, b = w / nrb;
   const long nn = (long)n * n;
   const long xb = (long)b * 2 * nn;
@@ -399,15 +401,17 @@ __global__ __launch_bounds__(kT2) void pass_a_kernel(const void* __restrict__ x,
     rx0[u] = rx1[u] = rm[u] = rp0[u] = rp1[u] = z;
     if (e < nb * Ph && i1 < n && j < n) {
       const long o = (long)i1 * n + j;
-      rx0[u] = ccast<R>(ld_c<IO>(x, xb + o));
-      rx1[u] = ccast<R>(ld_c<IO>(x, xb + nn + o));
-      rm[u] = m[o];
-      rp0[u] = p[o];
-      rp1[u] = p[nn + o];
+      if (!FEW || f0 != 1) rx0[u] = ccast<R>(ld_c<IO>(x, xb + o));
+      if (!FEW || f0 != 0) rx1[u] = ccast<R>(ld_c<IO>(x, xb + nn + o));
+      if (!FEW || f0 != 2) rm[u] = m[o];
+      if (!FEW || f0 == 2) {
+        rp0[u] = p[o];
+        rp1[u] = p[nn + o];
+      }
     }
   }
 #pragma unroll 1
-  for (int f = 0; f < 3; ++f) {
+  for (int f = f0; f < f1; ++f) {
 #pragma unroll
     for (int u = 0; u < UA; ++u) {
       const int e = threadIdx.x + kT2 * u;
@@ -553,6 +557,65 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
       if (i1 < n) out[(size_t)i1 * P + e % nb] = X[e];
     }
     __syncthreads();
+  }
+}
+
+// pass B of one column and rhs per block, its three forward transforms run
+// together and then its two inverse ones: 2 nst stages with a barrier each
+// instead of 5 nst.  For launches of few columns, which wait for those stages
+// one after the other (few_columns).  At the FP32 register lengths its rounding
+// differs from pass_b_reg_kernel's.
+template <typename R, int PT>
+__global__ __launch_bounds__(kT2) void pass_b_few_kernel(const C<R>* __restrict__ T, C<R>* __restrict__ T2,
+                                                         const C<R>* __restrict__ symc, int n, int P_, int H,
+                                                         Radices rd_, int nrhs, const C<R>* __restrict__ tw) {
+  const int P = PT > 0 ? PT : P_;
+  const Radices rd = PT > 0 ? factor_radices(PT) : rd_;
+  extern __shared__ unsigned char lds_raw[];
+  C<R>* a = reinterpret_cast<C<R>*>(lds_raw);
+  C<R>* bb = a + 3 * (size_t)P;
+  const Tw<R> tws = load_twiddles(bb + 3 * (size_t)P, tw, P);
+  const int w = xcd_work_index(blockIdx.x, P * nrhs);
+  const int b = w % nrhs, q2 = w / nrhs;
+  for (int e = threadIdx.x; e < 3 * (P / 2); e += kT2) {   // rows past P/2 are never read
+    const int f = e % 3, i1 = e / 3;
+    a[e] = i1 < n ? T[((size_t)(b * 3 + f) * n + i1) * P + q2] : cmk<R>(0, 0);
+  }
+  // the symbol of the thread's rows, ahead of the transforms
+  constexpr int US = (std::min<int>(kMaxP2, kLds2 / (6 * sizeof(C<R>))) + kT2 - 1) / kT2;
+  C<R> sv[3][PT > 0 ? (PT + kT2 - 1) / kT2 : US];
+#pragma unroll
+  for (int u = 0; u < (PT > 0 ? (PT + kT2 - 1) / kT2 : US); ++u) {
+    const int q1 = threadIdx.x + kT2 * u;
+    const bool f1 = q1 > P / 2, f2 = q2 > P / 2;
+    const int a1 = f1 ? P - q1 : q1, a2 = f2 ? P - q2 : q2;
+#pragma unroll
+    for (int c = 0; c < 3; ++c) {
+      const C<R> v = q1 < P ? symc[((size_t)c * H + a2) * H + a1] : cmk<R>(0, 0);
+      sv[c][u] = (c == 1 && f1) || (c == 2 && f2) ? cmk<R>(-v.re, -v.im) : v;
+    }
+  }
+  __syncthreads();
+  C<R>* X;
+  if constexpr (PT > 0) X = lds_fft_ct<R, -1, true, true, false, kT2, PT, false>(a, bb, 3, 3, 1, tws);
+  else X = lds_fft<R, -1, true, true, false>(a, bb, P, rd, 3, 3, 1, tws);
+  C<R>* Y = X == a ? bb : a;
+#pragma unroll
+  for (int u = 0; u < (PT > 0 ? (PT + kT2 - 1) / kT2 : US); ++u) {
+    const int q1 = threadIdx.x + kT2 * u;
+    if (q1 < P) {
+      const C<R> u0 = X[3 * q1], u1 = X[3 * q1 + 1], v = X[3 * q1 + 2];
+      Y[2 * q1] = cfma(sv[1][u], v, sv[0][u] * u0);
+      Y[2 * q1 + 1] = cfma(sv[2][u], v, sv[0][u] * u1);
+    }
+  }
+  __syncthreads();
+  const C<R>* Z;
+  if constexpr (PT > 0) Z = lds_fft_ct<R, 1, true, false, true, kT2, PT, true>(Y, X, 2, 2, 1, tws);
+  else Z = lds_fft<R, 1, true, false, true>(Y, X, P, reverse_radices(rd), 2, 2, 1, tws);
+  for (int e = threadIdx.x; e < 2 * n; e += kT2) {
+    const int d = e & 1, i1 = e >> 1;
+    T2[((size_t)(b * 2 + d) * n + i1) * P + q2] = Z[e];
   }
 }
 
@@ -957,6 +1020,18 @@ __host__ __device__ constexpr int batch_for(int P, size_t budget = kLdsTarget) {
 template <typename R>
 size_t lds_bytes(int P, int nb) { return (2 * (size_t)nb * P + tw_entries(P)) * sizeof(C<R>); }
 
+// Row launches of fewer blocks than this (two per CU) take a block per field:
+// n = 239, complex128, one rhs 31.4 to 28.0 us a call, n = 20 35.6 to 29.7; from
+// there on (n = 239, 3 rhs) the two are equal.
+constexpr int kFewBlocks = 512;
+// Column launches of few columns take pass_b_few_kernel.  Fewer than 2048
+// columns, eight blocks per CU: n = 20 one rhs 29.7 to 20.3 us, n = 119 complex64
+// one rhs 19.9 to 15.2 and 6 rhs 23.6 to 20.5, n = 60 12 rhs 39.8 to 31.3 (complex64)
+// and 35.6 to 32.4.  And at most 2^20 elements, past which a column's
+// transforms occupy a workgroup by themselves: n = 239 4 rhs 42.0 to 39.1 and 55.4
+// to 51.4, n = 479 complex64 one rhs 50.6 to 47.5, but two rhs 59.6 to 71.6.
+inline bool few_columns(int P, int nr) { return (long)P * nr < 2048 && (long)P * P * nr <= 1 << 20; }
+
 template <typename R, typename IO, int PT>
 ls_status run_apply_p(Plan2& pl, const void* x, void* y, int nrhs, bool minus_conv, hipStream_t s,
                       hipEvent_t* ev) {
@@ -983,12 +1058,20 @@ ls_status run_apply_p(Plan2& pl, const void* x, void* y, int nrhs, bool minus_co
     void* yr = (unsigned char*)y + off;
     const int wa = nr * nrb;
     if (ev) LS_HIP(hipEventRecord(ev[0], s));
-    hipLaunchKernelGGL((pass_a_kernel<R, IO, PT, NBA>), dim3(wa), dim3(kT2), lds, s, xr, m, p, T, n, P, pl.rd, nb, nrb, wa,
-                       tw);
+    if (wa < kFewBlocks)
+      hipLaunchKernelGGL((pass_a_kernel<R, IO, PT, NBA, true>), dim3(3 * wa), dim3(kT2), lds, s, xr, m, p, T, n, P,
+                         pl.rd, nb, nrb, 3 * wa, tw);
+    else
+      hipLaunchKernelGGL((pass_a_kernel<R, IO, PT, NBA, false>), dim3(wa), dim3(kT2), lds, s, xr, m, p, T, n, P, pl.rd,
+                         nb, nrb, wa, tw);
     LS_HIP(hipGetLastError());
     constexpr int EMAX = (int)(kLds2 / (2 * sizeof(C<R>)) / kTB);
     if (ev) LS_HIP(hipEventRecord(ev[1], s));
-    if constexpr (std::is_same<R, float>::value && PT > 0 && ColRegCfg<(PT > 0 ? PT : 1)>::N1 > 0) {
+    const size_t ldsf = (6 * (size_t)P + tw_entries(P)) * sizeof(C<R>);
+    if (few_columns(P, nr) && ldsf <= kLds2) {
+      hipLaunchKernelGGL((pass_b_few_kernel<R, PT>), dim3(P * nr), dim3(kT2), ldsf, s, T, T2, symc, n, P, pl.H, pl.rd, nr,
+                         tw);
+    } else if constexpr (std::is_same<R, float>::value && PT > 0 && ColRegCfg<(PT > 0 ? PT : 1)>::N1 > 0) {
       using Cfg = ColRegCfg<PT>;
       hipLaunchKernelGGL((pass_b_reg_kernel<PT>), dim3(((PT + Cfg::NB - 1) / Cfg::NB) * nr), dim3(Cfg::THREADS), 0, s, T,
                          T2, sym, n, pl.H, nr, tw);

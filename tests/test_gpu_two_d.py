@@ -244,3 +244,23 @@ def test_paper_2d_claim(lib):
         assert st == 0 and rr <= 1.01e-6
         assert info[0]["iters"] < gold["claim_max_iters"]
         plan.close()
+
+
+@pytest.mark.parametrize("n,nrhs,max_rhs", [(12, 85, 85), (12, 86, 86), (119, 9, 8), (239, 5, 4), (300, 2, 2)])
+def test_apply_few_and_many_columns(lib, n, nrhs, max_rhs):
+    """The last batch whose columns take a workgroup each and the first that
+    does not (2048 columns, 2^20 elements), the row pass with a block per field
+    and without, and a batch whose last chunk changes route, against the oracle."""
+    from paper_1804_02297_amd.binding import Plan2
+    k = I.paper_wavenumber(n)
+    m = I.medium2_random_complex(n, 70 + n, scale=0.2)
+    x = I.random_field2(nrhs, n, 500 + n)
+    print(f"n={n} x{nrhs}", flush=True)
+    plan = Plan2(n, k, _dev(m), max_rhs=max_rhs)
+    ref = o2.apply_fft2(n, k, m, x)
+    scale = np.abs(ref).max()
+    assert np.abs(plan.apply(_dev(x)).cpu().numpy() - ref).max() <= 1e-12 * scale
+    assert np.abs(plan.apply(_dev(x), prec="mixed").cpu().numpy() - ref).max() <= 2e-5 * scale
+    y = plan.apply(_dev(x.astype(np.complex64)), prec="c64").cpu().numpy()
+    assert np.abs(y - ref).max() <= 2e-5 * scale
+    plan.close()
