@@ -47,7 +47,7 @@ MEASURED_TRAFFIC = {
 # reported only while the sources are the measured ones.
 MEASURED_TRAFFIC_2D = {
     "sources": ["twod.hip", "twod.h", "cplx.h"],
-    "sha256": "cf6e2a189cd9b62519a9921a5757e0a3f4e7ffea85c18c279ef83f30936b6f2f",
+    "sha256": "79f470a5333080f818b0932fa8a1c570d100ee38e4f1a8931ef66fdc2aa9aec8",
     "workload": (959, 8, "c64"),
     "bytes": 9.343e8,
     "profile": "profiles/ls2_apply_n959_b8_c64.md",

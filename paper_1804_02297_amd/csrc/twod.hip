@@ -16,7 +16,8 @@
 //   pass B  columns: per workgroup one rhs and a few adjacent columns: FFT
 //                    of the three fields along i1, the 2x3 symbol multiply
 //                    in registers, two inverse FFTs, rows i1 < n kept;
-//                    [rhs][2][n][P];
+//                    [rhs][2][n][P] (launches of few columns: one column per
+//                    workgroup, its transforms together);
 //   pass C  rows:    inverse FFT along i2, the first n kept, + x.
 // The symbol (k^2 Ghat, Ghat^1, Ghat^2) / P^2 is stored on the quadrant
 // [H][H][3], H = P/2 + 1: k^2 Ghat is even in both frequencies, Ghat^1 is
