@@ -694,8 +694,8 @@ struct CAcc {
   }
 };
 
-// Schur updates F[rows][cols] -= F[rows][K] F[K][cols] on a 32 x 32 tile per
-// workgroup (four waves of 16 x 16, the complex product as CAcc forms it:
+// Schur updates F[rows][cols] -= F[rows][K] F[K][cols] on a TS x TS tile per
+// workgroup (four waves of TS/2 x TS/2, the complex product as CAcc forms it:
 // three real MFMA products in FP32, four in FP64).  With the 48-column step kb
 // inside the outer block starting at kb0 (obe = min(kb0 + kOB, np)):
 //   step:  rows [ke, nf), cols [ke, obe) (the first nbx x nby tiles) and
@@ -706,24 +706,25 @@ struct CAcc {
 // step; the rest of the trailing matrix is read by nothing inside the block,
 // so its update waits and is applied once with K up to kOB.
 // What bounds it: the block update the FP64 matrix cores, the step a chain of
-// latencies at the top of the tree, so both its parts are one launch.  Why 32:
+// latencies at the top of the tree, so both its parts are one launch.  Why TS = 32:
 // 112 VGPRs and 17 KB of LDS let four workgroups share a CU, and few tiles
 // spread wider; with 64 x 64 tiles (226 VGPRs, two) the block update of two
 // fronts of 3741 took 844 us (52 TFLOP/s) against 806, that of one of 2300 185
 // against 146, the root's steps 2 x 20 against 8 to 16.  64 x 32 and 32 x 64 lie
 // between; tile rows padded to a multiple of the eight XCDs lost 2%.  A complete
-// n = 29 set-up's FP64 updates: 25.9 to 20.8 ms; FP32, n = 32: 20.5 to 18.2.
-constexpr int kST = 32;
-template <typename R>
-__global__ __launch_bounds__(256) void schur_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl,
-                                                    int nlvl, int kb, int kb0, int nbx, int nby, bool step,
-                                                    R* __restrict__ buf) {
+// n = 29 set-up's FP64 updates: 25.9 to 20.8 ms; FP32, n = 32: 20.5 to 18.2.  On
+// larger fronts TS = 64 (kSchurCols): a 32 x 32 tile reads twice as much per product.
+template <typename R, int TS>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(2))) void schur_kernel(
+    const FrontDev* __restrict__ fr, const int* __restrict__ lvl, int nlvl, int kb, int kb0, int nbx, int nby, bool step,
+    R* __restrict__ buf) {
   typedef typename Mma<R>::v4 v4;
-  constexpr int U = kST / 16;   // chunk elements per thread and plane
-  __shared__ R Ar[kST][17], Ai[kST][17];
-  __shared__ R Br[16][kST + 1], Bi[16][kST + 1];
+  constexpr int W = TS / 32;   // 16-tiles of a wave per dimension
+  constexpr int U = TS / 16;   // chunk elements per thread and plane
+  __shared__ R Ar[TS][17], Ai[TS][17];
+  __shared__ R Br[16][TS + 1], Bi[16][TS + 1];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wm = (wave >> 1) * 16, wn = (wave & 1) * 16;
+  const int wm = (wave >> 1) * (TS / 2), wn = (wave & 1) * (TS / 2);
   const int tiles = nbx * nby;
   const bool second = step && (int)blockIdx.x >= tiles;
   const int tile = second ? blockIdx.x - tiles : blockIdx.x;
@@ -747,13 +748,13 @@ __global__ __launch_bounds__(256) void schur_kernel(const FrontDev* __restrict__
       c0 = second ? obe : k1;
       c1 = second ? nf : obe;
     }
-    const long i0 = r0 + (long)kST * by, j0 = c0 + (long)kST * bx;
+    const long i0 = r0 + (long)TS * by, j0 = c0 + (long)TS * bx;
     if (i0 >= r1 || j0 >= c1) continue;
     const int tw = (int)(k1 - k0);
     const long kb_ = k0;
     R* Fr = buf + d.f;
     R* Fi = Fr + nf * nf;
-    CAcc<R, 1, 1> acc;
+    CAcc<R, W, W> acc;
     acc.zero();
     // the next 16-deep K chunk is loaded into registers while the MFMAs
     // consume the current one from LDS
@@ -767,7 +768,7 @@ __global__ __launch_bounds__(256) void schur_kernel(const FrontDev* __restrict__
         const long src = (i0 + ii) * nf + kb_ + kc + kk;
         par[u] = ok ? Fr[src] : R(0);
         pai[u] = ok ? Fi[src] : R(0);
-        const int kr = o / kST, jj = o % kST;
+        const int kr = o / TS, jj = o % TS;
         const bool okb = kc + kr < tw && j0 + jj < c1;
         const long srcb = (kb_ + kc + kr) * nf + j0 + jj;
         pbr[u] = okb ? Fr[srcb] : R(0);
@@ -781,24 +782,28 @@ __global__ __launch_bounds__(256) void schur_kernel(const FrontDev* __restrict__
         const int o = tid + 256 * u;
         Ar[o >> 4][o & 15] = par[u];
         Ai[o >> 4][o & 15] = pai[u];
-        Br[o / kST][o % kST] = pbr[u];
-        Bi[o / kST][o % kST] = pbi[u];
+        Br[o / TS][o % TS] = pbr[u];
+        Bi[o / TS][o % TS] = pbi[u];
       }
       __syncthreads();
       if (kc + 16 < tw) fetch(kc + 16);
-      acc.mma(&Ar[0][0], &Ai[0][0], 17, &Br[0][0], &Bi[0][0], kST + 1, 16, wm, wn, lane);
+      acc.mma(&Ar[0][0], &Ai[0][0], 17, &Br[0][0], &Bi[0][0], TS + 1, 16, wm, wn, lane);
       __syncthreads();
     }
-    v4 cr[1][1], ci[1][1];
+    v4 cr[W][W], ci[W][W];
     acc.result(cr, ci);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const long gi = i0 + wm + Mma<R>::row(lane, r), gj = j0 + wn + (lane & 15);
-      if (gi < r1 && gj < c1) {
-        Fr[gi * nf + gj] -= cr[0][0][r];
-        Fi[gi * nf + gj] -= ci[0][0][r];
-      }
-    }
+    for (int a = 0; a < W; ++a)
+#pragma unroll
+      for (int b = 0; b < W; ++b)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const long gi = i0 + wm + 16 * a + Mma<R>::row(lane, r), gj = j0 + wn + 16 * b + (lane & 15);
+          if (gi < r1 && gj < c1) {
+            Fr[gi * nf + gj] -= cr[a][b][r];
+            Fi[gi * nf + gj] -= ci[a][b][r];
+          }
+        }
   }
 }
 
@@ -2163,13 +2168,24 @@ struct GpuSolver {
 
 namespace {
 
+// Extents from which the updates take 64 x 64 tiles (schur_kernel): the factor at
+// n = 64, complex64 / complex128, spends 929 / 1981 ms in them with 4096, 929 / 1987
+// with 3072, 942 / 1984 with 6144, 1085 / 2160 with 32 x 32 tiles only.
+constexpr long kSchurCols = 4096;
 // cols x rows: extents of the (first) part, at most
 template <typename R>
 void launch_schur(long cols, long rows, bool step, unsigned gy, hipStream_t s, const FrontDev* fr, const int* lvl,
                   int nl, int kb, int kb0, R* buf) {
-  const long nbx = std::max(1L, (cols + kST - 1) / kST), nby = std::max(1L, (rows + kST - 1) / kST);
-  hipLaunchKernelGGL(schur_kernel<R>, dim3((unsigned)((step ? 2 : 1) * nbx * nby), gy), dim3(256), 0, s, fr, lvl, nl, kb,
-                     kb0, (int)nbx, (int)nby, step, buf);
+  const auto go = [&](auto TS) {
+    constexpr int ts = decltype(TS)::value;
+    const long nbx = std::max(1L, (cols + ts - 1) / ts), nby = std::max(1L, (rows + ts - 1) / ts);
+    hipLaunchKernelGGL((schur_kernel<R, ts>), dim3((unsigned)((step ? 2 : 1) * nbx * nby), gy), dim3(256), 0, s, fr, lvl,
+                       nl, kb, kb0, (int)nbx, (int)nby, step, buf);
+  };
+  if (cols <= kSchurCols || rows <= kSchurCols)
+    go(std::integral_constant<int, 32>{});
+  else
+    go(std::integral_constant<int, 64>{});
 }
 
 template <typename R>
