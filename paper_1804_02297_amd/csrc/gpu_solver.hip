@@ -49,6 +49,7 @@
 #include <vector>
 
 #include "nd_tree.h"
+#include "solve_work.h"
 
 namespace ls {
 
@@ -2159,9 +2160,8 @@ struct GpuSolver {
   DevBuf cinv;                         // children's rows per front point (child_map_kernel)
   DevBuf ipm;                          // inverse of the final elimination order (natural -> position)
   long u_rows = 0;                     // sum of nb over the nodes
-  DevBuf X, Z, U;                      // solve work, sized for cap_rhs
+  SolveWork<DevBuf> work;              // vectors of the solves
   DevBuf P;                            // split-K partial sums of the U12 products
-  int cap_rhs = 0;
   size_t bytes = 0;
   double flops = 0.0;
 };
@@ -2358,21 +2358,16 @@ ls_status solve_numeric(GpuSolver& g, const C<double>* b, C<double>* xo, int nrh
     if (nks[dep] > 1)
       pelems = std::max(pelems, (size_t)g.levels[dep].size() * nks[dep] * (size_t)g.lvl_np[dep] * nrhs);
   }
-  if (g.cap_rhs < nrhs) {
-    LS_TRY(g.X.alloc(2 * (size_t)g.N * nrhs * sizeof(R)));
-    LS_TRY(g.Z.alloc(2 * (size_t)g.N * nrhs * sizeof(R)));
-    LS_TRY(g.U.alloc(2 * (size_t)std::max(1L, g.u_rows) * nrhs * sizeof(R)));
-    g.cap_rhs = nrhs;
-  }
+  LS_TRY(g.work.reserve(nrhs, 2 * (size_t)g.N * sizeof(R), 2 * (size_t)std::max(1L, g.u_rows) * sizeof(R)));
   if (g.P.bytes < 2 * pelems * sizeof(R)) LS_TRY(g.P.alloc(2 * pelems * sizeof(R)));
   R* Pr = g.P.as<R>();
   R* Pi = Pr + pelems;
   const long N = g.N;
-  R* Xr = g.X.as<R>();
+  R* Xr = g.work.X.as<R>();
   R* Xi = Xr + N * nrhs;
-  R* Zr = g.Z.as<R>();
+  R* Zr = g.work.Z.as<R>();
   R* Zi = Zr + N * nrhs;
-  R* Ur = g.U.as<R>();
+  R* Ur = g.work.U.as<R>();
   R* Ui = Ur + std::max(1L, g.u_rows) * nrhs;
   const FrontDev* fr = g.fd.as<FrontDev>();
   const int* ib = g.ib.as<int>();
