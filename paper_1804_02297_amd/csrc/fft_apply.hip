@@ -33,6 +33,7 @@
 #include <cstdio>
 #include <vector>
 
+#include "buffers.h"
 #include "common.h"
 #include "fft_kernels.h"
 
@@ -291,13 +292,13 @@ ls_status apply_plan_set_form(ApplyPlan& ap, int form, hipStream_t s) {
   if (form == 1 && !ap.kp64.p) {
     const int n = ap.n, P = ap.P, H = ap.H;
     const long n3 = (long)n * n * n, H3 = (long)H * H * H;
-    LS_TRY(ap.kp64.alloc(H3 * 4 * sizeof(C<double>)));
-    LS_TRY(ap.kp32.alloc(H3 * 4 * sizeof(C<float>)));
-    LS_TRY(ap.p64.alloc(3 * n3 * sizeof(C<double>)));
-    LS_TRY(ap.p32.alloc(3 * n3 * sizeof(C<float>)));
-    // FP64 sizes: X1 and X2 of four fields and W of one, per rhs
+    // FP64 sizes of the workspace: X1 and X2 of four fields and W of one, per rhs
     const size_t per = apply_work_bytes(ap, LS_C128, 4) + (size_t)n3 * sizeof(C<double>);
-    LS_TRY(ap.work34.alloc(per * (size_t)ap.max_rhs));
+    LS_TRY(alloc_all<DevBuf>({{&ap.kp64, H3 * 4 * sizeof(C<double>)},
+                              {&ap.kp32, H3 * 4 * sizeof(C<float>)},
+                              {&ap.p64, 3 * n3 * sizeof(C<double>)},
+                              {&ap.p32, 3 * n3 * sizeof(C<float>)},
+                              {&ap.work34, per * (size_t)ap.max_rhs}}));
     hipLaunchKernelGGL(gradient_p_kernel, dim3((unsigned)((n3 + 255) / 256)), dim3(256), 0, s,
                        ap.m64.as<C<double>>(), n, ap.h, ap.p64.as<C<double>>(), ap.p32.as<C<float>>());
     LS_HIP(hipGetLastError());

@@ -33,6 +33,7 @@
 // update of the rows below (pivot rows in place, boundary rows into the
 // node's update vector).  Backward from the root: subtract U12 x_boundary,
 // then per tile (last first) x = U^-1 z and the update of the rows above.
+#include "buffers.h"
 #include "gpu_solver.h"
 #include "gpu_symbolic.h"
 
@@ -49,7 +50,6 @@
 #include <vector>
 
 #include "nd_tree.h"
-#include "solve_work.h"
 
 namespace ls {
 

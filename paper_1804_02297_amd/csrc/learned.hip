@@ -293,8 +293,7 @@ ls_status mlp_add_samples(MlpState& st, StencilData& sd, int n, double k, const 
     added += cg;
   }
   LS_HIP(hipStreamSynchronize(s));
-  st.nsamples += added;
-  sd.have_point = false;      // palpha now holds a partial fit: not a usable per-point stencil set
+  st.nsamples += added;       // sd.have_point stays false: palpha holds a partial fit, not a usable stencil set
   return LS_OK;
 }
 

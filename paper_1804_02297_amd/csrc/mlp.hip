@@ -27,6 +27,7 @@
 #include <string>
 #include <vector>
 
+#include "buffers.h"
 #include "common.h"
 #include "mlp.h"
 
@@ -452,11 +453,10 @@ ls_status mlp_refresh_bf16(MlpState& st, hipStream_t s) {
 ls_status mlp_infer(MlpState& st, const unsigned short* xb, int Bm, hipStream_t s) {
   LS_TRY(mlp_workspace(st, Bm));
   if (st.fver != st.wver) {
-    if (!st.w1f.p) {
-      LS_TRY(st.w1f.alloc((size_t)MLP_IP * MLP_H * 2));
-      LS_TRY(st.w2f.alloc((size_t)MLP_H * MLP_H * 2));
-      LS_TRY(st.w3f.alloc((size_t)MLP_H * MLP_OP * 2));
-    }
+    if (!st.w1f.p)
+      LS_TRY(alloc_all<DevBuf>({{&st.w1f, (size_t)MLP_IP * MLP_H * 2},
+                                {&st.w2f, (size_t)MLP_H * MLP_H * 2},
+                                {&st.w3f, (size_t)MLP_H * MLP_OP * 2}}));
     hipLaunchKernelGGL(frag_bf16_kernel, dim3(nbk((long)MLP_IP * MLP_H, 256)), dim3(256), 0, s,
                        st.w1b.as<unsigned short>(), MLP_H, st.w1f.as<unsigned short>());
     hipLaunchKernelGGL(frag_bf16_kernel, dim3(nbk((long)MLP_H * MLP_H, 256)), dim3(256), 0, s,
@@ -476,19 +476,20 @@ ls_status mlp_infer(MlpState& st, const unsigned short* xb, int Bm, hipStream_t 
 
 ls_status mlp_workspace(MlpState& st, int Bm) {
   if (st.ws_rows >= Bm) return LS_OK;
-  LS_TRY(st.z1.alloc((size_t)Bm * MLP_H * 4));
-  LS_TRY(st.z2.alloc((size_t)Bm * MLP_H * 4));
-  LS_TRY(st.h1b.alloc((size_t)Bm * MLP_H * 2));
-  LS_TRY(st.h2b.alloc((size_t)Bm * MLP_H * 2));
-  LS_TRY(st.y.alloc((size_t)Bm * MLP_OP * 4));
-  LS_TRY(st.dyb.alloc((size_t)Bm * MLP_OP * 2));
-  LS_TRY(st.dz2.alloc((size_t)Bm * MLP_H * 4));
-  LS_TRY(st.dz2b.alloc((size_t)Bm * MLP_H * 2));
-  LS_TRY(st.dz1.alloc((size_t)Bm * MLP_H * 4));
-  LS_TRY(st.dz1b.alloc((size_t)Bm * MLP_H * 2));
-  LS_TRY(st.dw.alloc((size_t)kGradSplit * MLP_IP * MLP_OP * 4));
-  LS_TRY(st.sq.alloc(256 * 4));
-  LS_TRY(st.part.alloc((size_t)kColChunks * MLP_OP * 4));
+  st.ws_rows = 0;                      // until all are there
+  LS_TRY(alloc_all<DevBuf>({{&st.z1, (size_t)Bm * MLP_H * 4},
+                            {&st.z2, (size_t)Bm * MLP_H * 4},
+                            {&st.h1b, (size_t)Bm * MLP_H * 2},
+                            {&st.h2b, (size_t)Bm * MLP_H * 2},
+                            {&st.y, (size_t)Bm * MLP_OP * 4},
+                            {&st.dyb, (size_t)Bm * MLP_OP * 2},
+                            {&st.dz2, (size_t)Bm * MLP_H * 4},
+                            {&st.dz2b, (size_t)Bm * MLP_H * 2},
+                            {&st.dz1, (size_t)Bm * MLP_H * 4},
+                            {&st.dz1b, (size_t)Bm * MLP_H * 2},
+                            {&st.dw, (size_t)kGradSplit * MLP_IP * MLP_OP * 4},
+                            {&st.sq, (size_t)256 * 4},
+                            {&st.part, (size_t)kColChunks * MLP_OP * 4}}));
   st.ws_rows = Bm;
   return LS_OK;
 }

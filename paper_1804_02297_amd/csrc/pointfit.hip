@@ -22,6 +22,7 @@
 //                        class Ritz vectors as dense triangular products,
 //                        Rayleigh-Ritz with a lane-parallel 8x8 Jacobi
 //   point_beta_kernel  : beta_p = B^H alpha_p
+#include "buffers.h"
 #include "common.h"
 #include "kernel_eval.h"
 #include "pointfit.h"
@@ -628,9 +629,10 @@ ls_status point_fit(StencilData& sd, int n, double k, const C<double>* m, double
   if (!sd.have_class || n < 4 || !(m0 > 0.0)) return LS_ESTATE;
   const double h = 1.0 / (n + 1);
   const long n3 = (long)n * n * n;
-  LS_TRY(sd.palpha.alloc((size_t)n3 * 243 * sizeof(C<double>)));
-  LS_TRY(sd.pbeta.alloc((size_t)n3 * 243 * sizeof(C<double>)));
-  LS_TRY(sd.peval.alloc((size_t)n3 * 3 * sizeof(double)));
+  sd.have_point = false;      // until the fit is complete
+  LS_TRY(alloc_all<DevBuf>({{&sd.palpha, (size_t)n3 * 243 * sizeof(C<double>)},
+                            {&sd.pbeta, (size_t)n3 * 243 * sizeof(C<double>)},
+                            {&sd.peval, (size_t)n3 * 3 * sizeof(double)}}));
   LS_HIP(hipMemsetAsync(sd.peval.p, 0, sd.peval.bytes, s));
   hipLaunchKernelGGL(broadcast_class_kernel, dim3(nb(n3 * 243, 256)), dim3(256), 0, s, n, sd.alpha.as<C<double>>(),
                      sd.beta.as<C<double>>(), sd.palpha.as<C<double>>(), sd.pbeta.as<C<double>>());
@@ -690,9 +692,10 @@ ls_status pointfit_prepare(PointFitCtx& ctx, StencilData& sd, int n, double k, i
   const long n3 = (long)n * n * n;
   ctx.n = n;
   ctx.batch = batch;
-  LS_TRY(sd.palpha.alloc((size_t)n3 * 243 * sizeof(C<double>)));
-  LS_TRY(sd.pbeta.alloc((size_t)n3 * 243 * sizeof(C<double>)));
-  LS_TRY(sd.peval.alloc((size_t)n3 * 3 * sizeof(double)));
+  sd.have_point = false;      // until the fit is complete
+  LS_TRY(alloc_all<DevBuf>({{&sd.palpha, (size_t)n3 * 243 * sizeof(C<double>)},
+                            {&sd.pbeta, (size_t)n3 * 243 * sizeof(C<double>)},
+                            {&sd.peval, (size_t)n3 * 3 * sizeof(double)}}));
   LS_HIP(hipMemsetAsync(sd.peval.p, 0, sd.peval.bytes, s));
   hipLaunchKernelGGL(broadcast_class_kernel, dim3(nb(n3 * 243, 256)), dim3(256), 0, s, n, sd.alpha.as<C<double>>(),
                      sd.beta.as<C<double>>(), sd.palpha.as<C<double>>(), sd.pbeta.as<C<double>>());

@@ -3,7 +3,7 @@
 #include <cstdlib>
 #include <initializer_list>
 
-#include "solve_work.h"
+#include "buffers.h"
 
 namespace {
 
@@ -13,7 +13,7 @@ void check(bool ok, const char* what) {
   failures += !ok;
 }
 
-// ---- solve work ----------------------------------------------------------------
+// ---- buffers that belong together ----------------------------------------------------------------
 
 int allocations_left = 1 << 30;   // how many more succeed
 
@@ -23,16 +23,29 @@ struct HostBuf {
   HostBuf() = default;
   HostBuf(const HostBuf&) = delete;
   ~HostBuf() { std::free(p); }
-  ls_status alloc(size_t b) {
+  void release() {
     std::free(p);
     p = nullptr;
     bytes = 0;
+  }
+  ls_status alloc(size_t b) {
+    release();
     if (allocations_left-- <= 0) return LS_ENOMEM;
     p = std::malloc(b);
     bytes = b;
     return LS_OK;
   }
 };
+
+// A group whose fail-th allocation fails leaves no buffer, as a caller that looks at any one of them has to find it.
+void group_is_all_or_nothing(int fail) {
+  HostBuf a, b, c;
+  const auto group = [&](size_t n) { return ls::alloc_all<HostBuf>({{&a, n}, {&b, 2 * n}, {&c, 3 * n}}); };
+  allocations_left = 1 << 30;
+  check(group(8) == LS_OK && a.bytes == 8 && b.bytes == 16 && c.bytes == 24, "a group that fits");
+  allocations_left = fail;
+  check(group(16) == LS_ENOMEM && !a.p && !b.p && !c.p, "a group that does not: nothing held");
+}
 
 // After a growth whose fail-th allocation fails, a smaller request (which the old buffers
 // would have held) either finds all three buffers large enough or is refused.
@@ -53,7 +66,10 @@ void solve_work_after_a_failed_growth(int fail) {
 }  // namespace
 
 int main() {
-  for (int fail = 0; fail < 3; ++fail) solve_work_after_a_failed_growth(fail);
+  for (int fail = 0; fail < 3; ++fail) {
+    group_is_all_or_nothing(fail);
+    solve_work_after_a_failed_growth(fail);
+  }
   std::printf(failures ? "FAILED %d\n" : "ALL OK\n", failures);
   return failures ? 1 : 0;
 }

@@ -1,6 +1,6 @@
 """The library's device-memory bookkeeping on a pretended device (CPU only).
 
-tests/sanitize/memory_driver.cpp runs csrc/solve_work.h against an allocator
+tests/sanitize/memory_driver.cpp runs csrc/buffers.h against an allocator
 that can run out, under AddressSanitizer and UndefinedBehaviorSanitizer.
 """
 import os
