@@ -2,14 +2,27 @@
 #include <cstdio>
 #include <cstdlib>
 #include <initializer_list>
+#include <new>
+#include <set>
 
 #include "buffers.h"
+#include "devstore.h"
+
+// host memory that can be made to run out
+static thread_local bool host_memory = true;
+void* operator new(size_t n) {
+  void* p = host_memory ? std::malloc(n) : nullptr;
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void* p) noexcept { std::free(p); }
+void operator delete(void* p, size_t) noexcept { std::free(p); }
 
 namespace {
 
 int failures = 0;
 void check(bool ok, const char* what) {
-  std::printf("%s: %s\n", ok ? "ok" : "FAILED", what);
+  if (!ok) std::printf("FAILED: %s\n", what);
   failures += !ok;
 }
 
@@ -63,9 +76,94 @@ void solve_work_after_a_failed_growth(int fail) {
   for (int n : {4, 1, 16}) check(w.reserve(n, vec, upd) == LS_OK && holds(n), "memory again: all three there");
 }
 
+// ---- the store of released blocks ------------------------------------------------
+
+// A pretended card of `room` bytes.
+struct Card {
+  size_t room = 1 << 20, used = 0;
+  std::set<void*> live;
+  ~Card() {
+    for (void* p : live) std::free(p);
+  }
+};
+struct CardDev {
+  Card* card;
+  int dev = 0;
+  bool current(int* d) const { return *d = dev, true; }
+  void* alloc(size_t n) {
+    if (card->used + n > card->room) return nullptr;
+    size_t* p = static_cast<size_t*>(std::malloc(sizeof(size_t) + n));
+    *p = n;
+    card->used += n;
+    card->live.insert(p);
+    return p;
+  }
+  void free(void* q) {
+    size_t* p = static_cast<size_t*>(q);
+    check(card->live.erase(p) == 1, "freed once");
+    card->used -= *p;
+    std::free(p);
+  }
+  bool wait(int d) const { return d == dev; }
+};
+using Store = ls::BlockStore<CardDev>;
+constexpr std::chrono::milliseconds kLong(60000);
+
+// A destructor gives a buffer back: that works, and throws nothing, without host memory.
+void give_without_host_memory() {
+  Card card;
+  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, kLong});
+  size_t got[100];
+  int dev;
+  void* p[100];
+  for (int i = 0; i < 100; ++i) p[i] = s.take(40, &got[i], &dev);
+  host_memory = false;
+  for (int i = 0; i < 100; ++i) [&]() noexcept { s.give(p[i], got[i], dev); }();
+  host_memory = true;
+  check(card.used <= 4096 && card.used >= 40, "blocks held within the bound");
+  for (int i = 0; i < 200; ++i) p[0] = s.take(4 + i % 60, &got[0], &dev), s.give(p[0], got[0], dev);
+  check(card.used <= 4096, "within the bound after many sizes");
+}
+
+// The oldest go first, a block serves requests of at least 4/5 of its size, and an allocation
+// that fails has everything held given back.
+void bounds_of_the_store() {
+  Card card;
+  Store s(CardDev{&card}, ls::StoreLimits{16, 1000, kLong});
+  size_t got;
+  int dev;
+  void* a = s.take(400, &got, &dev);
+  void* b = s.take(500, &got, &dev);
+  void* c = s.take(300, &got, &dev);
+  void* d = s.take(1001, &got, &dev);
+  void* e = s.take(15, &got, &dev);
+  s.give(a, 400, 0);
+  s.give(b, 500, 0);
+  check(card.used == 2216, "two held");
+  s.give(c, 300, 0);
+  check(card.used == 1816, "the oldest is freed past the bound");
+  s.give(d, 1001, 0);
+  s.give(e, 15, 0);
+  check(card.used == 800, "too large and too small ones are not held");
+  void* x = s.take(399, &got, &dev);
+  check(x != b && got == 399 && card.used == 1199, "a block of more than 5/4 does not serve");
+  void* y = s.take(400, &got, &dev);
+  check(y == b && got == 500, "one of 5/4 does");
+  s.give(y, got, 1);
+  check(card.used == 699, "not held while another device is current");
+  s.give(x, 399, 0);
+  check(card.used == 699, "held again");
+  void* z = s.take(card.room, &got, &dev);
+  check(z && card.used == card.room, "an allocation that failed had the store drained");
+  check(!s.take(16, &got, &dev), "no memory");
+  s.give(z, card.room, 0);
+}
+
 }  // namespace
 
 int main() {
+  give_without_host_memory();
+  bounds_of_the_store();
   for (int fail = 0; fail < 3; ++fail) {
     group_is_all_or_nothing(fail);
     solve_work_after_a_failed_growth(fail);

@@ -1,7 +1,8 @@
 """The library's device-memory bookkeeping on a pretended device (CPU only).
 
-tests/sanitize/memory_driver.cpp runs csrc/buffers.h against an allocator
-that can run out, under AddressSanitizer and UndefinedBehaviorSanitizer.
+tests/sanitize/memory_driver.cpp runs csrc/buffers.h and csrc/devstore.h
+against allocators that can run out, under AddressSanitizer and
+UndefinedBehaviorSanitizer.
 """
 import os
 import subprocess
