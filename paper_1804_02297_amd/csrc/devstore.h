@@ -2,6 +2,7 @@
 #pragma once
 
 #include <chrono>
+#include <condition_variable>
 #include <cstddef>
 #include <mutex>
 
@@ -22,7 +23,8 @@ class BlockStore {
   BlockStore(Dev dev, StoreLimits lim) : dev_(dev), lim_(lim) {}
 
   // At least `bytes` on the current device: a held block of at most 5/4 of that, the smallest that
-  // fits, or a new one.  When none can be had, every held block goes back and it is tried once more.
+  // fits, or a new one.  When none can be had, every held block goes back, what other threads are
+  // giving back is waited for, and it is tried once more.
   void* take(size_t bytes, size_t* got, int* dev) {
     if (!dev_.current(dev)) return nullptr;
     void* p = nullptr;
@@ -48,13 +50,15 @@ class BlockStore {
     *got = bytes;
     p = dev_.alloc(bytes);
     if (p) return p;
-    out.n = 0;
     {
       std::lock_guard<std::mutex> lock(mu_);
       while (n_) oldest_to(out);
     }
-    if (!out.n) return nullptr;
     free_all(out);
+    {
+      std::unique_lock<std::mutex> lock(mu_);
+      freed_.wait(lock, [this] { return freeing_ == 0; });
+    }
     return dev_.alloc(bytes);
   }
 
@@ -97,13 +101,19 @@ class BlockStore {
   void oldest_to(Gone& out) {
     out.p[out.n++] = held_[0].p;
     drop(0);
+    ++freeing_;
   }
   void expired(Gone& out) {
     const auto now = Clock::now();
     while (n_ && now - held_[0].since > lim_.idle) oldest_to(out);
   }
-  void free_all(const Gone& out) {
+  void free_all(Gone& out) {
+    if (!out.n) return;
     for (int i = 0; i < out.n; ++i) dev_.free(out.p[i]);
+    std::lock_guard<std::mutex> lock(mu_);
+    freeing_ -= out.n;
+    out.n = 0;
+    freed_.notify_all();
   }
 
   Dev dev_;
@@ -112,6 +122,8 @@ class BlockStore {
   Block held_[kSlots];                 // oldest first
   int n_ = 0;
   size_t bytes_ = 0;
+  int freeing_ = 0;                    // blocks taken out of the store and not yet freed
+  std::condition_variable freed_;
 };
 
 }  // namespace ls

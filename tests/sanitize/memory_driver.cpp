@@ -1,15 +1,22 @@
 // Device-memory bookkeeping of the library on a pretended device (host memory that can run out).
+#include <atomic>
+#include <chrono>
 #include <cstdio>
 #include <cstdlib>
+#include <functional>
 #include <initializer_list>
+#include <mutex>
 #include <new>
 #include <set>
+#include <thread>
+#include <vector>
 
 #include "buffers.h"
 #include "devstore.h"
 
-// host memory that can be made to run out
+// host memory that can be made to run out (ThreadSanitizer brings its own operator new)
 static thread_local bool host_memory = true;
+#if !__has_feature(thread_sanitizer)
 void* operator new(size_t n) {
   void* p = host_memory ? std::malloc(n) : nullptr;
   if (!p) throw std::bad_alloc();
@@ -17,10 +24,11 @@ void* operator new(size_t n) {
 }
 void operator delete(void* p) noexcept { std::free(p); }
 void operator delete(void* p, size_t) noexcept { std::free(p); }
+#endif
 
 namespace {
 
-int failures = 0;
+std::atomic<int> failures{0};
 void check(bool ok, const char* what) {
   if (!ok) std::printf("FAILED: %s\n", what);
   failures += !ok;
@@ -80,8 +88,12 @@ void solve_work_after_a_failed_growth(int fail) {
 
 // A pretended card of `room` bytes.
 struct Card {
-  size_t room = 1 << 20, used = 0;
+  size_t room = 1 << 20;
+  std::atomic<size_t> used{0};
+  std::atomic<int> refused{0};          // allocations that did not fit
   std::set<void*> live;
+  std::mutex mu;
+  std::function<void()> on_free;        // runs before a block goes
   ~Card() {
     for (void* p : live) std::free(p);
   }
@@ -91,7 +103,8 @@ struct CardDev {
   int dev = 0;
   bool current(int* d) const { return *d = dev, true; }
   void* alloc(size_t n) {
-    if (card->used + n > card->room) return nullptr;
+    std::lock_guard<std::mutex> lock(card->mu);
+    if (card->used + n > card->room) return ++card->refused, nullptr;
     size_t* p = static_cast<size_t*>(std::malloc(sizeof(size_t) + n));
     *p = n;
     card->used += n;
@@ -100,6 +113,8 @@ struct CardDev {
   }
   void free(void* q) {
     size_t* p = static_cast<size_t*>(q);
+    if (card->on_free) card->on_free();
+    std::lock_guard<std::mutex> lock(card->mu);
     check(card->live.erase(p) == 1, "freed once");
     card->used -= *p;
     std::free(p);
@@ -159,15 +174,61 @@ void bounds_of_the_store() {
   s.give(z, card.room, 0);
 }
 
+// An allocation that fails while another thread is giving the held blocks back waits for them.
+void allocation_during_a_drain() {
+  Card card;
+  card.room = 1000;
+  Store s(CardDev{&card}, ls::StoreLimits{16, 1000, kLong});
+  size_t got, got2;
+  int dev, dev2;
+  s.give(s.take(900, &got, &dev), got, dev);
+  std::atomic<bool> draining{false};
+  card.on_free = [&] {
+    draining = true;
+    while (card.refused < 2) std::this_thread::yield();          // until the other thread was refused
+    std::this_thread::sleep_for(std::chrono::milliseconds(50));
+  };
+  void* a = nullptr;
+  std::thread t([&] { a = s.take(600, &got, &dev); });
+  while (!draining) std::this_thread::yield();
+  void* b = s.take(200, &got2, &dev2);
+  t.join();
+  card.on_free = nullptr;
+  check(a && b && card.used == 800, "both threads have their blocks");
+}
+
+// Threads that take and give at once: every block is one thread's alone.
+void many_threads() {
+  Card card;
+  Store s(CardDev{&card}, ls::StoreLimits{16, 3000, kLong});
+  std::vector<std::thread> ts;
+  for (int t = 0; t < 4; ++t)
+    ts.emplace_back([&s, t] {
+      for (int i = 0; i < 2000; ++i) {
+        size_t got;
+        int dev;
+        unsigned char* p = static_cast<unsigned char*>(s.take(8 + 37 * (i % 29), &got, &dev)) + sizeof(size_t);
+        p[0] = p[7] = (unsigned char)t;
+        std::this_thread::yield();
+        check(p[0] == t && p[7] == t, "nobody else writes to a block");
+        s.give(p - sizeof(size_t), got, dev);
+      }
+    });
+  for (auto& t : ts) t.join();
+  check(card.used <= 3000, "within the bound");
+}
+
 }  // namespace
 
 int main() {
+  allocation_during_a_drain();
+  many_threads();
   give_without_host_memory();
   bounds_of_the_store();
   for (int fail = 0; fail < 3; ++fail) {
     group_is_all_or_nothing(fail);
     solve_work_after_a_failed_growth(fail);
   }
-  std::printf(failures ? "FAILED %d\n" : "ALL OK\n", failures);
+  std::printf(failures ? "FAILED %d\n" : "ALL OK\n", failures.load());
   return failures ? 1 : 0;
 }

@@ -1,8 +1,8 @@
 """The library's device-memory bookkeeping on a pretended device (CPU only).
 
 tests/sanitize/memory_driver.cpp runs csrc/buffers.h and csrc/devstore.h
-against allocators that can run out, under AddressSanitizer and
-UndefinedBehaviorSanitizer.
+against allocators that can run out, with several threads, under
+AddressSanitizer and UndefinedBehaviorSanitizer and under ThreadSanitizer.
 """
 import os
 import subprocess
@@ -32,3 +32,8 @@ def test_under_address_and_undefined_behaviour_sanitizers(tmp_path):
     r = _run(tmp_path, "memory_asan", ["-fsanitize=address,undefined", "-fno-sanitize-recover=undefined"],
              {"ASAN_OPTIONS": "detect_leaks=1"})
     assert "runtime error" not in r.stderr and "ERROR: AddressSanitizer" not in r.stderr
+
+
+def test_under_thread_sanitizer(tmp_path):
+    r = _run(tmp_path, "memory_tsan", ["-fsanitize=thread"], {})
+    assert "ThreadSanitizer" not in r.stderr, r.stderr[-3000:]
