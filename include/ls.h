@@ -23,6 +23,12 @@
  * HIP stream passed in (NULL = the default stream); the calls that do host
  * work synchronise that stream before they return.
  *
+ * Device memory: buffers of 1 MiB and more that the library releases (a
+ * destroyed plan's, the fronts of a factorisation) are kept for its next
+ * allocations for up to 5 seconds, at most 8 GiB and a sixteenth of the
+ * memory that is free on the device; then they are freed, without any further
+ * call.  ls_release_memory frees them at once.
+ *
  * Every call returns an ls_status.  On an error the outputs are unspecified,
  * except LS_ENOCONV, where x holds the last iterate and info is filled.
  */
@@ -362,6 +368,10 @@ ls_status ls_plan_set_form(ls_plan* plan, ls_form form, void* hip_stream);
 int ls_plan_fft_size(const ls_plan* plan);
 
 void ls_plan_destroy(ls_plan* plan);
+
+/* Free the device memory that the library holds from released buffers (see
+ * above).  Live plans, factors and networks keep theirs.  Any thread. */
+void ls_release_memory(void);
 const char* ls_status_string(ls_status s);
 
 #ifdef __cplusplus

@@ -75,6 +75,7 @@ SIGNATURES = [
     ("ls_plan_set_form", _I, [_VP, _I, _VP]),
     ("ls_plan_tune", _I, [_VP, _I, _I, _VP, _VP]), ("ls_plan_set_tune", _I, [_VP, _I, _I, _I, _I, _I]),
     ("ls_plan_destroy", None, [_VP]),
+    ("ls_release_memory", None, []),
     # the 2-D variant
     ("ls2_plan_create", _I, [_I, _D, _I, _VP, _VP, ctypes.POINTER(_VP)]),
     ("ls2_apply", _I, [_VP, _VP, _VP, _I, _I, _VP]),
@@ -307,6 +308,11 @@ def hbm_copy(dst, src, nbytes: int):
     load()
     _check(_lib.ls_hbm_copy(ctypes.c_void_p(dst.data_ptr()), ctypes.c_void_p(src.data_ptr()), nbytes, _stream()),
            "ls_hbm_copy")
+
+
+def release_memory():
+    """Free the device memory that the library holds from released buffers."""
+    load().ls_release_memory()
 
 
 def _ptr(t):

@@ -1,4 +1,7 @@
 // Device-memory bookkeeping of the library on a pretended device (host memory that can run out).
+#include <sys/wait.h>
+#include <unistd.h>
+
 #include <atomic>
 #include <chrono>
 #include <cstdio>
@@ -88,7 +91,7 @@ void solve_work_after_a_failed_growth(int fail) {
 
 // A pretended card of `room` bytes.
 struct Card {
-  size_t room = 1 << 20;
+  size_t room = 1 << 20, spare = 1 << 20;   // in all; what the card says is free
   std::atomic<size_t> used{0};
   std::atomic<int> refused{0};          // allocations that did not fit
   std::set<void*> live;
@@ -120,6 +123,8 @@ struct CardDev {
     std::free(p);
   }
   bool wait(int d) const { return d == dev; }
+  size_t spare() const { return card->spare; }
+  static void enter() {}
 };
 using Store = ls::BlockStore<CardDev>;
 constexpr std::chrono::milliseconds kLong(60000);
@@ -127,10 +132,10 @@ constexpr std::chrono::milliseconds kLong(60000);
 // A destructor gives a buffer back: that works, and throws nothing, without host memory.
 void give_without_host_memory() {
   Card card;
-  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, kLong});
+  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, 1, kLong});
   size_t got[100];
   int dev;
-  void* p[100];
+  void* p[100];                         // (the first take starts the store's thread)
   for (int i = 0; i < 100; ++i) p[i] = s.take(40, &got[i], &dev);
   host_memory = false;
   for (int i = 0; i < 100; ++i) [&]() noexcept { s.give(p[i], got[i], dev); }();
@@ -144,7 +149,7 @@ void give_without_host_memory() {
 // that fails has everything held given back.
 void bounds_of_the_store() {
   Card card;
-  Store s(CardDev{&card}, ls::StoreLimits{16, 1000, kLong});
+  Store s(CardDev{&card}, ls::StoreLimits{16, 1000, 1, kLong});
   size_t got;
   int dev;
   void* a = s.take(400, &got, &dev);
@@ -174,33 +179,118 @@ void bounds_of_the_store() {
   s.give(z, card.room, 0);
 }
 
+bool comes_true(const std::function<bool()>& f) {
+  for (int i = 0; i < 2000; ++i) {
+    if (f()) return true;
+    std::this_thread::sleep_for(std::chrono::milliseconds(5));
+  }
+  return false;
+}
+
 // An allocation that fails while another thread is giving the held blocks back waits for them.
 void allocation_during_a_drain() {
   Card card;
   card.room = 1000;
-  Store s(CardDev{&card}, ls::StoreLimits{16, 1000, kLong});
+  Store s(CardDev{&card}, ls::StoreLimits{16, 1000, 1, kLong});
   size_t got, got2;
   int dev, dev2;
   s.give(s.take(900, &got, &dev), got, dev);
   std::atomic<bool> draining{false};
   card.on_free = [&] {
     draining = true;
-    while (card.refused < 2) std::this_thread::yield();          // until the other thread was refused
+    comes_true([&] { return card.refused >= 2; });              // the other thread was refused
     std::this_thread::sleep_for(std::chrono::milliseconds(50));
   };
   void* a = nullptr;
   std::thread t([&] { a = s.take(600, &got, &dev); });
-  while (!draining) std::this_thread::yield();
+  check(comes_true([&] { return draining.load(); }), "the first thread drains the store");
   void* b = s.take(200, &got2, &dev2);
   t.join();
   card.on_free = nullptr;
   check(a && b && card.used == 800, "both threads have their blocks");
 }
 
+// A block that nobody takes again goes back without any further call, and one that is taken in time stays.
+void given_back_when_idle() {
+  Card card;
+  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, 1, std::chrono::milliseconds(200)});
+  size_t got, got2;
+  int dev;
+  void *p = s.take(1000, &got, &dev), *q = s.take(500, &got2, &dev);
+  s.give(p, got, dev);
+  s.give(q, got2, dev);
+  check(card.used == 1500, "held at first");
+  check(comes_true([&] { return card.used == 0; }), "given back with no call");
+  p = s.take(1000, &got, &dev);
+  s.give(p, got, dev);
+  for (int i = 0; i < 10; ++i) {
+    void* r = s.take(1000, &got, &dev);
+    check(r == p, "reused");
+    std::this_thread::sleep_for(std::chrono::milliseconds(50));
+    s.give(r, got, dev);
+  }
+  check(comes_true([&] { return card.used == 0; }), "given back again");
+}
+
+// What is held leaves most of a nearly full card to others; release() and stop() leave nothing.
+void given_back_on_request() {
+  Card card;
+  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, 4, kLong});
+  size_t got;
+  int dev;
+  void* a = s.take(1000, &got, &dev);
+  void* b = s.take(1000, &got, &dev);
+  card.spare = 3999;
+  s.give(a, 1000, 0);
+  check(card.used == 1000, "more than a quarter of what is free: not held");
+  card.spare = 4000;
+  s.give(b, 1000, 0);
+  check(card.used == 1000, "a quarter: held");
+  s.release();
+  check(card.used == 0, "release");
+  b = s.take(1000, &got, &dev);
+  s.stop();
+  s.give(b, got, 0);
+  check(card.used == 0, "nothing held after stop");
+}
+
+// A forked child, which has no thread to free blocks, holds none and ends as usual.
+void forked_child() {
+#if !__has_feature(thread_sanitizer)
+  static Card card;
+  const auto get = []() -> Store& {
+    return ls::ProcessStore<CardDev>::get(CardDev{&card}, ls::StoreLimits{16, 4096, 1, kLong});
+  };
+  size_t got, got2;
+  int dev;
+  void* p = get().take(100, &got, &dev);
+  void* q = get().take(200, &got2, &dev);
+  get().give(p, got, dev);
+  check(card.used == 300, "held in the parent");
+  std::fflush(stdout);
+  const pid_t pid = fork();
+  if (pid == 0) {
+    failures = 0;
+    get().give(q, got2, dev);
+    check(card.used == 100, "not held in the child");
+    get().give(get().take(300, &got, &dev), got, dev);
+    check(card.used == 100, "nor later");
+    get().release();
+    std::exit(failures ? 1 : 0);         // runs the exit handlers
+  }
+  int st = -1;
+  check(waitpid(pid, &st, 0) == pid && WIFEXITED(st) && WEXITSTATUS(st) == 0, "the child ends as usual");
+  get().give(q, got2, dev);
+  check(card.used == 300, "held in the parent after the fork");
+  get().release();
+  check(card.used == 0, "released in the parent");
+#endif
+}
+
 // Threads that take and give at once: every block is one thread's alone.
 void many_threads() {
   Card card;
-  Store s(CardDev{&card}, ls::StoreLimits{16, 3000, kLong});
+  Store s(CardDev{&card}, ls::StoreLimits{16, 3000, 1, kLong});
   std::vector<std::thread> ts;
   for (int t = 0; t < 4; ++t)
     ts.emplace_back([&s, t] {
@@ -222,6 +312,9 @@ void many_threads() {
 
 int main() {
   allocation_during_a_drain();
+  given_back_when_idle();
+  given_back_on_request();
+  forked_child();
   many_threads();
   give_without_host_memory();
   bounds_of_the_store();

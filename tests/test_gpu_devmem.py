@@ -2,6 +2,8 @@
 the buffers of destroyed plans (of other media, sizes and precisions) gives
 bit for bit what a plan on its own memory gave, and two live plans never share
 a buffer."""
+import time
+
 import numpy as np
 import pytest
 
@@ -37,3 +39,66 @@ def test_reused_buffers_leave_no_trace(lib, prec):
     assert not np.array_equal(zb.cpu().numpy(), keep[0])
     a.close()
     b.close()
+
+
+def _free():
+    torch.cuda.synchronize()
+    torch.cuda.empty_cache()
+    return torch.cuda.mem_get_info()[0]
+
+
+def _comes_back(level, seconds=30):
+    end = time.monotonic() + seconds
+    while _free() < level and time.monotonic() < end:
+        time.sleep(0.5)
+    return _free() >= level
+
+
+def test_memory_of_a_destroyed_plan_comes_back(lib):
+    """After a plan is destroyed its device memory is free again for the rest
+    of the process: without any further call, and at once on request."""
+    from paper_1804_02297_amd.binding import release_memory
+    n, prec = 24, "c128"
+    _solve(n, 1, prec)[0].close()               # code objects, scratch memory
+    release_memory()
+    before = _free()
+    for ask in (False, True):
+        plan, z, y = _solve(n, 2, prec)
+        del z, y
+        used = before - _free()
+        print(f"plan holds {used / 2**20:.0f} MiB", flush=True)
+        assert used >= 400 << 20
+        plan.close()
+        if ask:
+            release_memory()
+        assert _comes_back(before - used // 16, 1 if ask else 30)
+
+
+def test_memory_comes_back_during_capture(lib):
+    """Blocks that go back while this thread captures a graph: they do, and the
+    graph replays as the eager call."""
+    from paper_1804_02297_amd.binding import release_memory
+    n = 16
+    plan, _, _ = _solve(n, 1, "c128")
+    x = torch.from_numpy(I.random_field(2, n, 7)).to("cuda:0")
+    y, want = torch.empty_like(x), plan.apply(x)
+    _solve(24, 2, "c128")[0].close()
+    release_memory()
+    before = _free()
+    _solve(24, 2, "c128")[0].close()
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        plan.apply(x, y)
+        time.sleep(8)
+    assert _comes_back(before - (64 << 20))
+    for seed in (7, 8, 9):
+        x.copy_(torch.from_numpy(I.random_field(2, n, seed)))
+        y.zero_()
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(y, plan.apply(x)), seed
+    x.copy_(torch.from_numpy(I.random_field(2, n, 7)))
+    g.replay()
+    torch.cuda.synchronize()
+    assert torch.equal(y, want)
+    plan.close()
