@@ -366,6 +366,19 @@ __global__ void gradient_kernel(const C<double>* __restrict__ m, C<double>* __re
 template <typename T>
 __device__ __forceinline__ C<T> ld_c(const void* p, long i) { return reinterpret_cast<const C<T>*>(p)[i]; }
 
+// s v and a + s v of the symbol multiply with every rounding spelled out: left
+// to the compiler, which product of a sum goes into the fused multiply-add
+// differed between the column kernels, and a field's bits with the number of
+// fields in its launch.
+template <typename R>
+__device__ __forceinline__ C<R> sym_mul(C<R> s, C<R> v) {
+  return cmk<R>(fma(s.re, v.re, -(s.im * v.im)), fma(s.re, v.im, s.im * v.re));
+}
+template <typename R>
+__device__ __forceinline__ C<R> sym_add(C<R> s, C<R> v, C<R> a) {
+  return cmk<R>(fma(-s.im, v.im, fma(s.re, v.re, a.re)), fma(s.im, v.re, fma(s.re, v.im, a.im)));
+}
+
 // pass A: block w -> (rhs b, row block rb); the three fields of its rows in
 // turn, from x, m and p loaded once into registers.  FEW: one field per block
 // (w -> (b, rb, field)), for launches that leave most of the chip idle.
@@ -527,12 +540,12 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
         if constexpr (SPRE) s01 = sv[u];
         else s01 = symv(e, f == 2 ? 1 : 0);
         if (f == 0) {
-          o0[u] = s01 * v;
+          o0[u] = sym_mul(s01, v);
         } else if (f == 1) {
-          o1[u] = s01 * v;
+          o1[u] = sym_mul(s01, v);
         } else {
-          o0[u] = cfma(s01, v, o0[u]);
-          o1[u] = cfma(symv(e, 2), v, o1[u]);
+          o0[u] = sym_add(s01, v, o0[u]);
+          o1[u] = sym_add(symv(e, 2), v, o1[u]);
         }
       }
     }
@@ -564,8 +577,7 @@ __global__ __launch_bounds__(NTH) __attribute__((amdgpu_waves_per_eu(4, 8))) voi
 // pass B of one column and rhs per block, its three forward transforms run
 // together and then its two inverse ones: 2 nst stages with a barrier each
 // instead of 5 nst.  For launches of few columns, which wait for those stages
-// one after the other (few_columns).  At the FP32 register lengths its rounding
-// differs from pass_b_reg_kernel's.
+// one after the other (few_columns).  Rounds as pass_b_kernel does, bit for bit.
 template <typename R, int PT>
 __global__ __launch_bounds__(kT2) void pass_b_few_kernel(const C<R>* __restrict__ T, C<R>* __restrict__ T2,
                                                          const C<R>* __restrict__ symc, int n, int P_, int H,
@@ -606,8 +618,8 @@ __global__ __launch_bounds__(kT2) void pass_b_few_kernel(const C<R>* __restrict_
     const int q1 = threadIdx.x + kT2 * u;
     if (q1 < P) {
       const C<R> u0 = X[3 * q1], u1 = X[3 * q1 + 1], v = X[3 * q1 + 2];
-      Y[2 * q1] = cfma(sv[1][u], v, sv[0][u] * u0);
-      Y[2 * q1 + 1] = cfma(sv[2][u], v, sv[0][u] * u1);
+      Y[2 * q1] = sym_add(sv[1][u], v, sym_mul(sv[0][u], u0));
+      Y[2 * q1 + 1] = sym_add(sv[2][u], v, sym_mul(sv[0][u], u1));
     }
   }
   __syncthreads();
@@ -1026,11 +1038,14 @@ size_t lds_bytes(int P, int nb) { return (2 * (size_t)nb * P + tw_entries(P)) * 
 // there on (n = 239, 3 rhs) the two are equal.
 constexpr int kFewBlocks = 512;
 // Column launches of few columns take pass_b_few_kernel.  Fewer than 2048
-// columns, eight blocks per CU: n = 20 one rhs 29.7 to 20.3 us, n = 119 complex64
-// one rhs 19.9 to 15.2 and 6 rhs 23.6 to 20.5, n = 60 12 rhs 39.8 to 31.3 (complex64)
-// and 35.6 to 32.4.  And at most 2^20 elements, past which a column's
-// transforms occupy a workgroup by themselves: n = 239 4 rhs 42.0 to 39.1 and 55.4
-// to 51.4, n = 479 complex64 one rhs 50.6 to 47.5, but two rhs 59.6 to 71.6.
+// columns, eight blocks per CU: n = 20 one rhs 29.8 to 19.7 us a call, n = 119
+// complex64 one rhs 19.9 to 13.7 and 6 rhs 23.3 to 20.1, n = 60 12 rhs 39.6 to
+// 31.2 (complex64) and 35.7 to 32.4.  And at most 2^20 elements, past which a
+// column's transforms occupy a workgroup by themselves: n = 239 one rhs 27.8 to
+// 25.7 and 4 rhs 55.0 to 51.3, n = 300 2 rhs 62.1 to 51.8 (complex64) and 82.2
+// to 70.6.  Not at the FP32 lengths of pass_b_reg_kernel, whose four-step
+// transforms round otherwise: a field's bits would depend on how many others
+// share its launch (n = 239 complex64 one rhs 34.6 us, 20.6 with this kernel).
 inline bool few_columns(int P, int nr) { return (long)P * nr < 2048 && (long)P * P * nr <= 1 << 20; }
 
 template <typename R, typename IO, int PT>
@@ -1068,11 +1083,12 @@ ls_status run_apply_p(Plan2& pl, const void* x, void* y, int nrhs, bool minus_co
     LS_HIP(hipGetLastError());
     constexpr int EMAX = (int)(kLds2 / (2 * sizeof(C<R>)) / kTB);
     if (ev) LS_HIP(hipEventRecord(ev[1], s));
+    constexpr bool REG = std::is_same<R, float>::value && PT > 0 && ColRegCfg<(PT > 0 ? PT : 1)>::N1 > 0;
     const size_t ldsf = (6 * (size_t)P + tw_entries(P)) * sizeof(C<R>);
-    if (few_columns(P, nr) && ldsf <= kLds2) {
+    if (!REG && few_columns(P, nr) && ldsf <= kLds2) {
       hipLaunchKernelGGL((pass_b_few_kernel<R, PT>), dim3(P * nr), dim3(kT2), ldsf, s, T, T2, symc, n, P, pl.H, pl.rd, nr,
                          tw);
-    } else if constexpr (std::is_same<R, float>::value && PT > 0 && ColRegCfg<(PT > 0 ? PT : 1)>::N1 > 0) {
+    } else if constexpr (REG) {
       using Cfg = ColRegCfg<PT>;
       hipLaunchKernelGGL((pass_b_reg_kernel<PT>), dim3(((PT + Cfg::NB - 1) / Cfg::NB) * nr), dim3(Cfg::THREADS), 0, s, T,
                          T2, sym, n, pl.H, nr, tw);

@@ -264,3 +264,24 @@ def test_apply_few_and_many_columns(lib, n, nrhs, max_rhs):
     y = plan.apply(_dev(x.astype(np.complex64)), prec="c64").cpu().numpy()
     assert np.abs(y - ref).max() <= 2e-5 * scale
     plan.close()
+
+
+@pytest.mark.parametrize("n,nrhs,max_rhs", [(12, 90, 90), (60, 18, 18), (119, 17, 16), (120, 9, 9), (239, 5, 5), (243, 9, 4),
+                                            (300, 3, 3), (479, 3, 2), (486, 2, 2)])
+def test_apply_of_a_batch_equals_its_fields(lib, n, nrhs, max_rhs):
+    """A field's result does not depend on how many others share its launch,
+    bit for bit, in every precision: batches on either side of the route for
+    few columns (2048 columns, 2^20 elements), compiled and other lengths, and
+    a short last chunk, against each field alone."""
+    from paper_1804_02297_amd.binding import Plan2
+    plan = Plan2(n, I.paper_wavenumber(n), _dev(I.medium2_random_complex(n, 70 + n, scale=0.2)), max_rhs=max_rhs)
+    x = _dev(I.random_field2(nrhs, n, 600 + n))
+    bad = []
+    for prec in ("c128", "mixed", "c64"):
+        xp = x.to(torch.complex64) if prec == "c64" else x
+        y = plan.apply(xp, prec=prec)
+        bad += [(prec, i) for i in (0, nrhs // 2, nrhs - 1)
+                if not torch.equal(plan.apply(xp[i:i + 1].contiguous(), prec=prec), y[i:i + 1])]
+    print(f"n={n} P={plan.P} {bad}", flush=True)
+    assert not bad
+    plan.close()
