@@ -473,6 +473,8 @@ constexpr int kPR = 64;   // 256 threads load kPR x kT values in kT / 4 rounds
 // of the diagonal are formed once, and every load is in flight before the first
 // wait.  FP64, average launch of the n = 29 factor: 37 us (152 us with one
 // thread per row and the row in LDS).
+// A reciprocal is held as the sum of two values (recip): a product with the
+// rounded reciprocal alone has one rounding more per entry of L than a division.
 template <int Q>
 __device__ __forceinline__ float quad_bcast(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), Q * 0x55, 0xF, 0xF, false));
@@ -482,14 +484,28 @@ __device__ __forceinline__ double quad_bcast(double v) {
   return __hiloint2double(__builtin_amdgcn_mov_dpp(__double2hiint(v), Q * 0x55, 0xF, 0xF, false),
                           __builtin_amdgcn_mov_dpp(__double2loint(v), Q * 0x55, 0xF, 0xF, false));
 }
+// 1 / u to about twice the precision of R: g, and the rest h = g (1 - g u).
+template <typename R>
+__device__ __forceinline__ void recip(R ur, R ui, C<R>& g, C<R>& h) {
+#pragma clang fp contract(off)
+  const R den = ur * ur + ui * ui;
+  g = cmk(ur / den, -ui / den);
+  // 1 - g u: exact products, the larger part of the sum taken from 1 first
+  const R a = g.re * ur, b = -g.im * ui, c = g.re * ui, d = g.im * ur;
+  const R ea = fma(g.re, ur, -a), eb = fma(-g.im, ui, -b), ec = fma(g.re, ui, -c), ed = fma(g.im, ur, -d);
+  const bool al = a >= b;
+  const R er = ((R(1) - (al ? a : b)) - (al ? b : a)) - (ea + eb), ei = -(c + d) - (ec + ed);
+  h = cmk(g.re * er - g.im * ei, g.re * ei + g.im * er);
+}
+
 template <typename R>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) == 4 ? 3 : 2))) void panel_kernel(const FrontDev* __restrict__ fr, const int* __restrict__ lvl,
                                                     int nlvl, int kb, int half, R* __restrict__ buf,
                                                     const int* __restrict__ ib) {
   // T[j][c]: U[j][c] for the rows, L[c][j] for the columns, zero at and left of the diagonal
-  // and past the tile; gr, gi: 1 / U[j][j] (rows)
+  // and past the tile; g, h: 1 / U[j][j] (rows) and its rest
   __shared__ R Tr[kT][kT], Ti[kT][kT];
-  __shared__ R gr[kT], gi[kT];
+  __shared__ C<R> g[kT], h[kT];
   __shared__ R Bs[kPR][kT + 1];                  // one plane of the rows at a time (two workgroups per CU in FP64)
   const int tid = threadIdx.x, row = tid >> 2, qd = tid & 3;
   const bool lrole = (int)blockIdx.x < half;
@@ -534,9 +550,10 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) =
       Tr[j][k] = in ? vr[u] : R(0);
       Ti[j][k] = in ? vi[u] : R(0);
       if (k == j) {
-        const R den = vr[u] * vr[u] + vi[u] * vi[u];
-        gr[k] = k >= tw ? R(0) : lrole ? vr[u] / den : R(1);
-        gi[k] = k >= tw || !lrole ? R(0) : -vi[u] / den;
+        C<R> gk = cmk(k < tw ? R(1) : R(0), R(0)), hk = cmk(R(0), R(0));
+        if (lrole && k < tw) recip(vr[u], vi[u], gk, hk);
+        g[k] = gk;
+        h[k] = hk;
       }
     }
 #pragma unroll
@@ -555,8 +572,9 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) =
     auto step = [&](auto M, auto Q) {
       constexpr int m0 = decltype(M)::value, q0 = decltype(Q)::value, j = 4 * m0 + q0;
       const R zr = quad_bcast<q0>(br[m0]), zi = quad_bcast<q0>(bi[m0]);
-      const R wr = gr[j], wi = gi[j];
-      const R xr = zr * wr - zi * wi, xi = zr * wi + zi * wr;
+      const C<R> w = g[j], e = h[j];
+      const R xr = fma(zr, w.re, fma(-zi, w.im, fma(zr, e.re, -(zi * e.im))));
+      const R xi = fma(zr, w.im, fma(zi, w.re, fma(zr, e.im, zi * e.re)));
       if (qd == q0) {
         br[m0] = xr;
         bi[m0] = xi;

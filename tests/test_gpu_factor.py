@@ -260,3 +260,34 @@ def test_few_rhs_solves_on_larger_fronts(lib, prec, n):
     for nr in (2, 3, 4):
         assert np.array_equal(sp.solve(_dev(b[:nr])).cpu().numpy(), single[:nr]), nr
     sp.close()
+
+
+@pytest.mark.parametrize("prec", ["c128", "c64"])
+@pytest.mark.parametrize("unit", [1, 1j])
+def test_factor_rows_have_the_rounding_of_a_division(lib, prec, unit):
+    """Rows of L are quotients: with an S of whole numbers (a diagonal d of 3
+    to 199 in every unknown, k d in the rows that couple a separator's points
+    to one of their eliminated neighbours) they are the whole numbers k, and a
+    right-hand side of whole numbers that satisfies the separator's rows
+    leaves exactly nothing there."""
+    from paper_1804_02297_amd.binding import SparseGpu
+    n, nrhs, sep = 5, 6, 2                     # the root separator is the plane i1 = 2
+    g = np.random.Generator(np.random.PCG64(17))
+    d = g.integers(3, 200, (n, n, n, 3)).astype(float)
+    k = g.integers(1, 10, (n, n, 3)).astype(float)
+    rows = np.zeros((n, n, n, 3, 27, 3), complex)
+    b = np.zeros((nrhs, 3, n, n, n), complex)
+    b[:, :, [0, 1, 3, 4]] = g.integers(-9, 10, (nrhs, 3, 4, n, n))
+    for r in range(3):
+        rows[:, :, :, r, 13, r] = unit * d[..., r]
+        rows[sep, :, :, r, 4, r] = unit * k[..., r] * d[sep - 1, :, :, r]      # slot 4: the neighbour at i1 - 1
+        b[:, r, sep] = k[..., r] * b[:, r, sep - 1]
+    sp = SparseGpu(n, rows.reshape(n ** 3, 3, 27, 3), prec=prec)
+    for nr in (1, nrhs):
+        x = sp.solve(_dev(b[:nr])).cpu().numpy()
+        print(f"{prec} {unit} {nr} rhs: {np.count_nonzero(x[:, :, sep])} not zero", flush=True)
+        want = b[:nr] / (unit * np.moveaxis(d, 3, 0))
+        want[:, :, sep] = 0
+        assert np.abs(x - want).max() <= (1e-14 if prec == "c128" else 1e-5) * np.abs(want).max()
+        assert not x[:, :, sep].any()
+    sp.close()
