@@ -68,8 +68,9 @@ constexpr int col_tile(int P, int mode) {
 // Lines are contiguous (index `line` in [0, L)); the transform runs along rows
 // with strides in_rs and out_rs (the contrast and the identity term have
 // stride L).  The last pass reads lines laid out in rows of wrap_ld of which
-// wrap_n are used: line -> (line / wrap_n) wrap_ld + line % wrap_n.  Block = T lines x TPL threads; work item blk = batch * ntiles +
-// tile.  An ordinary launch has one workgroup per item (blk = blockIdx.x); a
+// wrap_n are used: line -> (line / wrap_n) wrap_ld + line % wrap_n.
+// Block = T lines x TPL threads; work item blk = batch * ntiles + tile.  An
+// ordinary launch has one workgroup per item (blk = blockIdx.x); a
 // PERSIST launch has the workgroups the device holds at once, which take
 // blk = blockIdx.x, blockIdx.x + gridDim.x, ... < nblk.  The two are
 // separate instantiations so that the ordinary one keeps its registers (in a
@@ -729,7 +730,7 @@ template <typename R, int P, int NF>
 struct PlaneCfg {
   static constexpr Fac f = col_factors(P);
   static constexpr int TPL = cmax(f.n1, f.n2);
-  static constexpr int JL = TPL <= 4 ? 4 : TPL <= 8 ? 8 : 16;
+  static constexpr int JL = TPL <= 4 ? 4 : 8;
   // a thread per row lane, up to 512; half of them at P = 48 in FP64, where the rows' values,
   // symbol and transforms need more than the 256 registers that six waves leave (194 spilled)
   static constexpr int ROWS = sizeof(R) == 8 && P == 48 ? P / 2 : P;
@@ -737,15 +738,15 @@ struct PlaneCfg {
   static constexpr int CPB = NT / TPL;                       // columns per batch of the dim-2 steps
   static constexpr int W = cmax(NF * P / 2, P + f.n2);
   static constexpr int RS = (W + 7) / 16 * 16 + 8;
-  static constexpr bool FITS = P <= 64 && (P * RS + P) * 2 * (int)sizeof(R) <= 160 * 1024;
+  static constexpr bool FITS = P <= 64 && (P * RS + P) * 2 * (int)sizeof(R) <= 160 * 1024;   // n <= 32: rows not padded
 };
 
+// X: X1 in, Y1 out, [NF B][P][n][n].
 template <typename R, int P, int NF>
-__global__ __launch_bounds__((PlaneCfg<R, P, NF>::NT)) void plane_kernel(const C<R>* X, C<R>* Y,   // may be one array
-                                                                         const C<R>* __restrict__ Kh,
-                                                                         const C<R>* __restrict__ tw, int n, int B,
-                                                                         long in_rs, int out_ld) {
+__global__ __launch_bounds__((PlaneCfg<R, P, NF>::NT)) void plane_kernel(C<R>* X, const C<R>* __restrict__ Kh,
+                                                                         const C<R>* __restrict__ tw, int n, int B) {
   using Cfg = PlaneCfg<R, P, NF>;
+  static_assert(Cfg::TPL <= Cfg::JL, "a row's lanes hold a column each");
   constexpr int N1 = Cfg::f.n1, N2 = Cfg::f.n2, TPL = Cfg::TPL, JL = Cfg::JL, NT = Cfg::NT, CPB = Cfg::CPB,
                 RS = Cfg::RS, H = P / 2 + 1;
   constexpr int KIN = (N2 + 1) / 2;          // t = j + N1 k < n <= P/2
@@ -756,7 +757,7 @@ __global__ __launch_bounds__((PlaneCfg<R, P, NF>::NT)) void plane_kernel(const C
   const int tid = threadIdx.x;
   const int b = blockIdx.x / P, q1 = blockIdx.x % P;
   for (int e = tid; e < P; e += NT) twl[e] = tw[e];
-  auto field = [&](int c) { return c < 3 ? 3 * b + c : 3 * B + b; };
+  auto field = [&](int c) { return X + ((long)(c < 3 ? 3 * b + c : 3 * B + b) * P + q1) * n * n; };   // this plane
   const int ct = tid % CPB, cj = tid / CPB;
   __syncthreads();
   // dim 2 forward: rows i2 < n of the plane in, slots (step 1) and rows q2 (step 3) of LDS out
@@ -765,7 +766,7 @@ __global__ __launch_bounds__((PlaneCfg<R, P, NF>::NT)) void plane_kernel(const C
     const bool live = col < NF * n;
     if (live && cj < N1) {
       const int c = col / n;
-      const C<R>* src = X + ((long)field(c) * P + q1) * in_rs + (col - c * n);
+      const C<R>* src = field(c) + (col - c * n);
       C<R> v[N2];
 #pragma unroll
       for (int k = 0; k < KIN; ++k) {
@@ -899,7 +900,7 @@ __global__ __launch_bounds__((PlaneCfg<R, P, NF>::NT)) void plane_kernel(const C
     __syncthreads();
     if (live && cj < N2) {
       const int c = col / n;
-      C<R>* dst = Y + ((long)(3 * b + c) * P + q1) * n * out_ld + (col - c * n);
+      C<R>* dst = field(c) + (col - c * n);
       C<R> w[N1];
 #pragma unroll
       for (int jj = 0; jj < N1; ++jj) w[jj] = S[(jj * N2 + cj) * RS + col];
@@ -907,7 +908,7 @@ __global__ __launch_bounds__((PlaneCfg<R, P, NF>::NT)) void plane_kernel(const C
 #pragma unroll
       for (int a = 0; a < QOUT; ++a) {
         const int i2 = cj + N2 * a;
-        if (i2 < n) dst[(long)i2 * out_ld] = w[a];
+        if (i2 < n) dst[(long)i2 * n] = w[a];
       }
     }
   }
@@ -1047,13 +1048,12 @@ static ls_status launch_kmul(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int
   return launch_kmul_w<R, P, NF, 1>(X, Kh, tw, n, ld, B, persist, s);
 }
 
-// Passes 2 to 4 as one plane_kernel launch: X1 rows of in_rs in, Y1 [3B][P][n][out_ld] out.
+// Passes 2 to 4 as one plane_kernel launch, in place.
 template <typename R, int P, int NF>
-static ls_status launch_plane(const C<R>* X, C<R>* Y, const C<R>* Kh, const C<R>* tw, int n, int B, long in_rs,
-                              int out_ld, hipStream_t s) {
+static ls_status launch_plane(C<R>* X, const C<R>* Kh, const C<R>* tw, int n, int B, hipStream_t s) {
   if ((long)B * P > 0x7fffffffL) return LS_EINVAL;
-  hipLaunchKernelGGL((plane_kernel<R, P, NF>), dim3((unsigned)(B * P)), dim3(PlaneCfg<R, P, NF>::NT), 0, s, X, Y, Kh,
-                     tw, n, B, in_rs, out_ld);
+  hipLaunchKernelGGL((plane_kernel<R, P, NF>), dim3((unsigned)(B * P)), dim3(PlaneCfg<R, P, NF>::NT), 0, s, X, Kh, tw, n,
+                     B);
   return hipGetLastError() == hipSuccess ? LS_OK : LS_EHIP;
 }
 
@@ -1100,12 +1100,10 @@ static ls_status run_passes(ApplyPlan& ap, const void* x, void* y, int nrhs, con
   LS_TRY((launch_col_rt<R, IO, P, COL_P1>(tn.half_runs & 1, pe, x, X1, m, tw, n, P, ColShape{n2, n2, r1, n3, P * r1},
                                           nb, (R)1, s)));
   LS_MARK(1);
-  C<R>* Y1 = X1;
   if constexpr (PlaneCfg<R, P, 3>::FITS) {
-    // passes 2 to 4 (timed as pass 3), in place when the rows of X1 and Y1 are alike
-    if (r1 != w1) Y1 = X2;
+    // passes 2 to 4 (timed as pass 3)
     LS_MARK(2);
-    LS_TRY((launch_plane<R, P, 3>(X1, Y1, kh, tw, n, nrhs, r1, ld, s)));
+    LS_TRY((launch_plane<R, P, 3>(X1, kh, tw, n, nrhs, s)));
     LS_MARK(3);
     LS_MARK(4);
   } else {
@@ -1122,7 +1120,7 @@ static ls_status run_passes(ApplyPlan& ap, const void* x, void* y, int nrhs, con
     LS_MARK(4);
   }
   // pass 5: inverse along dim 1, y = x + v, or y = -K*(m x) when minus_conv
-  LS_TRY((launch_col_rt<R, IO, P, COL_P5>(tn.half_runs & 8, pe, Y1, y, minus_conv ? nullptr : x, tw, P, n,
+  LS_TRY((launch_col_rt<R, IO, P, COL_P5>(tn.half_runs & 8, pe, X1, y, minus_conv ? nullptr : x, tw, P, n,
                                           ColShape{n2, w1, n2, P * w1, n3, n, ld}, nb, minus_conv ? (R)-1 : (R)1, s)));
   LS_MARK(5);
 #undef LS_MARK
@@ -1131,7 +1129,7 @@ static ls_status run_passes(ApplyPlan& ap, const void* x, void* y, int nrhs, con
 
 // The paper's form: passes 1 and 2 on the three fields m x_d and on p.x, the
 // 3x4 multiply in pass 3, passes 4 and 5 on the three results as in the
-// dyadic form.  work34: X1 [4B][P][n^2], X2 [4B][P][P][n], W [B][n^3].
+// dyadic form.  work34: X1 [4B][P][r1] (as Y1 [3B][P][n][ld]), X2 [4B][P][P][ld], W [B][n^3].
 template <typename R, typename IO, int P>
 static ls_status run_passes34(ApplyPlan& ap, const void* x, void* y, int nrhs, const C<R>* m, const C<R>* p,
                               const C<R>* kp, const C<R>* tw, bool minus_conv, hipStream_t s, hipEvent_t* ev) {
@@ -1139,9 +1137,9 @@ static ls_status run_passes34(ApplyPlan& ap, const void* x, void* y, int nrhs, c
   const long n2 = (long)n * n, n3 = n2 * n;
   const int ld = work_ld(n, sizeof(C<R>));
   const long r1 = work_ld2(n, sizeof(C<R>)), w1 = (long)n * ld;
-  C<R>* X1 = ap.work34.as<C<R>>();                         // [4B][P][r1]; as Y1 [3B][P][n][ld]
-  C<R>* X2 = X1 + (long)nrhs * 4 * P * w1;                 // [4B][P][P][ld]
-  C<R>* W = X2 + (long)nrhs * 4 * P * P * ld;              // [B][n^3]
+  C<R>* X1 = ap.work34.as<C<R>>();
+  C<R>* X2 = X1 + (long)nrhs * 4 * P * w1;
+  C<R>* W = X2 + (long)nrhs * 4 * P * P * ld;
   const long nb = (long)nrhs * 3;
 #define LS_MARK(i) \
   if (ev) LS_HIP(hipEventRecord(ev[i], s))
@@ -1153,11 +1151,9 @@ static ls_status run_passes34(ApplyPlan& ap, const void* x, void* y, int nrhs, c
   LS_TRY((launch_col<R, R, P, COL_FWD>(W, X1 + nb * P * r1, nullptr, tw, n, P, ColShape{n2, n2, r1, n3, P * r1}, nrhs,
                                        (R)1, s)));
   LS_MARK(1);
-  C<R>* Y1 = X1;
   if constexpr (PlaneCfg<R, P, 4>::FITS) {
-    if (r1 != w1) Y1 = X2;
     LS_MARK(2);
-    LS_TRY((launch_plane<R, P, 4>(X1, Y1, kp, tw, n, nrhs, r1, ld, s)));
+    LS_TRY((launch_plane<R, P, 4>(X1, kp, tw, n, nrhs, s)));
     LS_MARK(3);
     LS_MARK(4);
   } else {
@@ -1170,7 +1166,7 @@ static ls_status run_passes34(ApplyPlan& ap, const void* x, void* y, int nrhs, c
                                          s)));
     LS_MARK(4);
   }
-  LS_TRY((launch_col<R, IO, P, COL_P5>(Y1, y, minus_conv ? nullptr : x, tw, P, n,
+  LS_TRY((launch_col<R, IO, P, COL_P5>(X1, y, minus_conv ? nullptr : x, tw, P, n,
                                        ColShape{n2, w1, n2, P * w1, n3, n, ld}, nb, minus_conv ? (R)-1 : (R)1, s)));
   LS_MARK(5);
 #undef LS_MARK
