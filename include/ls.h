@@ -117,7 +117,8 @@ typedef struct {
 /* Autotune the apply of prec for batches of nrhs: look the key (GPU, n, P,
  * form, prec, nrhs, max_rhs) up in the plan's tune_cache file; on a miss time the
  * choices on the plan's operator (scratch fields of nrhs, allocated and freed
- * here): every chunk x team count, then each strided pass with half runs in
+ * here), of those that change a launch at the plan's size: every chunk x team
+ * count, then each strided pass with half runs in
  * turn (kept where faster), then persistent launches of the strided passes, of
  * pass 3 and of both; keep the fastest and
  * append it to the cache file (a JSON array, one object per line; rewritten

@@ -137,8 +137,12 @@ ls_status apply_batched(ApplyPlan& ap, const void* x, void* y, int nrhs, ls_prec
 // form y_d = x_d + k^2 G*(m x_d) + G^d*(p.x) (its symbol, p and workspace are
 // built on the first selection).
 ls_status apply_plan_set_form(ApplyPlan& ap, int form, hipStream_t s);
-// Pass-3 team counts the plan's FFT size supports (1 always; 2 and 4 when a
-// team is one wavefront).
-std::vector<int> kmul_team_choices(const ApplyPlan& ap);
+// The launch choices that change something at the plan's FFT size and prec (the
+// other values of ApplyTune are accepted and have no effect).
+struct ApplyChoices {
+  std::vector<int> teams = {1};  // pass-3 teams (2 and 4 where no job straddles two wavefronts)
+  int half_runs = 0, persist = 0;   // bits as in ApplyTune
+};
+ApplyChoices apply_choices(const ApplyPlan& ap, ls_prec prec);
 
 }  // namespace ls

@@ -318,11 +318,30 @@ ls_status apply_plan_set_form(ApplyPlan& ap, int form, hipStream_t s) {
   return LS_OK;
 }
 
-std::vector<int> kmul_team_choices(const ApplyPlan& ap) {
-  const Fac f = col_factors(ap.P);
-  if (job_lanes(cmax(f.n1, f.n2)) == 16) return {1, 2, 4};
-  if (job_lanes(cmax(f.n1, f.n2)) == 32) return {1, 2};
-  return {1};
+template <typename R, int P>
+static ApplyChoices choices_at() {
+  ApplyChoices c;
+  if (has_half_runs<R>(P, COL_P1)) c.half_runs |= 1;
+  if (has_half_runs<R>(P, COL_P5)) c.half_runs |= 8;
+  c.persist = 1;
+  if (PlaneCfg<R, P, 3>::FITS) return c;       // passes 2 to 4 are one launch
+  const int jl = job_lanes(cmax(col_factors(P).n1, col_factors(P).n2));
+  if (jl == 16) c.teams = {1, 2, 4};
+  if (jl == 32) c.teams = {1, 2};
+  if (has_half_runs<R>(P, COL_FWD)) c.half_runs |= 2;
+  if (has_half_runs<R>(P, COL_INV)) c.half_runs |= 4;
+  c.persist |= 2;
+  return c;
+}
+
+ApplyChoices apply_choices(const ApplyPlan& ap, ls_prec prec) {
+  switch (ap.P) {
+#define X(SZ) \
+  case SZ: return prec == LS_C128 ? choices_at<double, SZ>() : choices_at<float, SZ>();
+    LS_FOR_SIZES(X)
+#undef X
+  }
+  return ApplyChoices{};
 }
 
 ls_status apply_run(ApplyPlan& ap, const void* x, void* y, int nrhs, ls_prec prec, hipStream_t s,

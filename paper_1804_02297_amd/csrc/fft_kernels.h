@@ -981,13 +981,18 @@ static ls_status launch_col(const void* in, void* out, const void* aux, const C<
   return hipGetLastError() == hipSuccess ? LS_OK : LS_EHIP;
 }
 
-// launch_col with the run length chosen at run time (half runs only where the
-// default run holds at least 16 lines and P >= 64; elsewhere the default)
+// Half runs exist where the default run holds at least 16 lines and P >= 64.
+template <typename R>
+constexpr bool has_half_runs(int P, int mode) {
+  return P >= 64 && col_tile<R>(P, mode) >= 16;
+}
+
+// launch_col with the run length chosen at run time
 template <typename R, typename IO, int P, int MODE>
 static ls_status launch_col_rt(bool half, bool persist, const void* in, void* out, const void* aux, const C<R>* tw,
                                int rows_in, int rows_out, const ColShape& c, long nbatch, R scale,
                                hipStream_t s) {
-  if constexpr (P >= 64 && col_tile<R>(P, MODE) >= 16) {
+  if constexpr (has_half_runs<R>(P, MODE)) {
     if (half)
       return launch_col<R, IO, P, MODE, true, true>(in, out, aux, tw, rows_in, rows_out, c, nbatch, scale, s,
                                                     persist);

@@ -16,8 +16,8 @@
 //     item, and a workgroup that waits for it idles its CU unless other
 //     workgroups are resident there, so it can prefer the ordinary grid
 //     where the strided passes gain).
-// Where passes 2 to 4 are one launch (P <= 64), only the chunk and the choices
-// of passes 1 and 5 have an effect.
+// Only choices that change a launch are tried (apply_choices): where passes 2 to
+// 4 are one launch (P <= 64), the chunk and those of passes 1 and 5.
 // The first two are searched jointly, then each pass's run length is halved
 // in turn and kept where it is faster, then the three persistent settings are
 // tried on the result; the three fastest choices are finally timed again,
@@ -170,7 +170,7 @@ ls_status apply_tune(ApplyPlan& ap, const std::string& cache, int nrhs, ls_prec 
   const int cmax = std::min(nrhs, ap.max_rhs);
   for (int c = 1; c < cmax; c *= 2) chunks.push_back(c);
   chunks.push_back(cmax);
-  const std::vector<int> teams = kmul_team_choices(ap);
+  const ApplyChoices can = apply_choices(ap, prec);
   ls_status st = LS_OK;
   double best = 1e300;
   ApplyTune pick = saved;
@@ -200,15 +200,16 @@ ls_status apply_tune(ApplyPlan& ap, const std::string& cache, int nrhs, ls_prec 
   };
   // 1. rhs per launch set x pass-3 teams
   for (size_t ci = 0; ci < chunks.size(); ++ci)
-    for (size_t wi = 0; wi < teams.size(); ++wi) {
-      if (teams[wi] > chunks[ci]) continue;       // a team needs its own right-hand side
+    for (const int w : can.teams) {
+      if (w > chunks[ci]) continue;               // a team needs its own right-hand side
       ApplyTune t;
       t.chunk = chunks[ci];
-      t.kmul_w = teams[wi];
+      t.kmul_w = w;
       trial(t);
     }
   // 2. half runs, one strided pass at a time
   for (int bit = 1; bit <= 8; bit <<= 1) {
+    if (!(can.half_runs & bit)) continue;
     ApplyTune t = pick;
     t.half_runs |= bit;
     trial(t);
@@ -217,6 +218,7 @@ ls_status apply_tune(ApplyPlan& ap, const std::string& cache, int nrhs, ls_prec 
   {
     const ApplyTune base = pick;
     for (int q = 1; q <= 3; ++q) {
+      if (q & ~can.persist) continue;
       ApplyTune t = base;
       t.persist = q;
       trial(t);

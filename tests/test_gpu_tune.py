@@ -135,3 +135,17 @@ def test_tune_refuses_the_paper_form(lib, tmp_path):
     plan.set_form("dyadic")
     assert plan.tune(4, "c64")["from_cache"] == 0
     plan.close()
+
+
+@pytest.mark.parametrize("n,prec,tried", [(16, "c64", 3 + 0 + 1), (16, "c128", 3 + 0 + 1), (32, "c64", 3 + 2 + 1),
+                                          (32, "c128", 3 + 2 + 1)])
+def test_tune_times_what_changes_a_launch(lib, n, prec, tried):
+    """Where the dim-2 and dim-3 passes are one kernel, the tuner tries the
+    right-hand sides per launch set (1, 2, 4), the run length of passes 1 and 5
+    (P = 64) and their persistent launch, and nothing else."""
+    plan = _plan(n, 4)
+    info = plan.tune(4, prec)
+    print(n, plan.P, info, flush=True)
+    assert info["n_tried"] == tried
+    assert info["kmul_w"] == 1 and info["half_runs"] & 6 == 0 and info["persist"] & 2 == 0
+    plan.close()
