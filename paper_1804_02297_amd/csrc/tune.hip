@@ -27,9 +27,11 @@
 // of about 2 %), the final three 2 x 30 times.
 //
 // Cache: a JSON array, one object per line,
-//   {"key": "<arch>|cu=<CUs>|v=3|n=<n>|P=<P>|form=<f>|prec=<p>|nrhs=<b>|max_rhs=<m>",
+//   {"key": "<arch>|cu=<CUs>|v=4|n=<n>|P=<P>|form=<f>|prec=<p>|nrhs=<b>|max_rhs=<m>",
 //    "chunk": c, "kmul_w": w, "half_runs": r, "persist": q, "ms_per_rhs": t}
 // read before timing (a hit skips it) and rewritten with the new entry after.
+// v changes with the kernels the choices were timed on, so entries of older
+// ones are not taken.
 #include <algorithm>
 #include <cstdio>
 #include <cstring>
@@ -55,7 +57,7 @@ std::string tune_key(const ApplyPlan& ap, int nrhs, ls_prec prec) {
     cus = prop.multiProcessorCount;
   }
   char buf[256];
-  std::snprintf(buf, sizeof buf, "%s|cu=%d|v=3|n=%d|P=%d|form=%d|prec=%d|nrhs=%d|max_rhs=%d", arch.c_str(), cus,
+  std::snprintf(buf, sizeof buf, "%s|cu=%d|v=4|n=%d|P=%d|form=%d|prec=%d|nrhs=%d|max_rhs=%d", arch.c_str(), cus,
                 ap.n, ap.P, ap.form, (int)prec, nrhs, ap.max_rhs);
   return buf;
 }

@@ -149,3 +149,18 @@ def test_tune_times_what_changes_a_launch(lib, n, prec, tried):
     assert info["n_tried"] == tried
     assert info["kmul_w"] == 1 and info["half_runs"] & 6 == 0 and info["persist"] & 2 == 0
     plan.close()
+
+
+def test_tune_takes_no_entry_of_older_kernels(lib, tmp_path):
+    """A cache file written for earlier kernels is kept, and not believed."""
+    cache = str(tmp_path / "tune.json")
+    plan = _plan(16, 2, cache)
+    plan.tune(2, "c64")
+    text = open(cache).read()
+    key = json.loads(text)[0]["key"]
+    old = "|".join("v=3" if f.startswith("v=") else f for f in key.split("|"))
+    open(cache, "w").write(text.replace(key, old))
+    assert plan.tune(2, "c64")["from_cache"] == 0
+    assert [e["key"] for e in json.load(open(cache))] == [old, key]
+    assert plan.tune(2, "c64")["from_cache"] == 1
+    plan.close()
