@@ -724,7 +724,7 @@ __global__ void pdot_kernel(const C<IO>* __restrict__ x, const C<R>* __restrict_
 // most 3.4 MB in FP64 at P = 64).  Above P = 64 (the LDS limit in FP64; at P = 96 in
 // FP32, one workgroup per CU, it gained 6% for 16 rhs and lost 17% for one)
 // the separate passes run.  Whole apply, complex128, against the three passes:
-// n = 16 one rhs 22.4 -> 17.4 us (three launches instead of five), 16 rhs
+// n = 16 one rhs 22.4 -> 16.8 us (three launches instead of five), 16 rhs
 // 102 -> 24 us; n = 32 16 rhs 210 -> 111 us (complex64 138 -> 60).
 template <typename R, int P, int NF>
 struct PlaneCfg {
