@@ -140,8 +140,9 @@ ls_status ls_plan_set_tune(ls_plan* plan, ls_prec prec, int chunk, int kmul_w, i
  * same kernels and result as ls_apply, with the pass intermediates in a
  * fixed 128 MiB device array that the library holds on every GPU it runs
  * on, instead of the plan's workspace.  No allocation of any kind happens in
- * the call.  One rhs needs 3 (P n^2 + P^2 n) complex values of 8 (LS_C64,
- * LS_MIXED) or 16 (LS_C128) bytes, P the plan's FFT length; larger batches
+ * the call.  One rhs needs 3 (P n + P^2) n' complex values of 8 (LS_C64,
+ * LS_MIXED) or 16 (LS_C128) bytes, P the plan's FFT length and n' = n, above
+ * n = 32 rounded up to whole 128-byte lines (16 or 8 values); larger batches
  * run in chunks that fit, and nrhs is not limited by max_rhs.  LS_ENOMEM
  * when one rhs needs more than 128 MiB (e.g. n = 96 in complex128, n = 128
  * in complex64); LS_ESTATE in the paper's form.  All calls on one GPU share

@@ -370,7 +370,11 @@ __global__ __launch_bounds__(256) void diag_kernel(const FrontDev* __restrict__ 
 // level's fronts (grid.x fronts, grid.y tiles), for the solves' super-blocks.
 // Both advance together, one row of each per barrier, as rank-1 updates of
 // register tiles (thread (ti, tj) of 16 x 16 owns rows ti + 16 a, columns
-// tj + 16 b).  About 45 us a launch whatever its size, once per level.
+// tj + 16 b).  48 dependent steps: about 45 us for a
+// launch that the chip holds at once, one a level (FP64, the nine levels of an
+// n = 29 factor: 54 us on average).  40 KB of LDS in FP64 let four workgroups
+// share a CU, so a level of more than about 1000 tiles takes that several times
+// over (2-D n = 959: 268 us on average).
 template <typename R>
 __global__ __launch_bounds__(256) void tile_inverse_kernel(const FrontDev* __restrict__ fr,
                                                            const int* __restrict__ lvl, int nlvl,
@@ -1675,8 +1679,15 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) =
 // launch waits for.  Every output keeps the order of products of the LDS
 // kernels (K ascending in steps of four into the same accumulators), so blocks
 // of any size above kGemvRhs agree bit for bit.
-// Measured, 16 rhs: complex128 preconditioner apply at n = 48 25.4 -> 8.4 ms; a launch at the top of the
-// tree 23.5 (FP64) and 17 us (FP32) -> 14.7 and 8 us.
+// Measured, preconditioner apply (us), with this kernel and with the LDS kernels:
+//              n = 48 complex128   n = 48 complex64   2-D n = 479 complex128
+//   5 rhs        7506 / 24729        3988 / 10100       2263 / 7427
+//   16 rhs       8159 / 25311        4341 / 10455       2836 / 7967
+//   17 rhs      10678 / 26159        6352 / 10890       3597 / 8408
+//   32 rhs      11127 / 27362        6639 / 11179       4047 / 9093
+// so every count from 5 to 32 takes it (17 and up two tiles of 16); 33 rhs take
+// the LDS kernels, 27409 / 11653 / 9204.  A launch at the top of the tree, 16
+// rhs: 23.5 (FP64) and 17 us (FP32) -> 14.7 and 8 us.
 constexpr int kThinRhs = 32;
 constexpr int kThinPad = 256;   // factor values past the end that thin_kernel may read
 // Four consecutive values from p (aligned to one value only), 16 bytes a load.
@@ -1935,7 +1946,11 @@ __global__ __launch_bounds__(SPLIT ? 128 : 256) __attribute__((amdgpu_waves_per_
 // is uniform, so loads and LDS reads are addressed by constant offsets (with a
 // clamp per load the kernels were bound by issuing address arithmetic); the
 // zero blocks of M and H are not read (thin_kernel).  2-D preconditioner apply, n = 479,
-// one rhs: 1450 to 923 us, the leaf level's three launches 525 to 355 us.
+// one rhs: 1450 to 923 us, the leaf level's three launches 525 to 355 us.  Up to
+// four rhs, where thin_kernel multiplies mostly zero columns: apply at n = 48,
+// complex128 / complex64, one rhs 4102 / 2483 us (thin_kernel 7300 / 3780), four
+// 5398 / 3309 (7465 / 3895), five by thin_kernel 7506 / 3988; 2-D n = 479
+// complex128 one rhs 935 (2104), four 1249 (2220), five 2263.
 constexpr int kGemvRhs = 4;
 constexpr int kGemvLanes = 16;   // lanes per row: four rows per wave, 128-byte row segments per load
 constexpr int kGemvRows = 256 / kGemvLanes;   // rows per workgroup: more workgroups per front
