@@ -36,7 +36,7 @@ KERNEL_NAMES = ["col_fft_kernel (mode 0)", "col_fft_kernel (mode 1)", "kmul_kern
 # only while the apply sources are the ones that were profiled.
 MEASURED_TRAFFIC = {
     "sources": ["fft_kernels.h", "fft_apply.hip", "fft_inst_e.hip", "common.h", "cplx.h"],
-    "sha256": "ed6421d00571305dcaf4c84f86c327986cc05dbe81b48098106f348e98caa637",
+    "sha256": "04a41da70944d5c2e92a6dc3e8fda7dfcf09ba348d7592ceb094f81fd9faa3ad",
     "workload": (128, 8, "c64"),
     "bytes": 3.3265e9,
     "profile": "profiles/ls_apply_n128_b8_c64.md",
@@ -47,9 +47,9 @@ MEASURED_TRAFFIC = {
 # reported only while the sources are the measured ones.
 MEASURED_TRAFFIC_2D = {
     "sources": ["twod.hip", "twod.h", "cplx.h"],
-    "sha256": "79f470a5333080f818b0932fa8a1c570d100ee38e4f1a8931ef66fdc2aa9aec8",
+    "sha256": "2eb5d907012c4dc2ac7db1af1f459eb0540ea113940db01f3e4dc7de863ecde6",
     "workload": (959, 8, "c64"),
-    "bytes": 9.343e8,
+    "bytes": 9.368e8,
     "profile": "profiles/ls2_apply_n959_b8_c64.md",
 }
 

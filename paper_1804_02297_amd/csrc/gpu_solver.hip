@@ -475,10 +475,11 @@ constexpr int kPR = 64;   // 256 threads load kPR x kT values in kT / 4 rounds
 // one lane's product, a broadcast inside the quad and at most twelve updates a
 // lane; the tile is read from LDS a quad's 4 values at a time, the reciprocals
 // of the diagonal are formed once, and every load is in flight before the first
-// wait.  FP64, average launch of the n = 29 factor: 37 us (152 us with one
+// wait.  FP64, average launch of the n = 29 factor: 40 us (152 us with one
 // thread per row and the row in LDS).
 // A reciprocal is held as the sum of two values (recip): a product with the
-// rounded reciprocal alone has one rounding more per entry of L than a division.
+// rounded reciprocal alone has one rounding more per entry of L than a division
+// (and took 38 us).
 template <int Q>
 __device__ __forceinline__ float quad_bcast(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), Q * 0x55, 0xF, 0xF, false));
