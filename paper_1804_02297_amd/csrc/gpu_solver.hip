@@ -475,11 +475,12 @@ constexpr int kPR = 64;   // 256 threads load kPR x kT values in kT / 4 rounds
 // one lane's product, a broadcast inside the quad and at most twelve updates a
 // lane; the tile is read from LDS a quad's 4 values at a time, the reciprocals
 // of the diagonal are formed once, and every load is in flight before the first
-// wait.  FP64, average launch of the n = 29 factor: 40 us (152 us with one
+// wait.  FP64, average launch of the n = 29 factor: 38 us (152 us with one
 // thread per row and the row in LDS).
 // A reciprocal is held as the sum of two values (recip): a product with the
-// rounded reciprocal alone has one rounding more per entry of L than a division
-// (and took 38 us).
+// rounded reciprocal alone has one rounding more per entry of L than a division.
+// A lane forms each once, while the rows are on their way through LDS (formed
+// where the tile is stored, by the lane that holds the value, 40 us).
 template <int Q>
 __device__ __forceinline__ float quad_bcast(float v) {
   return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), Q * 0x55, 0xF, 0xF, false));
@@ -554,12 +555,7 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) =
       const bool in = k > j && k < tw;
       Tr[j][k] = in ? vr[u] : R(0);
       Ti[j][k] = in ? vi[u] : R(0);
-      if (k == j) {
-        C<R> gk = cmk(k < tw ? R(1) : R(0), R(0)), hk = cmk(R(0), R(0));
-        if (lrole && k < tw) recip(vr[u], vi[u], gk, hk);
-        g[k] = gk;
-        h[k] = hk;
-      }
+      if (k == j) g[k] = cmk(vr[u], vi[u]);
     }
 #pragma unroll
     for (int pl = 0; pl < 2; ++pl) {
@@ -571,6 +567,12 @@ __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(sizeof(R) =
       __syncthreads();
 #pragma unroll
       for (int m = 0; m < kT / 4; ++m) (pl ? bi : br)[m] = Bs[row][4 * m + qd];
+      if (pl == 0 && tid < kT) {                  // the diagonal's reciprocals, a lane each
+        C<R> gk = cmk(tid < tw ? R(1) : R(0), R(0)), hk = cmk(R(0), R(0));
+        if (lrole && tid < tw) recip(g[tid].re, g[tid].im, gk, hk);
+        g[tid] = gk;
+        h[tid] = hk;
+      }
       __syncthreads();
     }
     // step j = 4 M + Q: x_j = f_j / T_jj, then f_c -= x_j T[j][c] for c > j (T is zero elsewhere)
