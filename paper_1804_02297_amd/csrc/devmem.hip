@@ -30,6 +30,7 @@ namespace {
 constexpr size_t kMinBlock = 1ull << 20;
 constexpr size_t kMaxHeld = 8ull << 30;
 constexpr int kPart = 16;
+constexpr std::chrono::milliseconds kFresh(100);   // the query takes 5 us, a set-up releases some 30 blocks
 constexpr std::chrono::seconds kIdle(5);   // a factor of the next medium, its stencils and the solves before it
 
 struct HipDev {
@@ -62,7 +63,7 @@ struct HipDev {
 };
 
 BlockStore<HipDev>& store() {
-  return ProcessStore<HipDev>::get(HipDev(), StoreLimits{kMinBlock, kMaxHeld, kPart, kIdle});
+  return ProcessStore<HipDev>::get(HipDev(), StoreLimits{kMinBlock, kMaxHeld, kPart, kFresh, kIdle});
 }
 
 }  // namespace

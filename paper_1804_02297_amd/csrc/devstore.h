@@ -18,7 +18,8 @@ namespace ls {
 struct StoreLimits {
   size_t min_block;                    // smaller blocks are not held
   size_t max_held;                     // bytes held over all devices, at most,
-  int part;                            // and of the memory that is free on the device: one part-th
+  int part;                            // and of the memory that is free on the device: one part-th,
+  std::chrono::milliseconds fresh;     // as it was at most this long ago
   std::chrono::milliseconds idle;      // a block not taken again within this goes back
 };
 
@@ -66,19 +67,23 @@ class BlockStore {
 
   // A block from take(): held, or freed where it is too small, too large or in use on another device.
   void give(void* p, size_t bytes, int dev) {
-    size_t most = 0;
-    if (bytes >= lim_.min_block && bytes <= lim_.max_held && dev_.wait(dev))
-      most = std::min(lim_.max_held, dev_.spare() / lim_.part);
     Gone out;
     bool held = false;
-    if (bytes <= most) {
+    if (bytes >= lim_.min_block && bytes <= lim_.max_held && dev_.wait(dev)) {
       std::lock_guard<std::mutex> lock(mu_);
-      if (started_ && !stop_) {
+      const auto now = Clock::now();
+      if (dev != spare_dev_ || now - spare_at_ >= lim_.fresh) {
+        spare_ = dev_.spare();
+        spare_dev_ = dev;
+        spare_at_ = now;
+      }
+      const size_t most = std::min(lim_.max_held, spare_ / lim_.part);
+      if (started_ && !stop_ && bytes <= most) {
         while (n_ == kSlots || (n_ && bytes_ + bytes > most)) oldest_to(out);
-        held_[n_++] = Block{p, bytes, dev, Clock::now()};
+        held_[n_++] = Block{p, bytes, dev, now};
         bytes_ += bytes;
         held = true;
-        wake_.notify_one();
+        if (asleep_) wake_.notify_one();         // else the thread waits for an older block's time
       }
     }
     if (!held) dev_.free(p);
@@ -159,7 +164,9 @@ class BlockStore {
     std::unique_lock<std::mutex> lock(mu_);
     while (!stop_) {
       if (!n_) {
+        asleep_ = true;
         wake_.wait(lock);
+        asleep_ = false;
         continue;
       }
       const auto due = held_[0].since + lim_.idle;
@@ -181,10 +188,13 @@ class BlockStore {
   Block held_[kSlots];                 // oldest first
   int n_ = 0;
   size_t bytes_ = 0;
+  size_t spare_ = 0;                   // bytes free on spare_dev_ at spare_at_
+  int spare_dev_ = -1;
+  Clock::time_point spare_at_;
   int freeing_ = 0;                    // blocks taken out of the store and not yet freed
   std::condition_variable freed_, wake_;
   std::thread thread_;
-  bool started_ = false, stop_ = false;
+  bool started_ = false, stop_ = false, asleep_ = false;
 };
 
 // The process's one store of Dev, never destroyed (buffers may be released after the statics are
@@ -196,7 +206,7 @@ class ProcessStore {
   static BlockStore<Dev>& get(Dev dev, StoreLimits lim) {
     static const bool made = [&] {
       at() = new BlockStore<Dev>(dev, lim);
-      in_child() = new BlockStore<Dev>(dev, StoreLimits{lim.min_block, 0, 1, lim.idle});
+      in_child() = new BlockStore<Dev>(dev, StoreLimits{lim.min_block, 0, 1, lim.fresh, lim.idle});
       if (std::atexit([] { at().load()->stop(); }) != 0 ||
           pthread_atfork(nullptr, nullptr, [] { at() = in_child().load(); }) != 0)
         at() = in_child().load();

@@ -127,12 +127,12 @@ struct CardDev {
   static void enter() {}
 };
 using Store = ls::BlockStore<CardDev>;
-constexpr std::chrono::milliseconds kLong(60000);
+constexpr std::chrono::milliseconds kNow(0), kLong(60000);
 
 // A destructor gives a buffer back: that works, and throws nothing, without host memory.
 void give_without_host_memory() {
   Card card;
-  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, 1, kLong});
+  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, 1, kNow, kLong});
   size_t got[100];
   int dev;
   void* p[100];                         // (the first take starts the store's thread)
@@ -149,7 +149,7 @@ void give_without_host_memory() {
 // that fails has everything held given back.
 void bounds_of_the_store() {
   Card card;
-  Store s(CardDev{&card}, ls::StoreLimits{16, 1000, 1, kLong});
+  Store s(CardDev{&card}, ls::StoreLimits{16, 1000, 1, kNow, kLong});
   size_t got;
   int dev;
   void* a = s.take(400, &got, &dev);
@@ -191,7 +191,7 @@ bool comes_true(const std::function<bool()>& f) {
 void allocation_during_a_drain() {
   Card card;
   card.room = 1000;
-  Store s(CardDev{&card}, ls::StoreLimits{16, 1000, 1, kLong});
+  Store s(CardDev{&card}, ls::StoreLimits{16, 1000, 1, kNow, kLong});
   size_t got, got2;
   int dev, dev2;
   s.give(s.take(900, &got, &dev), got, dev);
@@ -213,7 +213,7 @@ void allocation_during_a_drain() {
 // A block that nobody takes again goes back without any further call, and one that is taken in time stays.
 void given_back_when_idle() {
   Card card;
-  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, 1, std::chrono::milliseconds(200)});
+  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, 1, kNow, std::chrono::milliseconds(200)});
   size_t got, got2;
   int dev;
   void *p = s.take(1000, &got, &dev), *q = s.take(500, &got2, &dev);
@@ -235,7 +235,7 @@ void given_back_when_idle() {
 // What is held leaves most of a nearly full card to others; release() and stop() leave nothing.
 void given_back_on_request() {
   Card card;
-  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, 4, kLong});
+  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, 4, kNow, kLong});
   size_t got;
   int dev;
   void* a = s.take(1000, &got, &dev);
@@ -254,12 +254,29 @@ void given_back_on_request() {
   check(card.used == 0, "nothing held after stop");
 }
 
+// The free memory is asked for again once the answer is old, and not before.
+void free_memory_is_asked_for_again() {
+  Card card;
+  Store s(CardDev{&card}, ls::StoreLimits{16, 4096, 4, std::chrono::milliseconds(100), kLong});
+  size_t got;
+  int dev;
+  void *a = s.take(1000, &got, &dev), *b = s.take(900, &got, &dev);
+  card.spare = 8000;
+  s.give(a, 1000, 0);
+  card.spare = 40;
+  s.give(b, 900, 0);
+  check(card.used == 1900, "both held by the first answer");
+  std::this_thread::sleep_for(std::chrono::milliseconds(150));
+  s.give(s.take(1000, &got, &dev), 1000, 0);
+  check(card.used == 900, "not held by the second");
+}
+
 // A forked child, which has no thread to free blocks, holds none and ends as usual.
 void forked_child() {
 #if !__has_feature(thread_sanitizer)
   static Card card;
   const auto get = []() -> Store& {
-    return ls::ProcessStore<CardDev>::get(CardDev{&card}, ls::StoreLimits{16, 4096, 1, kLong});
+    return ls::ProcessStore<CardDev>::get(CardDev{&card}, ls::StoreLimits{16, 4096, 1, kNow, kLong});
   };
   size_t got, got2;
   int dev;
@@ -290,7 +307,7 @@ void forked_child() {
 // Threads that take and give at once: every block is one thread's alone.
 void many_threads() {
   Card card;
-  Store s(CardDev{&card}, ls::StoreLimits{16, 3000, 1, kLong});
+  Store s(CardDev{&card}, ls::StoreLimits{16, 3000, 1, kNow, kLong});
   std::vector<std::thread> ts;
   for (int t = 0; t < 4; ++t)
     ts.emplace_back([&s, t] {
@@ -314,6 +331,7 @@ int main() {
   allocation_during_a_drain();
   given_back_when_idle();
   given_back_on_request();
+  free_memory_is_asked_for_again();
   forked_child();
   many_threads();
   give_without_host_memory();
