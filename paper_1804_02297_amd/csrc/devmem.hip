@@ -41,7 +41,14 @@ struct HipDev {
     (void)hipGetLastError();
     return nullptr;
   }
-  static void free(void* p) { (void)hipFree(p); }
+  // also while this or another thread captures a graph, where hipFree is refused otherwise and the
+  // block would be lost
+  static void free(void* p) {
+    hipStreamCaptureMode m = hipStreamCaptureModeRelaxed;
+    const bool set = hipThreadExchangeStreamCaptureMode(&m) == hipSuccess;
+    (void)hipFree(p);
+    if (set) (void)hipThreadExchangeStreamCaptureMode(&m);
+  }
   static bool wait(int dev) {
     int cur = -1;
     if (!current(&cur) || cur != dev) return false;
@@ -54,11 +61,6 @@ struct HipDev {
     if (hipMemGetInfo(&bytes, &total) == hipSuccess) return bytes;
     (void)hipGetLastError();
     return 0;
-  }
-  // hipFree while another thread captures a graph
-  static void enter() {
-    hipStreamCaptureMode m = hipStreamCaptureModeRelaxed;
-    (void)hipThreadExchangeStreamCaptureMode(&m);
   }
 };
 

@@ -24,8 +24,8 @@ struct StoreLimits {
 };
 
 // Dev: bool current(int* dev), void* alloc(size_t), void free(void*), bool wait(int dev) (true once
-// nothing runs on device dev and it is the current one), size_t spare() (bytes free on the current
-// device) and void enter() (first call on the store's own thread).
+// nothing runs on device dev and it is the current one) and size_t spare() (bytes free on the current
+// device); alloc and free on any thread.
 //
 // Blocks that stay too long are freed by a thread of the store, which the first take() starts, so they
 // come back without any further call.  give() allocates no host memory: destructors call it.
@@ -160,7 +160,6 @@ class BlockStore {
     (void)pthread_sigmask(SIG_SETMASK, &old, nullptr);
   }
   void watch() {
-    dev_.enter();
     std::unique_lock<std::mutex> lock(mu_);
     while (!stop_) {
       if (!n_) {

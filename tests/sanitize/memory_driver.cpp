@@ -124,7 +124,6 @@ struct CardDev {
   }
   bool wait(int d) const { return d == dev; }
   size_t spare() const { return card->spare; }
-  static void enter() {}
 };
 using Store = ls::BlockStore<CardDev>;
 constexpr std::chrono::milliseconds kNow(0), kLong(60000);

@@ -74,9 +74,10 @@ def test_memory_of_a_destroyed_plan_comes_back(lib):
         assert _comes_back(before - used // 16, 1 if ask else 30)
 
 
-def test_memory_comes_back_during_capture(lib):
-    """Blocks that go back while this thread captures a graph: they do, and the
-    graph replays as the eager call."""
+@pytest.mark.parametrize("ask", [False, True])
+def test_memory_comes_back_during_capture(lib, ask):
+    """Blocks that go back while this thread captures a graph, by themselves or
+    on request: they do, and the graph replays as the eager call."""
     from paper_1804_02297_amd.binding import release_memory
     n = 16
     plan, _, _ = _solve(n, 1, "c128")
@@ -89,7 +90,7 @@ def test_memory_comes_back_during_capture(lib):
     g = torch.cuda.CUDAGraph()
     with torch.cuda.graph(g):
         plan.apply(x, y)
-        time.sleep(8)
+        release_memory() if ask else time.sleep(8)
     assert _comes_back(before - (64 << 20))
     for seed in (7, 8, 9):
         x.copy_(torch.from_numpy(I.random_field(2, n, seed)))
